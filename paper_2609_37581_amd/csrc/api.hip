@@ -52,8 +52,10 @@ trevs_status record(void* const* events, int slot, hipStream_t s) {
 
 // ------------------------------------------------------------------ stage 1
 struct PrellmLayout {
-  size_t row_stats, inv_tnorm, sal, rel, stats, rel_part, pivots, gram, dist, inv_norm, total;
+  size_t row_stats, inv_tnorm, sal, rel, stats, rel_part, total;
+  size_t inv_norm, pivots, ctrl, picks, gram, pick_part, rest, mx, dist, cand, cand_dist;  // diversity set
   RelPlan rel_plan;
+  PickPlan picks_plan;
 };
 
 trevs_status validate_prellm(const trevs_prellm_args* a) {
@@ -125,16 +127,32 @@ PrellmLayout prellm_layout(const trevs_prellm_args* a) {
   L.rel_plan = relevance_plan(a->B, a->N, a->M_max, a->d * elem_bytes(a->dtype));
   L.rel_part = off;  // partial products of a feature-dimension split
   off = align_up(off + L.rel_plan.part_floats() * sizeof(float));
-  L.pivots = L.gram = L.dist = L.inv_norm = off;
-  if (a->k_div > 0) {  // farthest point sampling: pivot list, Gram matrices, distances
-    L.pivots = off;
-    off = align_up(off + (size_t)a->B * (a->k_keep - a->k_div) * sizeof(int32_t));
-    L.gram = off;
-    off = align_up(off + (size_t)a->B * a->N * a->N * sizeof(float));
-    L.dist = off;
-    off = align_up(off + (size_t)fps_init_splits(a->k_keep - a->k_div) * a->B * a->N * sizeof(float));
-    L.inv_norm = off;
-    off = align_up(off + (size_t)a->B * a->N * sizeof(float));
+  L.inv_norm = L.pivots = L.ctrl = L.picks = L.gram = L.pick_part = off;
+  L.rest = L.mx = L.dist = L.cand = L.cand_dist = off;
+  L.picks_plan = PickPlan{};
+  if (a->k_div > 0) {
+    const int K_r = a->k_keep - a->k_div;
+    const size_t B = a->B, N = a->N, R = N - K_r;
+    L.picks_plan = pick_plan(a->B, a->N, K_r, a->k_div, a->dtype, a->d * elem_bytes(a->dtype));
+    const PickPlan& p = L.picks_plan;
+    auto take = [&](size_t& at, size_t n) {  // n 4-byte words
+      at = off;
+      off = align_up(off + n * 4);
+    };
+    take(L.inv_norm, B * N);
+    take(L.pivots, B * K_r);
+    take(L.ctrl, B * kPickCtrl);
+    take(L.picks, B * a->k_div);
+    take(L.gram, B * p.gram_floats(a->N));
+    if (p.rounds == 0) {
+      take(L.pick_part, p.n_psplit * B * N);
+    } else {
+      take(L.rest, B * R);
+      take(L.mx, p.n_mx * B * R);
+      take(L.dist, B * N);
+      take(L.cand, B * p.C);
+      take(L.cand_dist, B * p.C);
+    }
   }
   L.total = off;
   return L;
@@ -450,6 +468,7 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
   ra.split_slabs = rp.split_slabs;
   ra.part = reinterpret_cast<float*>(w + L.rel_part);
   ra.zpart = ra.part + (size_t)rp.n_split * a->B * a->M_max * a->N;
+  ra.inv_norm = a->k_div > 0 ? reinterpret_cast<float*>(w + L.inv_norm) : nullptr;
   TREVS_TRY(record(a->events, 2, s));
   TREVS_HIP(launch_relevance(ra, rp, a->dtype, s));
   TREVS_TRY(record(a->events, 3, s));
@@ -486,33 +505,35 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
   sa.K = K_r;
   sa.kept_idx = a->k_div > 0 ? pivots : a->kept_idx;
   sa.K_t = budget_text_count(a->textual_ratio, K_r);
+  sa.rest = L.picks_plan.rounds > 0 ? reinterpret_cast<int32_t*>(w + L.rest) : nullptr;
+  sa.pick_ctrl = a->k_div > 0 ? reinterpret_cast<int32_t*>(w + L.ctrl) : nullptr;
   TREVS_TRY(record(a->events, 6, s));
   if (budget)
     TREVS_HIP(launch_budget_select(sa, a->B, s));
   else
     TREVS_HIP(launch_prellm_select(sa, a->B, s));
   if (a->k_div > 0) {
-    GramArgs ga;
-    ga.Z = a->vis_feats;
-    ga.B = a->B;
-    ga.N = a->N;
-    ga.row_bytes = a->d * e;
-    ga.n_tiles = (a->N + 127) / 128;
-    ga.G = reinterpret_cast<float*>(w + L.gram);
-    ga.inv_norm = reinterpret_cast<float*>(w + L.inv_norm);
-    FpsArgs fa;
-    fa.G = ga.G;
-    fa.pivots = pivots;
-    fa.N = a->N;
-    fa.K_r = K_r;
-    fa.K_d = a->k_div;
-    fa.B = a->B;
-    fa.n_psplit = fps_init_splits(K_r);
-    fa.dist = reinterpret_cast<float*>(w + L.dist);
-    fa.inv_norm = reinterpret_cast<float*>(w + L.inv_norm);
-    fa.kept_idx = a->kept_idx;
-    fa.div_idx = a->div_idx;
-    TREVS_HIP(launch_fps(fa, ga, a->dtype, a->B, s));
+    PickArgs pa;
+    pa.p = L.picks_plan;
+    pa.B = a->B;
+    pa.N = a->N;
+    pa.K_r = K_r;
+    pa.K_d = a->k_div;
+    pa.R = a->N - K_r;
+    pa.pivots = pivots;
+    pa.rest = reinterpret_cast<const int32_t*>(w + L.rest);
+    pa.inv_norm = reinterpret_cast<const float*>(w + L.inv_norm);
+    pa.G = reinterpret_cast<float*>(w + L.gram);
+    pa.part = reinterpret_cast<float*>(w + L.pick_part);
+    pa.mx = reinterpret_cast<float*>(w + L.mx);
+    pa.dist = reinterpret_cast<float*>(w + L.dist);
+    pa.ctrl = reinterpret_cast<int32_t*>(w + L.ctrl);
+    pa.cand = reinterpret_cast<int32_t*>(w + L.cand);
+    pa.cand_dist = reinterpret_cast<float*>(w + L.cand_dist);
+    pa.picks = reinterpret_cast<int32_t*>(w + L.picks);
+    pa.kept_idx = a->kept_idx;
+    pa.div_idx = a->div_idx;
+    TREVS_HIP(launch_picks(pa, a->vis_feats, a->d * e, a->dtype, s));
   }
   TREVS_TRY(record(a->events, 7, s));
 

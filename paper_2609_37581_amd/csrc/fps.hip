@@ -1,15 +1,11 @@
-// Context preservation by farthest point sampling (Sec. 4.1, after Eq. (7)):
-// K_d tokens are added one at a time to the pivot set, each the candidate
-// whose cosine distance 1 - zbar_i . zbar_j to the nearest already-selected
-// token is largest (ties to the lower index).
-//
-// The picks are sequential, and every pick needs the distances of all
-// candidates to one more token.  Instead of re-reading Z for each pick, the
-// Gram matrix G = Z Z^T of the sample is formed once on the matrix cores;
-// a pick then reads one row of G (N floats).  ||z_i||^2 is its diagonal.
+// Products of the visual features with each other, for the context
+// preservation by farthest point sampling (Sec. 4.1, after Eq. (7)): the Gram
+// matrix of all tokens of a sample or of a pool of them, and, where only the
+// nearest selected token matters, maxima over the selected tokens.
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
-#include "select.hpp"
 
 namespace trevs {
 
@@ -24,10 +20,9 @@ namespace trevs {
 // cores, each a 64x64 block.  Bytes past a row's end (a partial last slab)
 // load as zero.  The tile is written in place and, off the diagonal, also
 // transposed; both go through LDS and out as 16-byte runs of whole rows.
-// Diagonal tiles also write 1/max(||z_i||, 1e-12) from G_ii.  G is written
-// with nontemporal stores: the picks read it back long after it has left the
-// caches, and cached stores would evict operand slabs the other resident
-// workgroups still read.
+// G is written with nontemporal stores: the picks read it back long after it
+// has left the caches, and cached stores would evict operand slabs the other
+// resident workgroups still read.
 // ---------------------------------------------------------------------------
 constexpr int kGramTile = 128;
 constexpr int kGramThreads = 256;
@@ -74,7 +69,7 @@ __device__ __forceinline__ void gram_tile_of(int t, int nT, int& tj, int& ti) {
   }
 }
 
-// Workgroup -> (sample b, dense tile index t).  With many tiles per sample
+// Workgroup w -> (sample b, dense tile index t).  With many tiles per sample
 // (kGramStripe or more) XCD x takes the x-th eighth of every sample's tiles
 // (a contiguous run in super-block order, for its L2), sample after sample,
 // so that at any time all XCDs stream the same sample's Z, which fits the
@@ -84,27 +79,107 @@ __device__ __forceinline__ void gram_tile_of(int t, int nT, int& tj, int& ti) {
 // samples instead (a contiguous range of workgroups per XCD), so that a
 // sample's Z is loaded into one L2 only.
 constexpr int kGramStripe = 64;
-__device__ __forceinline__ bool gram_work(int per_b, int B, int& b, int& t) {
+__device__ __forceinline__ bool gram_work(int w, int per_b, int B, int& b, int& t) {
   if (per_b < kGramStripe) {
-    const int lin = xcd_remap(blockIdx.x, gridDim.x);
+    const int lin = xcd_remap(w, B * per_b);
     b = lin / per_b;
     t = lin - b * per_b;
     return true;
   }
-  const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
+  const int x = w & 7, k = w >> 3;
   const int r0 = (x * per_b) >> 3, L = (((x + 1) * per_b) >> 3) - r0;  // L >= 8
   b = k / L;
   t = r0 + (k - b * L);
   return b < B;
 }
-__host__ __device__ constexpr int gram_grid(int n_tiles, int B) {
-  return gram_tiles(n_tiles) < kGramStripe ? B * gram_tiles(n_tiles) : 8 * B * ((gram_tiles(n_tiles) + 7) / 8);
+__host__ __device__ constexpr int gram_grid(int per_b, int B) {
+  return per_b < kGramStripe ? B * per_b : 8 * B * ((per_b + 7) / 8);
+}
+
+// What a Gram launch computes.  kGramFull: all pairs of a sample's tokens.
+// kGramPool: all pairs of a list of tokens (a.rows).  kGramMax: for every
+// token of one list (a.cols) the maximum over each row tile of another
+// (a.rows), so that the products themselves are never written.
+enum { kGramFull = 0, kGramPool = 1, kGramMax = 2 };
+
+__device__ __forceinline__ bool gram_done(const GramArgs& a, int b) {
+  return a.ctrl && a.ctrl[b * kPickCtrl + kCtrlPicks] >= a.K_d;
+}
+
+// kGramMax: workgroup -> (sample, row tile, column tile), false for a padding
+// workgroup.  Tiles are walked in groups of four column tiles, so that the
+// workgroups of one XCD share about as many rows as columns in its L2; with
+// 64 tiles or more a sample's are striped over the XCDs as above.
+__device__ __forceinline__ bool gram_list_work(const GramArgs& a, int w, int& b, int& tp, int& tc) {
+  int t;
+  if (!gram_work(w, a.n_rtiles * a.n_ctiles, a.B, b, t)) return false;
+  const int full = a.n_ctiles / 4 * 4 * a.n_rtiles;
+  if (t < full) {
+    const int g = t / (4 * a.n_rtiles);
+    t -= g * 4 * a.n_rtiles;
+    tp = t >> 2;
+    tc = 4 * g + (t & 3);
+  } else {
+    const int n = a.n_ctiles & 3;
+    t -= full;
+    tp = t / n;
+    tc = a.n_ctiles - n + t % n;
+  }
+  return true;
+}
+
+// kGramMax: the rows of this launch for sample b: all of a.rows, or the picks
+// of the last round.
+__device__ __forceinline__ const int32_t* gram_list_rows(const GramArgs& a, int b, int& count) {
+  const int32_t* rows = a.rows + (size_t)b * a.n_rows;
+  count = a.n_rows;
+  if (a.by_round) {
+    const int begin = a.ctrl[b * kPickCtrl + kCtrlRound];
+    count = a.ctrl[b * kPickCtrl + kCtrlPicks] - begin;
+    rows += begin;
+  }
+  return rows;
+}
+
+// kGramMax output of a tile of T x T products held as MB x NB blocks by 2 x 2
+// waves.  All rows: max G_ij / ||z_j||, from which the distance follows as
+// 1 - max / ||z_i||.  By round: minus the least distance, formed per product as
+// the picks form it.  izr: the rows' inverse norms (LDS); red: 2 T floats of LDS
+// that nothing reads any more.
+template <int T, int MB, int NB>
+__device__ __forceinline__ void gram_max_store(const GramArgs& a, const f32x16 (&acc)[MB][NB], const float* izr,
+                                               float* red, int b, int tp, int tc, int wj, int wi) {
+  const int tid = threadIdx.x, half = (tid >> 5) & 1, col = tid & 31;
+  const int32_t* cols = a.cols + (size_t)b * a.n_cols;
+  float mx[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    mx[n] = -INFINITY;
+    const int c = min(tc * T + wi * (T / 2) + n * 32 + col, a.n_cols - 1);
+    const float izc = a.by_round ? a.inv_norm[(size_t)b * a.N + cols[c]] : 0.f;
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float iz = izr[wj * (T / 2) + m * 32 + mfma_row(r, half)];
+        const float g = acc[m][n][r];
+        mx[n] = fmaxf(mx[n], a.by_round ? fmaf(g * izc, iz, -1.f) : g * iz);
+      }
+    mx[n] = fmaxf(mx[n], __shfl_xor(mx[n], 32, 64));
+  }
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+    if (half == 0) red[wj * T + wi * (T / 2) + n * 32 + col] = mx[n];
+  __syncthreads();
+  for (int c = tid; c < T; c += blockDim.x)
+    if (tc * T + c < a.n_cols)
+      a.mx[((size_t)tp * a.B + b) * a.n_cols + tc * T + c] = fmaxf(red[c], red[T + c]);
 }
 
 __device__ __forceinline__ int gram_swizzle(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-template <class In>
-__global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
+template <class In, int MODE>
+__device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   constexpr int T = kGramTile;
   constexpr int SLAB = T * 128;                  // bytes of one operand slab
   constexpr int VPT = SLAB / 16 / kGramThreads;  // vectors per thread per operand
@@ -116,19 +191,40 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
   const int half = lane >> 5, col = lane & 31;
   const int nT = a.n_tiles;
   int b, t, tj, ti;
-  if (!gram_work(gram_tiles(nT), a.B, b, t)) return;  // the whole workgroup: no barrier has run
-  gram_tile_of(t, nT, tj, ti);
-  const int N = a.N, rb = a.row_bytes;
+  // (every return below is the whole workgroup's: no barrier has run)
+  if (MODE == kGramMax) {
+    if (!gram_list_work(a, w, b, tj, ti)) return;
+  } else {
+    if (!gram_work(w, gram_tiles(nT), a.B, b, t)) return;
+  }
+  if (gram_done(a, b)) return;
+  if (MODE != kGramMax) gram_tile_of(t, nT, tj, ti);
+  const int rb = a.row_bytes;
+  int nj = a.N, ni = a.N;  // tokens along the rows and columns
+  const int32_t *rows = nullptr, *cols = nullptr;
+  __shared__ float izr[T];
+  if (MODE != kGramFull) {
+    rows = cols = gram_list_rows(a, b, nj);
+    ni = nj;
+    if (MODE == kGramMax) {
+      if (tj * T >= nj) return;
+      cols = a.cols + (size_t)b * a.n_cols;
+      ni = a.n_cols;
+      if (tid < T) izr[tid] = a.inv_norm[(size_t)b * a.N + rows[min(tj * T + tid, nj - 1)]];
+    }
+  }
+  const int N = ni, ld = a.ldg;
   const int n_slabs = (rb + 127) / 128;
   const int tail = rb & 127;  // bytes of a partial last slab, 0 if none
-  const uint8_t* zb = reinterpret_cast<const uint8_t*>(a.Z) + (size_t)b * N * rb;
+  const uint8_t* zb = reinterpret_cast<const uint8_t*>(a.Z) + (size_t)b * a.N * rb;
   const int cr = tid >> 3, cc = tid & 7;
-  const uint8_t* src[2 * VPT];  // row starts (rows past N re-read row N - 1)
+  const uint8_t* src[2 * VPT];  // row starts (rows past the last re-read it)
 #pragma unroll
   for (int k = 0; k < VPT; ++k) {
     const int r = cr + (kGramThreads / 8) * k;
-    src[k] = zb + (size_t)min(tj * T + r, N - 1) * rb;
-    src[VPT + k] = zb + (size_t)min(ti * T + r, N - 1) * rb;
+    const int j = min(tj * T + r, nj - 1), i = min(ti * T + r, ni - 1);
+    src[k] = zb + (size_t)(MODE == kGramFull ? j : rows[j]) * rb;
+    src[VPT + k] = zb + (size_t)(MODE == kGramFull ? i : cols[i]) * rb;
   }
   const int sdst = cr * 128 + gram_swizzle(cr, cc) * 16;  // rows 32 apart share the swizzle
   u32x4 g[2][2 * VPT];
@@ -200,21 +296,13 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
       if (s < n_slabs) compute(st);
     }
   }
+  if constexpr (MODE == kGramMax) {
+    __syncthreads();  // the operand slabs are no longer read
+    gram_max_store<T, 2, 2>(a, acc, izr, reinterpret_cast<float*>(lds), b, tj, ti, wj, wi);
+    return;
+  }
   // output: register r of block (m, n) is row wj*64 + m*32 + mfma_row(r),
   // column wi*64 + n*32 + col of the tile
-  if (tj == ti) {  // the diagonal tile holds ||z_i||^2
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int jl = wj * 64 + m * 32 + mfma_row(r, half), il = wi * 64 + n * 32 + col;
-          const int i = ti * T + il;
-          if (jl == il && i < N)
-            a.inv_norm[(size_t)b * N + i] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
-        }
-  }
   // The tile leaves through LDS, 32 rows j at a time, as 16-byte runs of
   // whole rows: tA (rows j, stride TA: 16-byte aligned rows, the half-waves'
   // writes on disjoint banks) for G[j, i]; off the diagonal tB (rows i, odd
@@ -224,9 +312,9 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
   static_assert((PR * TA + T * TB) * 4 <= LDS, "output staging fits the LDS");
   float* tA = reinterpret_cast<float*>(lds);
   float* tB = tA + PR * TA;
-  float* gb = a.G + (size_t)b * N * N;
+  float* gb = a.G + (size_t)b * nj * ld;
   const bool mirror = tj != ti;
-  const bool fast = (ti + 1) * T <= N && (N & 3) == 0;  // tj <= ti
+  const bool fast = (ti + 1) * T <= N && (ld & 3) == 0;  // tj <= ti
 #pragma unroll
   for (int p = 0; p < T / PR; ++p) {  // unrolled: the accumulator block m is a constant
     __syncthreads();  // the operand slabs, or the previous pass, are no longer read
@@ -248,11 +336,11 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
       const int j = tj * T + PR * p + row, i = ti * T + 4 * q;
       const u32x4 v = *reinterpret_cast<const u32x4*>(&tA[row * TA + 4 * q]);
       if (fast) {
-        stg16_stream(&gb[(size_t)j * N + i], v);
+        stg16_stream(&gb[(size_t)j * ld + i], v);
       } else {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (j < N && i + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gb[(size_t)j * N + i + u]);
+          if (j < N && i + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gb[(size_t)j * ld + i + u]);
       }
     }
     if (mirror) {  // G[i, j]: T rows of PR / 4 runs
@@ -264,11 +352,11 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
         const u32x4 v = {__float_as_uint(src[0]), __float_as_uint(src[1]), __float_as_uint(src[2]),
                          __float_as_uint(src[3])};
         if (fast) {
-          stg16_stream(&gb[(size_t)i * N + j], v);
+          stg16_stream(&gb[(size_t)i * ld + j], v);
         } else {
 #pragma unroll
           for (int u = 0; u < 4; ++u)
-            if (i < N && j + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gb[(size_t)i * N + j + u]);
+            if (i < N && j + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gb[(size_t)i * ld + j + u]);
         }
       }
     }
@@ -301,7 +389,8 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
 constexpr int kGram256Threads = 256;
 constexpr int kGram256MinN = 2048;
 
-__global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a) {
+template <int MODE>
+__device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   constexpr int T = 256;
   constexpr int SLAB = T * 128;                     // bytes of one operand's 128-byte stage
   constexpr int VPT = SLAB / 16 / kGram256Threads;  // 8 vectors per thread per operand
@@ -315,8 +404,14 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
   const int half = lane >> 5, col = lane & 31;
   const int nT = a.n_tiles;
   int b, t, tj, ti;
-  if (!gram_work(gram_tiles(nT), a.B, b, t)) return;  // the whole workgroup: no barrier has run
-  gram_tile_of(t, nT, tj, ti);
+  // (every return below is the whole workgroup's: no barrier has run)
+  if (MODE == kGramMax) {
+    if (!gram_list_work(a, w, b, tj, ti)) return;
+  } else {
+    if (!gram_work(w, gram_tiles(nT), a.B, b, t)) return;
+  }
+  if (gram_done(a, b)) return;
+  if (MODE != kGramMax) gram_tile_of(t, nT, tj, ti);
   const int N = a.N, rb = a.row_bytes;
   const int n_stages = (rb + 127) / 128;
   // rows past N read zeros (their offsets pass N * rb), and so do the chunks
@@ -331,6 +426,27 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
   const uint32_t rowA = (uint32_t)(tj * T + cr) * rb + cc * 16;
   const uint32_t rowB = (uint32_t)(ti * T + cr) * rb + cc * 16;
   const uint32_t kstride = (uint32_t)RSTEP * rb;
+  // listed tokens: an offset per row (rows past the last re-read it)
+  __shared__ float izr[MODE == kGramMax ? T : 1];
+  uint32_t offA[VPT], offB[VPT];
+  if constexpr (MODE == kGramMax) {
+    int nj;
+    const int32_t* rows = gram_list_rows(a, b, nj);
+    if (tj * T >= nj) return;
+    const int32_t* cols = a.cols + (size_t)b * a.n_cols;
+    if (tid < T) izr[tid] = a.inv_norm[(size_t)b * N + rows[min(tj * T + tid, nj - 1)]];
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+      offA[k] = (uint32_t)rows[min(tj * T + cr + RSTEP * k, nj - 1)] * rb + cc * 16;
+      offB[k] = (uint32_t)cols[min(ti * T + cr + RSTEP * k, a.n_cols - 1)] * rb + cc * 16;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+      offA[k] = rowA + k * kstride;
+      offB[k] = rowB + k * kstride;
+    }
+  }
   // LDS: operand A of buffers 0 and 1, then operand B of buffers 0 and 1
   // (every fragment address is one register per k-step and operand plus an
   // immediate offset)
@@ -340,11 +456,10 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
   // stage) takes an offset outside the buffer and reads zeros
   auto load = [&](int P, u32x4 (&dst)[2 * VPT]) {
     const uint32_t so = P * 128 + cc * 16 < rb ? (uint32_t)P * 128u : 0x80000000u;
-    const uint32_t oa = rowA + so, ob = rowB + so;
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
-      dst[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(zs, oa + k * kstride, 0, 0));
-      dst[VPT + k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(zs, ob + k * kstride, 0, 0));
+      dst[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(zs, offA[k] + so, 0, 0));
+      dst[VPT + k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(zs, offB[k] + so, 0, 0));
     }
   };
   auto store = [&](int c, const u32x4 (&v)[2 * VPT]) {
@@ -439,21 +554,12 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
       __syncthreads();
     }
   }
+  if constexpr (MODE == kGramMax) {  // (the loop ended on a barrier)
+    gram_max_store<T, 4, 4>(a, acc, izr, reinterpret_cast<float*>(lds), b, tj, ti, wj, wi);
+    return;
+  }
   // register r of block (m, n) is row wj*128 + m*32 + mfma_row(r), column
   // wi*128 + n*32 + col of the tile
-  if (tj == ti) {  // the diagonal tile holds ||z_i||^2
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int n = 0; n < 4; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int jl = wj * 128 + m * 32 + mfma_row(r, half), il = wi * 128 + n * 32 + col;
-          const int i = ti * T + il;
-          if (jl == il && i < N)
-            a.inv_norm[(size_t)b * N + i] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
-        }
-  }
   // The tile leaves through LDS, 32 rows j at a time, and is stored as
   // 16-byte runs of whole rows (each lane storing 4 bytes, or 16-byte runs
   // of a few bytes per row, writes G at a fraction of the rate): tA holds
@@ -464,9 +570,10 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
   // 16 bytes store without bounds checks.
   float* tA = reinterpret_cast<float*>(lds);
   float* tB = tA + PR * TA;
-  float* gbm = a.G + (size_t)b * N * N;
+  const int ld = a.ldg;
+  float* gbm = a.G + (size_t)b * N * ld;
   const bool mirror = tj != ti;
-  const bool fast = (ti + 1) * T <= N && (N & 3) == 0;  // tj <= ti
+  const bool fast = (ti + 1) * T <= N && (ld & 3) == 0;  // tj <= ti
 #pragma unroll
   for (int p = 0; p < T / PR; ++p) {  // unrolled: the accumulator block m is a constant
     __syncthreads();  // the operand slabs, or the previous pass, are no longer read
@@ -489,11 +596,11 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
       const int j = tj * T + PR * p + row, i = ti * T + 4 * q;
       const u32x4 v = *reinterpret_cast<const u32x4*>(&tA[row * TA + 4 * q]);
       if (fast) {
-        stg16_stream(&gbm[(size_t)j * N + i], v);
+        stg16_stream(&gbm[(size_t)j * ld + i], v);
       } else {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (j < N && i + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)j * N + i + u]);
+          if (j < N && i + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)j * ld + i + u]);
       }
     }
     if (mirror) {  // G[i, j]: T rows of PR / 4 runs
@@ -505,195 +612,103 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
         const u32x4 v = {__float_as_uint(srcp[0]), __float_as_uint(srcp[1]), __float_as_uint(srcp[2]),
                          __float_as_uint(srcp[3])};
         if (fast) {
-          stg16_stream(&gbm[(size_t)i * N + j], v);
+          stg16_stream(&gbm[(size_t)i * ld + j], v);
         } else {
 #pragma unroll
           for (int u = 0; u < 4; ++u)
-            if (i < N && j + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)i * N + j + u]);
+            if (i < N && j + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)i * ld + j + u]);
         }
       }
     }
   }
 }
 
-// ---------------------------------------------------------------------------
-// Initial distances: for every token i, 1 - max over the pivots j of
-// cos(z_i, z_j) = G_ij / (||z_i|| ||z_j||), with the inverse norms the Gram
-// pass wrote.  One thread per token; the pivots are split over n_psplit
-// workgroups per token block (grid z), each writing the maximum of
-// G_ij / ||z_j|| over its share; the picks kernel takes the maximum over the
-// splits (exact, so the order does not matter) and forms the distance.  The
-// pivot loop is unrolled so that several row reads of G are in flight (a
-// pivot's row is read at consecutive columns by consecutive threads).
-// ---------------------------------------------------------------------------
-constexpr int kFpsInitThreads = 256;
-
-__global__ __launch_bounds__(kFpsInitThreads) void fps_init_kernel(FpsArgs a) {
-  const int b = blockIdx.y, split = blockIdx.z, N = a.N;
-  const int i = min((int)(blockIdx.x * kFpsInitThreads + threadIdx.x), N - 1);
-  const float* gb = a.G + (size_t)b * N * N;
-  const float* inb = a.inv_norm + (size_t)b * N;
-  const int per = (a.K_r + a.n_psplit - 1) / a.n_psplit;
-  const int p_begin = min(split * per, a.K_r), p_end = min(p_begin + per, a.K_r);
-  const int32_t* piv = a.pivots + (size_t)b * a.K_r;
-  constexpr int U = 8;
-  float mx = -INFINITY;
-  int p = p_begin;
-  for (; p + U <= p_end; p += U) {
-    int j[U];
-    float g[U], izj[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = piv[p + u];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      g[u] = gb[(size_t)j[u] * N + i];
-      izj[u] = inb[j[u]];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) mx = fmaxf(mx, g[u] * izj[u]);
-  }
-  for (; p < p_end; ++p) {
-    const int j = piv[p];
-    mx = fmaxf(mx, gb[(size_t)j * N + i] * inb[j]);
-  }
-  if (blockIdx.x * kFpsInitThreads + threadIdx.x < N) a.dist[((size_t)split * a.B + b) * N + i] = mx;
+// ---------------------------------------------------------------- kernels
+// One tile per workgroup.
+template <class In, int MODE>
+__global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
+  gram_tile<In, MODE>(a, blockIdx.x);
+}
+template <int MODE>
+__global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a) {
+  gram256_tile<MODE>(a, blockIdx.x);
 }
 
-// ---------------------------------------------------------------------------
-// The picks: one workgroup per sample walks the K_d sequential steps with
-// the distances of its tokens in registers (element e*1024 + t of thread t,
-// as in the selection kernels), formed from the initial pass's per-split
-// maxima.  Each step reduces (distance desc, index asc) over the unselected
-// tokens, marks the winner, and lowers every distance with the winner's row
-// of G.  The selected set (pivots and picks) is then written in ascending
-// order.
-// ---------------------------------------------------------------------------
-template <int E>
-__global__ __launch_bounds__(kSelThreads) void fps_pick_kernel(FpsArgs a) {
-  __shared__ SelectShared sh;
-  __shared__ float wv[2][kSelWaves];
-  __shared__ int wi[2][kSelWaves];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int N = a.N, K_r = a.K_r;
-  const int32_t* piv = a.pivots + (size_t)b * K_r;
-  const float* gb = a.G + (size_t)b * N * N;
-  auto valid = [&](int e) { return e * kSelThreads + tid < N; };
-  // pivot membership: every thread marks its share of the pivot list in an
-  // LDS bitmap, then reads the bits of its own elements
-  __shared__ uint32_t pivbits[kMaxE * kSelThreads / 32];
-  for (int w = tid; w < (N + 31) / 32; w += kSelThreads) pivbits[w] = 0u;
-  float dist[E], iz[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = min(e * kSelThreads + tid, N - 1);
-    float mx = a.dist[(size_t)b * N + i];
-    for (int sp = 1; sp < a.n_psplit; ++sp) mx = fmaxf(mx, a.dist[((size_t)sp * a.B + b) * N + i]);
-    iz[e] = a.inv_norm[(size_t)b * N + i];
-    dist[e] = 1.f - mx * iz[e];
-  }
-  __syncthreads();
-  for (int p = tid; p < K_r; p += kSelThreads) {
-    const int j = min(max(piv[p], 0), N - 1);
-    atomicOr(&pivbits[j >> 5], 1u << (j & 31));
-  }
-  __syncthreads();
-  SelMask<E> sel = 0;  // bit e: element e is selected (a pivot or a pick)
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e * kSelThreads + tid;
-    if (valid(e) && ((pivbits[i >> 5] >> (i & 31)) & 1u)) sel |= SelMask<E>(1) << e;
-  }
-  // selected and padding elements hold distance -inf: they never win a step,
-  // and the row updates (a minimum) keep them there, so neither the argmax
-  // nor the update tests them
-#pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (!valid(e) || ((sel >> e) & 1u)) dist[e] = -INFINITY;
-  for (int t = 0; t < a.K_d; ++t) {
-    float v = -INFINITY;
-    uint32_t idx = 0xffffffffu;
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (dist[e] > v) {  // ascending e: the lower index wins ties
-        v = dist[e];
-        idx = (uint32_t)(e * kSelThreads + tid);
-      }
-    const float vm = wave_max(v);
-    const uint32_t im = wave_min_u32(v == vm ? idx : 0xffffffffu);
-    const int buf = t & 1;  // alternate slots: one barrier per step suffices
-    if (lane == 0) {
-      wv[buf][wave] = vm;
-      wi[buf][wave] = (int)im;
-    }
+// The full Gram matrix of the samples that the pool rounds left unfinished,
+// most often none: as many workgroups as are resident at once walk the tiles
+// (8320 workgroups that only find nothing to do take 104 us, these 5 us).
+__device__ __forceinline__ bool gram_any_left(const GramArgs& a) {
+  bool left = false;
+  for (int b = threadIdx.x; b < a.B; b += blockDim.x) left |= !gram_done(a, b);
+  return __syncthreads_or(left);
+}
+template <class In>
+__global__ __launch_bounds__(kGramThreads, 2) void gram_left_kernel(GramArgs a, int n_work) {
+  if (!gram_any_left(a)) return;
+  for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
+    gram_tile<In, kGramFull>(a, w);
     __syncthreads();
-    // every wave reduces the waves' winners itself (distance desc, index asc)
-    const float v2 = lane < kSelWaves ? wv[buf][lane] : -INFINITY;
-    const uint32_t i2 = lane < kSelWaves ? (uint32_t)wi[buf][lane] : 0xffffffffu;
-    const float bv = wave_max(v2);
-    int w = (int)wave_min_u32(v2 == bv ? i2 : 0xffffffffu);
-    w = __builtin_amdgcn_readfirstlane(min(max(w, 0), N - 1));  // K_r + K_d <= N leaves a candidate
-    if (tid == 0 && a.div_idx) a.div_idx[(size_t)b * a.K_d + t] = w;
-    const int we = w / kSelThreads;
-    const bool mine = (w & (kSelThreads - 1)) == tid;
-    if (mine) sel |= SelMask<E>(1) << we;
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (mine && e == we) dist[e] = -INFINITY;
-    // the winner's row of G through a buffer resource: a uniform base and a
-    // 32-bit offset per element (no 64-bit address per element), and the
-    // elements past N read 0 (their distance is -inf already)
-    const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(gb + (size_t)w * N), 0, N * 4, kBufferRsrcWord3);
-    const float izw = a.inv_norm[(size_t)b * N + w];
-    // the row's loads go out before any is used, up to 16 at a time (one
-    // round trip for N <= 16,384; 32 held values would spill)
-    constexpr int CH = E < 16 ? E : 16;
-#pragma unroll
-    for (int c0 = 0; c0 < E; c0 += CH) {
-      float gi[CH];
-#pragma unroll
-      for (int u = 0; u < CH; ++u)
-        gi[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row, ((c0 + u) * kSelThreads + tid) * 4, 0, 0));
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const float d = 1.f - gi[u] * iz[c0 + u] * izw;
-        dist[c0 + u] = d < dist[c0 + u] ? d : dist[c0 + u];
-      }
-    }
   }
-  block_write_mask<E>(sel, K_r + a.K_d, a.kept_idx + (size_t)b * (K_r + a.K_d), sh);
+}
+__global__ __launch_bounds__(kGram256Threads, 1) void gram256_left_kernel(GramArgs a, int n_work) {
+  if (!gram_any_left(a)) return;
+  for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
+    gram256_tile<kGramFull>(a, w);
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_fps(const FpsArgs& f, const GramArgs& g, int dtype, int B, hipStream_t s) {
-  // rows are a multiple of 16 bytes (checked at the boundary)
-  if (dtype == 1 && g.N >= kGram256MinN && (size_t)(g.N + 256) * g.row_bytes < (1u << 31)) {
-    GramArgs g2 = g;
-    g2.n_tiles = (g.N + 255) / 256;
-    const dim3 ggrid(gram_grid(g2.n_tiles, B));
-    hipLaunchKernelGGL(gram256_kernel, ggrid, dim3(kGram256Threads), 0, s, g2);
-  } else {
-    const dim3 ggrid(gram_grid(g.n_tiles, B));
-    if (dtype == 1)
-      hipLaunchKernelGGL(gram_kernel<BF16>, ggrid, dim3(kGramThreads), 0, s, g);
+bool gram256_ok(int dtype, int N, int row_bytes) {
+  return dtype == 1 && N >= kGram256MinN && (size_t)(N + 256) * row_bytes < (1u << 31);
+}
+
+hipError_t launch_gram_full(const GramArgs& g0, int dtype, hipStream_t s) {
+  GramArgs g = g0;
+  const bool big = gram256_ok(dtype, g.N, g.row_bytes);  // rows are a multiple of 16 bytes (checked at the boundary)
+  const int T = big ? 256 : kGramTile;
+  g.n_tiles = (g.N + T - 1) / T;
+  const int n_work = gram_grid(gram_tiles(g.n_tiles), g.B);
+  if (g.ctrl) {
+    const dim3 grid(std::min(n_work, big ? 256 : 512));
+    if (big)
+      hipLaunchKernelGGL(gram256_left_kernel, grid, dim3(kGram256Threads), 0, s, g, n_work);
+    else if (dtype == 1)
+      hipLaunchKernelGGL(gram_left_kernel<BF16>, grid, dim3(kGramThreads), 0, s, g, n_work);
     else
-      hipLaunchKernelGGL(gram_kernel<F32>, ggrid, dim3(kGramThreads), 0, s, g);
+      hipLaunchKernelGGL(gram_left_kernel<F32>, grid, dim3(kGramThreads), 0, s, g, n_work);
+  } else if (big) {
+    hipLaunchKernelGGL(gram256_kernel<kGramFull>, dim3(n_work), dim3(kGram256Threads), 0, s, g);
+  } else if (dtype == 1) {
+    hipLaunchKernelGGL((gram_kernel<BF16, kGramFull>), dim3(n_work), dim3(kGramThreads), 0, s, g);
+  } else {
+    hipLaunchKernelGGL((gram_kernel<F32, kGramFull>), dim3(n_work), dim3(kGramThreads), 0, s, g);
   }
-  hipLaunchKernelGGL(fps_init_kernel, dim3((f.N + kFpsInitThreads - 1) / kFpsInitThreads, B, f.n_psplit),
-                     dim3(kFpsInitThreads), 0, s, f);
-  const int E = select_e(f.N);
-#define CALL(E_) hipLaunchKernelGGL(fps_pick_kernel<E_>, dim3(B), dim3(kSelThreads), 0, s, f)
-  switch (E) {
-    case 1: CALL(1); break;
-    case 2: CALL(2); break;
-    case 4: CALL(4); break;
-    case 8: CALL(8); break;
-    case 16: CALL(16); break;
-    case 32: CALL(32); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef CALL
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_pool(const GramArgs& g0, int dtype, hipStream_t s) {
+  GramArgs g = g0;
+  g.n_tiles = (g.n_rows + kGramTile - 1) / kGramTile;
+  const dim3 grid(gram_grid(gram_tiles(g.n_tiles), g.B));
+  if (dtype == 1)
+    hipLaunchKernelGGL((gram_kernel<BF16, kGramPool>), grid, dim3(kGramThreads), 0, s, g);
+  else
+    hipLaunchKernelGGL((gram_kernel<F32, kGramPool>), grid, dim3(kGramThreads), 0, s, g);
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_max(const GramArgs& g0, int tile, int dtype, hipStream_t s) {
+  GramArgs g = g0;
+  g.n_rtiles = (g.n_rows + tile - 1) / tile;
+  g.n_ctiles = (g.n_cols + tile - 1) / tile;
+  const dim3 grid(gram_grid(g.n_rtiles * g.n_ctiles, g.B));
+  if (tile == 256)
+    hipLaunchKernelGGL(gram256_kernel<kGramMax>, grid, dim3(kGram256Threads), 0, s, g);
+  else if (dtype == 1)
+    hipLaunchKernelGGL((gram_kernel<BF16, kGramMax>), grid, dim3(kGramThreads), 0, s, g);
+  else
+    hipLaunchKernelGGL((gram_kernel<F32, kGramMax>), grid, dim3(kGramThreads), 0, s, g);
   return hipGetLastError();
 }
 

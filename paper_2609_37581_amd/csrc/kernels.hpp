@@ -37,6 +37,7 @@ struct RelArgs {
   int n_split, split_slabs;
   float* part;
   float* zpart;
+  float* inv_norm;           // [B,N] 1 / max(||z_i||, 1e-12), or null
 };
 
 // Launch shape of the relevance pass for one problem size.
@@ -67,6 +68,10 @@ struct SelArgs {
   float* score_out;          // [B,N] or null
   float* norm_stats;         // [B,4] or null
   int32_t* kept_idx;         // [B,K]
+  // with a diversity set: the control words of its picks, zeroed here, and for
+  // pool rounds the N - K other tokens, ascending (each null without)
+  int32_t* pick_ctrl;
+  int32_t* rest;
 };
 
 // ---------------------------------------------------------------- stage 2
@@ -115,31 +120,70 @@ struct ScoreArgs {
 };
 
 // ---------------------------------------------------------------- diversity set
+// Control words of one sample's picks, zeroed by the pivot selection.
+// kCtrlPicks: tokens picked so far; kCtrlRound: picks before the last round;
+// kCtrlBound: distance (float bits) that no token outside the round's pool
+// exceeds; kCtrlTie: the first token outside it at that distance.
+constexpr int kPickCtrl = 4;
+enum { kCtrlPicks = 0, kCtrlRound = 1, kCtrlTie = 2, kCtrlBound = 3 };
+
 struct GramArgs {
   const void* Z;             // [B,N,d]
-  int B, N, row_bytes, n_tiles; // n_tiles = ceil(N / tile rows)
-  float* G;                  // [B,N,N] fp32 dot products z_j . z_i
-  float* inv_norm;           // [B,N] 1 / max(||z_i||, 1e-12)
+  int B, N, row_bytes;
+  int n_tiles;               // tiles a side (set by the launchers, as n_rtiles and n_ctiles)
+  float* G;                  // [B,n,ldg] fp32 dot products z_j . z_i of n tokens
+  int ldg;                   // row stride of G, a multiple of 4
+  // samples whose picks (ctrl, if not null) have reached K_d are skipped
+  const int32_t* ctrl;
+  int K_d;
+  // products over lists of tokens
+  const int32_t* rows;       // [B,n_rows]
+  const int32_t* cols;       // [B,n_cols]
+  int n_rows, n_cols;
+  int n_rtiles, n_ctiles;
+  bool by_round;             // the rows are the last round's picks, not all of them
+  const float* inv_norm;     // [B,N] 1 / max(||z_i||, 1e-12)
+  float* mx;                 // [n_rtiles,B,n_cols] maxima over each row tile
 };
-struct FpsArgs {
-  const float* G;            // [B,N,N]
+bool gram256_ok(int dtype, int N, int row_bytes);  // 256-row tiles can be used
+// G of all N tokens; with ctrl, of the samples that are not finished.
+hipError_t launch_gram_full(const GramArgs& g, int dtype, hipStream_t s);
+// G of the listed tokens (rows).
+hipError_t launch_gram_pool(const GramArgs& g, int dtype, hipStream_t s);
+// Maxima over row tiles of `tile` (128, or 256 where gram256_ok).
+hipError_t launch_gram_max(const GramArgs& g, int tile, int dtype, hipStream_t s);
+
+// How the K_d picks are made (see pick_plan).
+struct PickPlan {
+  int rounds;                // pool rounds before the full Gram matrix (0: none)
+  int C, ldc;                // pool size, row stride of its Gram matrix
+  int row_tile;              // row tile of the first round's distances
+  int n_mx;                  // most row tiles of any round
+  int ldg;                   // row stride of the full Gram matrix
+  int n_psplit;              // pivot splits of the initial distances over the full Gram matrix
+  size_t gram_floats(int N) const;  // floats of a sample's Gram matrix, full or of the pool
+};
+constexpr int kRoundTile = 128;  // row tile of the later rounds' distances
+PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes);
+struct PickArgs {
+  PickPlan p;
+  int B, N, K_r, K_d, R;     // R = N - K_r
   const int32_t* pivots;     // [B,K_r] ascending
-  int N, K_r, K_d;
-  int B;
-  int n_psplit;              // pivot splits of the initial distances (fps_init_splits)
-  float* dist;               // [n_psplit,B,N] work: per split, max over its pivots j of G_ij / ||z_j||
-  float* inv_norm;           // [B,N] work: 1 / max(||z_i||, 1e-12), from the Gram pass
+  const int32_t* rest;       // [B,R] ascending, the other tokens (pool rounds)
+  const float* inv_norm;     // [B,N]
+  float* G;                  // [B,N,ldg], or [B,C,ldc]
+  float* part;               // [n_psplit,B,N]: per split, max over its pivots j of G_ij / ||z_j||
+  float* mx;                 // [n_mx,B,R]
+  float* dist;               // [B,N] distance to the selected set, -inf once picked (pool rounds)
+  int32_t* ctrl;             // [B,kPickCtrl]
+  int32_t* cand;             // [B,C] pool tokens, ascending
+  float* cand_dist;          // [B,C]
+  int32_t* picks;            // [B,K_d]
   int32_t* kept_idx;         // [B,K_r+K_d] ascending
   int32_t* div_idx;          // [B,K_d] picks in pick order, or null
 };
-// Gram matrix, initial distances and the K_d sequential picks.
-hipError_t launch_fps(const FpsArgs& f, const GramArgs& g, int dtype, int B, hipStream_t s);
-// Pivot splits of the initial-distance pass (workgroups per token block):
-// about 256 pivots each, at most 8.
-inline int fps_init_splits(int K_r) {
-  const int s = K_r / 256;
-  return s < 1 ? 1 : (s > 8 ? 8 : s);
-}
+// The K_d picks and the kept list.
+hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dtype, hipStream_t s);
 
 // ---------------------------------------------------------------- analysis
 struct ProfileArgs {

@@ -351,9 +351,11 @@ __device__ SelMask<E> block_topk_mask(KeyF keyf, int N, int K, SelectShared& sh)
 }
 
 // Writes the indices of the elements set in `mask` (K of them over the
-// workgroup) in ascending order to out[0..K).
+// workgroup) in ascending order to out[0..K), and, if rest is given, the other
+// indices below N to rest[0..N - K).
 template <int E>
-__device__ void block_write_mask(SelMask<E> mask, int K, int32_t* out, SelectShared& sh) {
+__device__ void block_write_mask(SelMask<E> mask, int K, int32_t* out, SelectShared& sh, int N = 0,
+                                 int32_t* rest = nullptr) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   auto lanes_below = [&](unsigned long long bal) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
@@ -369,39 +371,33 @@ __device__ void block_write_mask(SelMask<E> mask, int K, int32_t* out, SelectSha
   for (int e = 0; e < E; ++e) {
     const bool kp = (mask >> e) & 1u;
     const int pos = (int)sh.wcnt[e * kSelWaves + wave] + lanes_below(__ballot(kp));
-    if (kp && pos < K) out[pos] = e * kSelThreads + tid;  // exactly K kept; the bound guards memory
+    const int i = e * kSelThreads + tid;
+    if (kp && pos < K) out[pos] = i;  // exactly K kept; the bound guards memory
+    if (rest && !kp && i < N && i - pos < N - K) rest[i - pos] = i;
   }
 }
 
-// Stable top-K: keep every element whose score is above the K-th largest and
-// the lowest-index elements equal to it, and write the kept indices in
-// ascending order to out[0..K).  After the threshold selection one scan does
-// the rest: element i goes to slot above(i) + min(ties(i), need), where
-// above(i) and ties(i) count the elements before i (in index order) above the
-// threshold and equal to it, and need is how many ties are kept.  The two
-// counts travel packed in one word (low and high 16 bits: every exclusive
-// count is below N <= 65536).
+// Stable top-K: every element whose key is above the K-th largest and the
+// lowest-index elements equal to it are kept.  After the threshold selection
+// one scan does the rest: above(i) and ties(i) count the elements before i (in
+// index order) above the threshold and equal to it, need is how many ties are
+// kept, so above(i) + min(ties(i), need) kept elements precede element i.  The
+// two counts travel packed in one word (low and high 16 bits: every exclusive
+// count is below N <= 65536).  emit(e, keep, before) is called once for each
+// valid element e of this thread with its number of kept predecessors.
+// thr (if not null) takes the K-th largest key (0 < K < N).
 // have_range, kmin, kmax: bounds of the keys, as for block_select.
-template <int E>
-__device__ void block_topk_write(const float (&sc)[E], int N, int K, int32_t* out,
-                                 SelectShared& sh, bool have_range = false, uint32_t kmin = 0u,
-                                 uint32_t kmax = 0u) {
+template <int E, class Emit>
+__device__ __forceinline__ void block_topk_each(const uint32_t (&key)[E], int N, int K, Emit emit,
+                                                SelectShared& sh, bool have_range, uint32_t kmin,
+                                                uint32_t kmax, uint32_t* thr_out = nullptr) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int nv = thread_rounds<E>(N);
   auto valid = [&](int e) { return e < nv; };
-  if (K <= 0) return;
-  if (K >= N) {
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (valid(e)) out[e * kSelThreads + tid] = e * kSelThreads + tid;
-    return;
-  }
-  uint32_t key[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) key[e] = f2key(sc[e]);
   uint32_t thr;
   int less, eq;
   block_select<E>([&](int e) { return key[e]; }, N, N - K, thr, less, eq, sh, have_range, kmin, kmax);
+  if (thr_out) *thr_out = thr;
   const int need = K - (N - less - eq);  // ties kept, lowest index first
   auto lanes_below = [&](unsigned long long bal) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
@@ -415,11 +411,6 @@ __device__ void block_topk_write(const float (&sc)[E], int N, int K, int32_t* ou
     if (lane == 0) sh.wcnt[e * kSelWaves + wave] = (uint32_t)__popcll(ba) | ((uint32_t)__popcll(bt) << 16);
   }
   wcnt_scan(E * kSelWaves, sh);
-  // the output base lives in a VGPR pair: held in SGPRs through the
-  // selection it was spilled and re-read for every store
-  uint64_t obase = (uint64_t)(uintptr_t)out;
-  asm volatile("" : "+v"(obase));
-  int32_t* const o = (int32_t*)(uintptr_t)obase;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const uint32_t k = key[e];
@@ -429,11 +420,45 @@ __device__ void block_topk_write(const float (&sc)[E], int N, int K, int32_t* ou
     const uint32_t base = sh.wcnt[e * kSelWaves + wave];
     const int na = (int)(base & 0xffffu) + lanes_below(ba);  // above the threshold, before this element
     const int nt = (int)(base >> 16) + lanes_below(bt);      // ties before this element
-    if (above || (tie && nt < need)) {
-      const int pos = na + min(nt, need);
-      if (pos < K) o[pos] = e * kSelThreads + tid;  // exactly K kept; the bound guards memory
-    }
+    emit(e, valid(e), above || (tie && nt < need), na + min(nt, need));
   }
+}
+
+// Stable top-K written as ascending indices to out[0..K); with REST the other
+// N - K indices go, ascending, to rest.
+template <int E, bool REST = false>
+__device__ void block_topk_write(const float (&sc)[E], int N, int K, int32_t* out,
+                                 SelectShared& sh, bool have_range = false, uint32_t kmin = 0u,
+                                 uint32_t kmax = 0u, int32_t* rest = nullptr) {
+  const int tid = threadIdx.x;
+  const int nv = thread_rounds<E>(N);
+  auto valid = [&](int e) { return e < nv; };
+  if (K <= 0) return;
+  if (K >= N) {
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (valid(e)) out[e * kSelThreads + tid] = e * kSelThreads + tid;
+    return;
+  }
+  uint32_t key[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) key[e] = f2key(sc[e]);
+  // the output base lives in a VGPR pair: held in SGPRs through the
+  // selection it was spilled and re-read for every store
+  uint64_t obase = (uint64_t)(uintptr_t)out;
+  asm volatile("" : "+v"(obase));
+  int32_t* const o = (int32_t*)(uintptr_t)obase;
+  block_topk_each<E>(
+      key, N, K,
+      [&](int e, bool ok, bool keep, int before) {
+        const int i = e * kSelThreads + tid;
+        if (keep) {
+          if (before < K) o[before] = i;  // exactly K kept; the bound guards memory
+        } else if (REST && ok) {
+          if (i - before < N - K) rest[i - before] = i;
+        }
+      },
+      sh, have_range, kmin, kmax);
 }
 
 }  // namespace trevs

@@ -303,7 +303,10 @@ __global__ __launch_bounds__(64 * NW) void relevance_kernel(RelArgs a) {
   const float zz = zsq + __shfl_xor(zsq, 32, 64);
   const float rr = rsum + __shfl_xor(rsum, 32, 64);
   const float iz = 1.f / fmaxf(sqrtf(zz), 1e-12f);
-  if (half == 0 && tok_ok) a.rel[(size_t)b * N + tok] = sqrtf(rr * iz * iz / (float)Mb);
+  if (half == 0 && tok_ok) {
+    a.rel[(size_t)b * N + tok] = sqrtf(rr * iz * iz / (float)Mb);
+    if (a.inv_norm) a.inv_norm[(size_t)b * N + tok] = iz;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -569,7 +572,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
       for (int x = 1; x < TG; ++x) rr += rpart[x][t];
       const float zz = zsq[zb] + __shfl_xor(zsq[zb], 32, 64);
       const float iz = 1.f / fmaxf(sqrtf(zz), 1e-12f);
-      if (half == 0 && tok0 + t < N) a.rel[(size_t)b * N + tok0 + t] = sqrtf(rr * iz * iz / (float)Mb);
+      if (half == 0 && tok0 + t < N) {
+        a.rel[(size_t)b * N + tok0 + t] = sqrtf(rr * iz * iz / (float)Mb);
+        if (a.inv_norm) a.inv_norm[(size_t)b * N + tok0 + t] = iz;
+      }
     }
   }
 }
@@ -625,6 +631,7 @@ __global__ __launch_bounds__(kMergeTokens * kMergeGroups, 8) void relevance_merg
     }
     const float iz = 1.f / fmaxf(sqrtf(zz), 1e-12f);
     a.rel[(size_t)b * N + i] = sqrtf(rr * iz * iz / (float)Mb);
+    if (a.inv_norm) a.inv_norm[(size_t)b * N + i] = iz;
   }
 }
 
@@ -687,7 +694,7 @@ __global__ __launch_bounds__(kSelThreads) void norm_stats_kernel(NormArgs a) {
 // with temperature (Eq. (6)), branch weights and the consistency reward
 // (Eq. (7)), then the stable top-K.
 // ---------------------------------------------------------------------------
-template <int E>
+template <int E, bool REST>
 __global__ __launch_bounds__(kSelThreads) void fuse_topk_kernel(SelArgs a) {
   __shared__ SelectShared sh;
   const int b = blockIdx.x, tid = threadIdx.x, N = a.N;
@@ -727,8 +734,9 @@ __global__ __launch_bounds__(kSelThreads) void fuse_topk_kernel(SelArgs a) {
   // with lam >= 0 every score is a sum of non-negative terms, so the keys lie
   // in [key(+0), 0xffffffff] and the selection needs no min/max reduction
   // (the bound spans the same 31 bits as the exact range once any score is 0)
-  block_topk_write<E>(sc, N, a.K, a.kept_idx + (size_t)b * a.K, sh, a.lam >= 0.f, f2key(0.f),
-                      0xffffffffu);
+  block_topk_write<E, REST>(sc, N, a.K, a.kept_idx + (size_t)b * a.K, sh, a.lam >= 0.f, f2key(0.f),
+                            0xffffffffu, REST ? a.rest + (size_t)b * (N - a.K) : nullptr);
+  if (a.pick_ctrl && tid < kPickCtrl) a.pick_ctrl[b * kPickCtrl + tid] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -753,7 +761,9 @@ __global__ __launch_bounds__(kSelThreads) void budget_topk_kernel(SelArgs a) {
   const SelMask<E> by_text = block_topk_mask<E>([&](int e) { return f2key(st[e]); }, N, a.K_t, sh);
   const SelMask<E> by_sal = block_topk_mask<E>(
       [&](int e) { return (by_text >> e) & 1u ? 0u : f2key(sv[e]); }, N, a.K - a.K_t, sh);
-  block_write_mask<E>(by_text | by_sal, a.K, a.kept_idx + (size_t)b * a.K, sh);
+  block_write_mask<E>(by_text | by_sal, a.K, a.kept_idx + (size_t)b * a.K, sh, N,
+                      a.rest ? a.rest + (size_t)b * (N - a.K) : nullptr);
+  if (a.pick_ctrl && tid < kPickCtrl) a.pick_ctrl[b * kPickCtrl + tid] = 0;
 }
 
 template <int E>
@@ -929,9 +939,15 @@ hipError_t launch_norm_stats(const NormArgs& a, int B, hipStream_t s) {
 }
 
 hipError_t launch_prellm_select(const SelArgs& a, int B, hipStream_t s) {
-#define CALL(E) hipLaunchKernelGGL(fuse_topk_kernel<E>, dim3(B), dim3(kSelThreads), 0, s, a)
-  TREVS_SELECT_SWITCH(select_e(a.N), CALL)
+  if (a.rest) {
+#define CALL(E) hipLaunchKernelGGL((fuse_topk_kernel<E, true>), dim3(B), dim3(kSelThreads), 0, s, a)
+    TREVS_SELECT_SWITCH(select_e(a.N), CALL)
 #undef CALL
+  } else {
+#define CALL(E) hipLaunchKernelGGL((fuse_topk_kernel<E, false>), dim3(B), dim3(kSelThreads), 0, s, a)
+    TREVS_SELECT_SWITCH(select_e(a.N), CALL)
+#undef CALL
+  }
   return hipGetLastError();
 }
 
