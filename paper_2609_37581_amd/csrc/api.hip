@@ -53,7 +53,8 @@ trevs_status record(void* const* events, int slot, hipStream_t s) {
 // ------------------------------------------------------------------ stage 1
 struct PrellmLayout {
   size_t row_stats, inv_tnorm, sal, rel, stats, rel_part, total;
-  size_t inv_norm, pivots, ctrl, picks, gram, pick_part, rest, mx, dist, cand, cand_dist;  // diversity set
+  size_t inv_norm, pivots, ctrl, picks, gram, pick_part, rest, mx, near_piv, near_pick, cand, cand_piv, cand_pick,
+      cand_dist, mask;  // diversity set
   RelPlan rel_plan;
   PickPlan picks_plan;
 };
@@ -128,7 +129,7 @@ PrellmLayout prellm_layout(const trevs_prellm_args* a) {
   L.rel_part = off;  // partial products of a feature-dimension split
   off = align_up(off + L.rel_plan.part_floats() * sizeof(float));
   L.inv_norm = L.pivots = L.ctrl = L.picks = L.gram = L.pick_part = off;
-  L.rest = L.mx = L.dist = L.cand = L.cand_dist = off;
+  L.rest = L.mx = L.near_piv = L.near_pick = L.cand = L.cand_piv = L.cand_pick = L.cand_dist = L.mask = off;
   L.picks_plan = PickPlan{};
   if (a->k_div > 0) {
     const int K_r = a->k_keep - a->k_div;
@@ -148,10 +149,14 @@ PrellmLayout prellm_layout(const trevs_prellm_args* a) {
       take(L.pick_part, p.n_psplit * B * N);
     } else {
       take(L.rest, B * R);
-      take(L.mx, p.n_mx * B * R);
-      take(L.dist, B * N);
+      take(L.mx, B * R);
+      take(L.near_piv, B * N);
+      take(L.near_pick, B * N);
       take(L.cand, B * p.C);
+      take(L.cand_piv, B * p.C);
+      take(L.cand_pick, B * p.C);
       take(L.cand_dist, B * p.C);
+      take(L.mask, B * p.C * p.mask_words);
     }
   }
   L.total = off;
@@ -468,7 +473,7 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
   ra.split_slabs = rp.split_slabs;
   ra.part = reinterpret_cast<float*>(w + L.rel_part);
   ra.zpart = ra.part + (size_t)rp.n_split * a->B * a->M_max * a->N;
-  ra.inv_norm = a->k_div > 0 ? reinterpret_cast<float*>(w + L.inv_norm) : nullptr;
+  ra.inv_norm = L.picks_plan.rounds > 0 ? reinterpret_cast<float*>(w + L.inv_norm) : nullptr;
   TREVS_TRY(record(a->events, 2, s));
   TREVS_HIP(launch_relevance(ra, rp, a->dtype, s));
   TREVS_TRY(record(a->events, 3, s));
@@ -506,6 +511,7 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
   sa.kept_idx = a->k_div > 0 ? pivots : a->kept_idx;
   sa.K_t = budget_text_count(a->textual_ratio, K_r);
   sa.rest = L.picks_plan.rounds > 0 ? reinterpret_cast<int32_t*>(w + L.rest) : nullptr;
+  sa.rest_mx = reinterpret_cast<uint32_t*>(w + L.mx);
   sa.pick_ctrl = a->k_div > 0 ? reinterpret_cast<int32_t*>(w + L.ctrl) : nullptr;
   TREVS_TRY(record(a->events, 6, s));
   if (budget)
@@ -522,11 +528,15 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
     pa.R = a->N - K_r;
     pa.pivots = pivots;
     pa.rest = reinterpret_cast<const int32_t*>(w + L.rest);
-    pa.inv_norm = reinterpret_cast<const float*>(w + L.inv_norm);
+    pa.inv_norm = reinterpret_cast<float*>(w + L.inv_norm);
     pa.G = reinterpret_cast<float*>(w + L.gram);
     pa.part = reinterpret_cast<float*>(w + L.pick_part);
-    pa.mx = reinterpret_cast<float*>(w + L.mx);
-    pa.dist = reinterpret_cast<float*>(w + L.dist);
+    pa.mx = reinterpret_cast<uint32_t*>(w + L.mx);
+    pa.near_piv = reinterpret_cast<float*>(w + L.near_piv);
+    pa.near_pick = reinterpret_cast<float*>(w + L.near_pick);
+    pa.cand_piv = reinterpret_cast<float*>(w + L.cand_piv);
+    pa.cand_pick = reinterpret_cast<float*>(w + L.cand_pick);
+    pa.mask = reinterpret_cast<uint32_t*>(w + L.mask);
     pa.ctrl = reinterpret_cast<int32_t*>(w + L.ctrl);
     pa.cand = reinterpret_cast<int32_t*>(w + L.cand);
     pa.cand_dist = reinterpret_cast<float*>(w + L.cand_dist);

@@ -85,6 +85,15 @@ __device__ __forceinline__ f32x16 mfma_frag(const u32x4 (&a)[NQ], const u32x4 (&
 // Row of the 32x32 output block held by register r of a lane in half `half`.
 __device__ __forceinline__ int mfma_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
 
+// The diagonal element (col, col) of an output block, in both lanes of column
+// col: exactly one of the two half-waves holds it, the other adds zero.
+__device__ __forceinline__ float mfma_diag(const f32x16& c, int half, int col) {
+  float v = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v = mfma_row(r, half) == col ? c[r] : v;
+  return v + __shfl_xor(v, 32, 64);
+}
+
 __device__ __forceinline__ u32x4 ldg16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 __device__ __forceinline__ u32x4 ldg16_stream(const void* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));

@@ -20,9 +20,12 @@ namespace trevs {
 // cores, each a 64x64 block.  Bytes past a row's end (a partial last slab)
 // load as zero.  The tile is written in place and, off the diagonal, also
 // transposed; both go through LDS and out as 16-byte runs of whole rows.
-// G is written with nontemporal stores: the picks read it back long after it
-// has left the caches, and cached stores would evict operand slabs the other
-// resident workgroups still read.
+// Diagonal tiles also write 1/max(||z_i||, 1e-12) from G_ii.  G is written
+// with nontemporal stores: the picks read it back long after it has left the
+// caches, and cached stores would evict operand slabs the other resident
+// workgroups still read.  Products over lists take the k-steps in the order of
+// the full matrix (a.natural: that of the 256-row tiles), so that a product is
+// the same, bit for bit, wherever it is formed.
 // ---------------------------------------------------------------------------
 constexpr int kGramTile = 128;
 constexpr int kGramThreads = 256;
@@ -98,8 +101,10 @@ __host__ __device__ constexpr int gram_grid(int per_b, int B) {
 
 // What a Gram launch computes.  kGramFull: all pairs of a sample's tokens.
 // kGramPool: all pairs of a list of tokens (a.rows).  kGramMax: for every
-// token of one list (a.cols) the maximum over each row tile of another
-// (a.rows), so that the products themselves are never written.
+// token of one list (a.cols) the maximum over another (a.rows), so that the
+// products themselves are never written; row tiles meet in integer atomics, one
+// for each column of a tile (a partial maximum for each row tile had to be read back
+// by the one workgroup that selects the pool).
 enum { kGramFull = 0, kGramPool = 1, kGramMax = 2 };
 
 __device__ __forceinline__ bool gram_done(const GramArgs& a, int b) {
@@ -148,7 +153,7 @@ __device__ __forceinline__ const int32_t* gram_list_rows(const GramArgs& a, int 
 // that nothing reads any more.
 template <int T, int MB, int NB>
 __device__ __forceinline__ void gram_max_store(const GramArgs& a, const f32x16 (&acc)[MB][NB], const float* izr,
-                                               float* red, int b, int tp, int tc, int wj, int wi) {
+                                               float* red, int b, int tc, int wj, int wi) {
   const int tid = threadIdx.x, half = (tid >> 5) & 1, col = tid & 31;
   const int32_t* cols = a.cols + (size_t)b * a.n_cols;
   float mx[NB];
@@ -173,7 +178,7 @@ __device__ __forceinline__ void gram_max_store(const GramArgs& a, const f32x16 (
   __syncthreads();
   for (int c = tid; c < T; c += blockDim.x)
     if (tc * T + c < a.n_cols)
-      a.mx[((size_t)tp * a.B + b) * a.n_cols + tc * T + c] = fmaxf(red[c], red[T + c]);
+      atomicMax(&a.mx[(size_t)b * a.n_cols + tc * T + c], f2key(fmaxf(red[c], red[T + c])));
 }
 
 __device__ __forceinline__ int gram_swizzle(int r, int c) { return c ^ ((r >> 1) & 7); }
@@ -202,10 +207,16 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   const int rb = a.row_bytes;
   int nj = a.N, ni = a.N;  // tokens along the rows and columns
   const int32_t *rows = nullptr, *cols = nullptr;
-  __shared__ float izr[T];
+  __shared__ float izr[MODE == kGramFull ? 1 : T], izc[MODE == kGramPool ? T : 1], dr[MODE == kGramPool ? T : 1],
+      dc[MODE == kGramPool ? T : 1];
   if (MODE != kGramFull) {
     rows = cols = gram_list_rows(a, b, nj);
     ni = nj;
+    if (MODE == kGramPool) {  // tokens past the list have distance -inf: nothing is nearer
+      const int i = (tid < T ? tj * T : ti * T - T) + tid, ic = min(i, nj - 1);
+      (tid < T ? izr : izc)[tid & (T - 1)] = a.inv_norm[(size_t)b * a.N + rows[ic]];
+      (tid < T ? dr : dc)[tid & (T - 1)] = i < nj ? a.dist[(size_t)b * nj + ic] + kNearMargin : -INFINITY;
+    }
     if (MODE == kGramMax) {
       if (tj * T >= nj) return;
       cols = a.cols + (size_t)b * a.n_cols;
@@ -261,17 +272,22 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
     for (int n = 0; n < 2; ++n)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
-  auto frag = [&](const uint8_t* base, int row, u32x4 (&f)[4]) {
+  // k-step q: half h holds chunk 4h + q, or 2q + h in natural order.  The
+  // rows a lane reads (32 apart) share the swizzle.
+  const bool natural = MODE != kGramFull && a.natural;
+  uint32_t fo[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      f[q] = *reinterpret_cast<const u32x4*>(base + row * 128 + gram_swizzle(row, 4 * half + q) * 16);
+  for (int q = 0; q < 4; ++q) fo[q] = col * 128 + gram_swizzle(col, natural ? 2 * q + half : 4 * half + q) * 16;
+  auto frag = [&](const uint8_t* base, int row0, u32x4 (&f)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[q] = *reinterpret_cast<const u32x4*>(base + row0 * 128 + fo[q]);
   };
   auto compute = [&](const uint8_t* st) {
     u32x4 fa[2][4], fb[2][4];
 #pragma unroll
-    for (int m = 0; m < 2; ++m) frag(st, wj * 64 + m * 32 + col, fa[m]);
+    for (int m = 0; m < 2; ++m) frag(st, wj * 64 + m * 32, fa[m]);
 #pragma unroll
-    for (int n = 0; n < 2; ++n) frag(st + SLAB, wi * 64 + n * 32 + col, fb[n]);
+    for (int n = 0; n < 2; ++n) frag(st + SLAB, wi * 64 + n * 32, fb[n]);
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -298,11 +314,52 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   }
   if constexpr (MODE == kGramMax) {
     __syncthreads();  // the operand slabs are no longer read
-    gram_max_store<T, 2, 2>(a, acc, izr, reinterpret_cast<float*>(lds), b, tj, ti, wj, wi);
+    gram_max_store<T, 2, 2>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
     return;
   }
   // output: register r of block (m, n) is row wj*64 + m*32 + mfma_row(r),
   // column wi*64 + n*32 + col of the tile
+  if (MODE == kGramFull && tj == ti) {  // the diagonal tile holds ||z_i||^2
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int jl = wj * 64 + m * 32 + mfma_row(r, half), il = wi * 64 + n * 32 + col;
+          const int i = ti * T + il;
+          if (jl == il && i < N)
+            a.inv_norm[(size_t)b * N + i] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
+        }
+  }
+  if constexpr (MODE == kGramPool) {
+    // mask words of the tile, 32 tokens each: of row j, bit col where j may
+    // bring col nearer (one ballot per register: a word for each half-wave's
+    // row); off the diagonal of column i, bit row where i may bring row nearer
+    uint32_t* mask = a.mask + (size_t)b * nj * a.mask_words;
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const int c = wi * 64 + n * 32 + col;
+        const float iz = izc[c], d = dc[c];
+        uint32_t wrow = 0u, wcol = 0u;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = mfma_row(r, half), j = wj * 64 + m * 32 + row;
+          const float nd = 1.f - acc[m][n][r] * iz * izr[j];
+          const unsigned long long bal = __ballot(nd < d);
+          wrow = lane == mfma_row(r, 0) ? (uint32_t)bal : wrow;
+          wrow = lane == mfma_row(r, 1) ? (uint32_t)(bal >> 32) : wrow;
+          wcol |= nd < dr[j] ? 1u << row : 0u;
+        }
+        wcol |= __shfl_xor(wcol, 32, 64);
+        const int j = tj * T + wj * 64 + m * 32 + lane, i = ti * T + c;
+        const int jw = (tj * T + wj * 64) / 32 + m, iw = (ti * T + wi * 64) / 32 + n;
+        if (lane < 32 && j < nj && iw < a.mask_words) mask[(size_t)j * a.mask_words + iw] = wrow;
+        if (lane < 32 && tj != ti && i < nj && jw < a.mask_words) mask[(size_t)i * a.mask_words + jw] = wcol;
+      }
+  }
   // The tile leaves through LDS, 32 rows j at a time, as 16-byte runs of
   // whole rows: tA (rows j, stride TA: 16-byte aligned rows, the half-waves'
   // writes on disjoint banks) for G[j, i]; off the diagonal tB (rows i, odd
@@ -555,11 +612,24 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
     }
   }
   if constexpr (MODE == kGramMax) {  // (the loop ended on a barrier)
-    gram_max_store<T, 4, 4>(a, acc, izr, reinterpret_cast<float*>(lds), b, tj, ti, wj, wi);
+    gram_max_store<T, 4, 4>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
     return;
   }
   // register r of block (m, n) is row wj*128 + m*32 + mfma_row(r), column
   // wi*128 + n*32 + col of the tile
+  if (MODE == kGramFull && tj == ti) {  // the diagonal tile holds ||z_i||^2
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int n = 0; n < 4; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int jl = wj * 128 + m * 32 + mfma_row(r, half), il = wi * 128 + n * 32 + col;
+          const int i = ti * T + il;
+          if (jl == il && i < N)
+            a.inv_norm[(size_t)b * N + i] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
+        }
+  }
   // The tile leaves through LDS, 32 rows j at a time, and is stored as
   // 16-byte runs of whole rows (each lane storing 4 bytes, or 16-byte runs
   // of a few bytes per row, writes G at a fraction of the rate): tA holds
@@ -623,6 +693,51 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Inverse norms of listed bf16 tokens, from the diagonal of their products with
+// themselves in the k order of the Gram matrix, so that a round's distances are
+// those of the Gram matrix.  One wave per 32 tokens, operands straight from
+// memory; a ring of slabs keeps 48 loads in flight (with 16 issued and awaited
+// together, 480 of 2,880 tokens x 16 took 30 us instead of 15).  fp32 keeps the
+// norms of the relevance pass, which are sums in fp32 as well: the multiplies
+// alone would take 55 us here.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(64) void gram_norms_kernel(GramArgs a) {
+  const int lane = threadIdx.x, half = lane >> 5, col = lane & 31;
+  const int b = blockIdx.y, rb = a.row_bytes;
+  const int tok = a.rows[(size_t)b * a.n_rows + min((int)blockIdx.x * 32 + col, a.n_rows - 1)];
+  const uint8_t* src = reinterpret_cast<const uint8_t*>(a.Z) + ((size_t)b * a.N + tok) * rb;
+  const int c0 = a.natural ? half : 4 * half, cs = a.natural ? 2 : 1;
+  const int n_slabs = (rb + 127) / 128;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  constexpr int U = 12;
+  u32x4 z[U][4];
+  auto load = [&](int s, u32x4 (&dst)[4]) {  // chunks past the row's end read its first
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int off = s * 128 + (c0 + cs * q) * 16;
+      dst[q] = ldg16(src + (off < rb ? off : 0));
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) load(u, z[u]);
+  for (int s0 = 0; s0 < n_slabs; s0 += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      u32x4 v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = (s0 + u) * 128 + (c0 + cs * q) * 16 < rb ? z[u][q] : zero4();
+      load(s0 + u + U, z[u]);
+      __builtin_amdgcn_sched_barrier(0);
+      acc = mfma_frag(v, v, acc, BF16{});
+    }
+  }
+  const float zz = mfma_diag(acc, half, col);
+  if (half == 0) a.inv_norm[(size_t)b * a.N + tok] = 1.f / fmaxf(sqrtf(fmaxf(zz, 0.f)), 1e-12f);
+}
+
 // ---------------------------------------------------------------- kernels
 // One tile per workgroup.
 template <class In, int MODE>
@@ -643,7 +758,7 @@ __device__ __forceinline__ bool gram_any_left(const GramArgs& a) {
   return __syncthreads_or(left);
 }
 template <class In>
-__global__ __launch_bounds__(kGramThreads, 2) void gram_left_kernel(GramArgs a, int n_work) {
+__global__ __launch_bounds__(kGramThreads) void gram_left_kernel(GramArgs a, int n_work) {
   if (!gram_any_left(a)) return;
   for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
     gram_tile<In, kGramFull>(a, w);
@@ -687,8 +802,16 @@ hipError_t launch_gram_full(const GramArgs& g0, int dtype, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_gram_norms(const GramArgs& g0, hipStream_t s) {
+  GramArgs g = g0;
+  g.natural = gram256_ok(1, g.N, g.row_bytes);
+  hipLaunchKernelGGL(gram_norms_kernel, dim3((g.n_rows + 31) / 32, g.B), dim3(64), 0, s, g);
+  return hipGetLastError();
+}
+
 hipError_t launch_gram_pool(const GramArgs& g0, int dtype, hipStream_t s) {
   GramArgs g = g0;
+  g.natural = gram256_ok(dtype, g.N, g.row_bytes);
   g.n_tiles = (g.n_rows + kGramTile - 1) / kGramTile;
   const dim3 grid(gram_grid(gram_tiles(g.n_tiles), g.B));
   if (dtype == 1)
@@ -700,6 +823,7 @@ hipError_t launch_gram_pool(const GramArgs& g0, int dtype, hipStream_t s) {
 
 hipError_t launch_gram_max(const GramArgs& g0, int tile, int dtype, hipStream_t s) {
   GramArgs g = g0;
+  g.natural = gram256_ok(dtype, g.N, g.row_bytes);
   g.n_rtiles = (g.n_rows + tile - 1) / tile;
   g.n_ctiles = (g.n_cols + tile - 1) / tile;
   const dim3 grid(gram_grid(g.n_rtiles * g.n_ctiles, g.B));

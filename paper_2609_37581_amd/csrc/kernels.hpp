@@ -72,6 +72,7 @@ struct SelArgs {
   // pool rounds the N - K other tokens, ascending (each null without)
   int32_t* pick_ctrl;
   int32_t* rest;
+  uint32_t* rest_mx;         // [B,N - K], zeroed
 };
 
 // ---------------------------------------------------------------- stage 2
@@ -123,9 +124,9 @@ struct ScoreArgs {
 // Control words of one sample's picks, zeroed by the pivot selection.
 // kCtrlPicks: tokens picked so far; kCtrlRound: picks before the last round;
 // kCtrlBound: distance (float bits) that no token outside the round's pool
-// exceeds; kCtrlTie: the first token outside it at that distance.
+// exceeds by more than kNearMargin.
 constexpr int kPickCtrl = 4;
-enum { kCtrlPicks = 0, kCtrlRound = 1, kCtrlTie = 2, kCtrlBound = 3 };
+enum { kCtrlPicks = 0, kCtrlRound = 1, kCtrlBound = 2 };
 
 struct GramArgs {
   const void* Z;             // [B,N,d]
@@ -141,24 +142,36 @@ struct GramArgs {
   const int32_t* cols;       // [B,n_cols]
   int n_rows, n_cols;
   int n_rtiles, n_ctiles;
+  bool natural;              // k order of the 256-row tiles (set by the launchers)
   bool by_round;             // the rows are the last round's picks, not all of them
-  const float* inv_norm;     // [B,N] 1 / max(||z_i||, 1e-12)
-  float* mx;                 // [n_rtiles,B,n_cols] maxima over each row tile
+  float* inv_norm;           // [B,N] 1 / max(||z_i||, 1e-12); set from G by launch_gram_full
+  uint32_t* mx;              // [B,n_cols] maxima, as keys (f2key), over 0 or what is there
+  // pool: bit i of row j of mask [B,n_rows,mask_words] is set where token j may
+  // bring token i nearer than dist [B,n_rows] (see kNearMargin)
+  uint32_t* mask;
+  int mask_words;
+  const float* dist;
 };
+// Distances formed with inverse norms of the relevance pass are within this of
+// those formed with the norms of the Gram matrix: the two sums of d squares
+// differ by less than 1e-5 of the norm, and a distance by that times the cosine.
+constexpr float kNearMargin = 2e-5f;
 bool gram256_ok(int dtype, int N, int row_bytes);  // 256-row tiles can be used
 // G of all N tokens; with ctrl, of the samples that are not finished.
 hipError_t launch_gram_full(const GramArgs& g, int dtype, hipStream_t s);
 // G of the listed tokens (rows).
 hipError_t launch_gram_pool(const GramArgs& g, int dtype, hipStream_t s);
-// Maxima over row tiles of `tile` (128, or 256 where gram256_ok).
+// Maxima, by tiles of `tile` rows and columns (128, or 256 where gram256_ok).
 hipError_t launch_gram_max(const GramArgs& g, int tile, int dtype, hipStream_t s);
+// inv_norm of the listed bf16 tokens (rows), as launch_gram_full would set it.
+hipError_t launch_gram_norms(const GramArgs& g, hipStream_t s);
 
 // How the K_d picks are made (see pick_plan).
 struct PickPlan {
   int rounds;                // pool rounds before the full Gram matrix (0: none)
   int C, ldc;                // pool size, row stride of its Gram matrix
+  int mask_words;            // 32-bit words of a row of its mask, a multiple of 4
   int row_tile;              // row tile of the first round's distances
-  int n_mx;                  // most row tiles of any round
   int ldg;                   // row stride of the full Gram matrix
   int n_psplit;              // pivot splits of the initial distances over the full Gram matrix
   size_t gram_floats(int N) const;  // floats of a sample's Gram matrix, full or of the pool
@@ -170,14 +183,19 @@ struct PickArgs {
   int B, N, K_r, K_d, R;     // R = N - K_r
   const int32_t* pivots;     // [B,K_r] ascending
   const int32_t* rest;       // [B,R] ascending, the other tokens (pool rounds)
-  const float* inv_norm;     // [B,N]
+  float* inv_norm;           // [B,N]
   float* G;                  // [B,N,ldg], or [B,C,ldc]
   float* part;               // [n_psplit,B,N]: per split, max over its pivots j of G_ij / ||z_j||
-  float* mx;                 // [n_mx,B,R]
-  float* dist;               // [B,N] distance to the selected set, -inf once picked (pool rounds)
   int32_t* ctrl;             // [B,kPickCtrl]
+  // pool rounds
+  uint32_t* mx;              // [B,R] keys, zeroed by the pivot selection
+  float* near_piv;           // [B,N] max over the pivots j of G_ij / ||z_j||
+  float* near_pick;          // [B,N] least distance to a pick of an earlier round, -inf once picked
   int32_t* cand;             // [B,C] pool tokens, ascending
-  float* cand_dist;          // [B,C]
+  float* cand_piv;           // [B,C] their near_piv,
+  float* cand_pick;          // [B,C] near_pick
+  float* cand_dist;          // [B,C] and distance, from the relevance pass's norms
+  uint32_t* mask;            // [B,C,mask_words]
   int32_t* picks;            // [B,K_d]
   int32_t* kept_idx;         // [B,K_r+K_d] ascending
   int32_t* div_idx;          // [B,K_d] picks in pick order, or null

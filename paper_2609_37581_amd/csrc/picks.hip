@@ -73,60 +73,71 @@ __global__ __launch_bounds__(kFpsInitThreads) void fps_init_kernel(PickArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Pool of a round: one workgroup per sample brings the distances of the
+// Pool of a round: one workgroup per sample brings what is known of the
 // sample's other tokens (rest) up to date with the maxima that the list
 // products left (round 0: over the pivots; later: over the last round's
-// picks), and keeps the C farthest, in index order.  No token outside the pool
-// is farther than the C-th largest distance (the bound), and those at that
-// distance follow the pool's in index order.
+// picks, as minus the least distance), and keeps the C farthest, in index
+// order.  The distances here are formed with the norms of the relevance pass,
+// which every token has; no token outside the pool is farther than the C-th
+// largest of them (the bound) by more than the two norms differ.
 // ---------------------------------------------------------------------------
 template <int E>
-__global__ __launch_bounds__(kSelThreads) void pool_select_kernel(PickArgs a, int round, int row_tile) {
+__global__ __launch_bounds__(kSelThreads) void pool_select_kernel(PickArgs a, int round) {
   __shared__ SelectShared sh;
-  __shared__ int first_tie;
   const int b = blockIdx.x, tid = threadIdx.x, R = a.R, C = a.p.C;
   if (picks_done(a, b)) return;
   int32_t* ctrl = a.ctrl + b * kPickCtrl;
-  const int n_rows = round ? ctrl[kCtrlPicks] - ctrl[kCtrlRound] : a.K_r;
-  const int n_tiles = (n_rows + row_tile - 1) / row_tile;
   const int32_t* rest = a.rest + (size_t)b * R;
-  float* dist = a.dist + (size_t)b * a.N;
-  const float* mxp = a.mx + (size_t)b * R;
-  const size_t tstride = (size_t)a.B * R;
-  if (tid == 0) first_tie = INT_MAX;
-  float d[E];
+  float* near_piv = a.near_piv + (size_t)b * a.N;
+  float* near_pick = a.near_pick + (size_t)b * a.N;
+  uint32_t* mx = a.mx + (size_t)b * R;
+  float d[E], v[E];
   int tok[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    d[e] = -INFINITY;
-    tok[e] = rest[min(e * kSelThreads + tid, R - 1)];
+    const int i = min(e * kSelThreads + tid, R - 1);
+    d[e] = key2f(mx[i]);
+    tok[e] = rest[i];
   }
-  for (int t = 0; t < n_tiles; ++t) {
-    float v[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = mxp[t * tstride + min(e * kSelThreads + tid, R - 1)];
+  for (int e = 0; e < E; ++e)  // the next round's maxima start over
+    if (e * kSelThreads + tid < R) mx[e * kSelThreads + tid] = 0u;
+  if (round == 0) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) d[e] = fmaxf(d[e], v[e]);
-  }
-  {
-    float v[E];
-    const float* src = round ? dist : a.inv_norm + (size_t)b * a.N;
+    for (int e = 0; e < E; ++e)
+      if (e * kSelThreads + tid < R) {
+        near_piv[tok[e]] = d[e];
+        near_pick[tok[e]] = INFINITY;
+      }
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = src[tok[e]];
+    for (int e = 0; e < E; ++e) v[e] = a.inv_norm[(size_t)b * a.N + tok[e]];
 #pragma unroll
-    for (int e = 0; e < E; ++e) d[e] = round ? (-d[e] < v[e] ? -d[e] : v[e]) : 1.f - d[e] * v[e];
+    for (int e = 0; e < E; ++e) d[e] = 1.f - d[e] * v[e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = near_pick[tok[e]];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      d[e] = -d[e] < v[e] ? -d[e] : v[e];
+      if (e * kSelThreads + tid < R) near_pick[tok[e]] = d[e];
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = 1.f - near_piv[tok[e]] * a.inv_norm[(size_t)b * a.N + tok[e]];
+#pragma unroll
+    for (int e = 0; e < E; ++e) d[e] = d[e] < v[e] ? d[e] : v[e];
   }
   uint32_t key[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (e * kSelThreads + tid < R) dist[tok[e]] = d[e];
-    key[e] = f2key(d[e]);
-  }
+  for (int e = 0; e < E; ++e) key[e] = f2key(d[e]);
   int32_t* cand = a.cand + (size_t)b * C;
   float* cand_dist = a.cand_dist + (size_t)b * C;
+  float* cand_piv = a.cand_piv + (size_t)b * C;
+  float* cand_pick = a.cand_pick + (size_t)b * C;
   auto put = [&](int at, int e) {
     cand[at] = tok[e];
     cand_dist[at] = d[e];
+    cand_piv[at] = near_piv[tok[e]];
+    cand_pick[at] = near_pick[tok[e]];
   };
   float bound = -INFINITY;
   if (C >= R) {
@@ -135,48 +146,358 @@ __global__ __launch_bounds__(kSelThreads) void pool_select_kernel(PickArgs a, in
       if (e * kSelThreads + tid < R) put(e * kSelThreads + tid, e);
   } else {
     uint32_t thr;
-    int tie = INT_MAX;
     block_topk_each<E>(
-        key, R, C,
-        [&](int e, bool ok, bool keep, int before) {
-          if (keep && before < C) put(before, e);
-          if (ok && !keep && key[e] == thr) tie = min(tie, tok[e]);
-        },
-        sh, false, 0u, 0u, &thr);
+        key, R, C, [&](int e, bool, bool keep, int before) { if (keep && before < C) put(before, e); }, sh, false, 0u,
+        0u, &thr);
     bound = key2f(thr);
-    if (tie != INT_MAX) atomicMin(&first_tie, tie);
   }
-  __syncthreads();
-  if (tid == 0) {
-    ctrl[kCtrlTie] = first_tie;
-    ctrl[kCtrlBound] = __float_as_int(bound);
-  }
+  if (tid == 0) ctrl[kCtrlBound] = __float_as_int(bound);
 }
 
 // ---------------------------------------------------------------------------
-// The picks, one workgroup per sample, over the pool of a round or (FULL) over
-// all tokens, with the distances in registers: element e of thread t is entry
-// (e / CH) * CH * 1024 + t * CH + e % CH, so that rows of G load as vectors of
-// CH values.
-// A step that reduces over the workgroup and then waits for a row of G takes
-// about 2 us, so the picks are made in batches.  The entries with the largest
-// distances (at most kBatch: those in the first bins of a scale that starts at
-// the largest) go with their mutual distances to LDS; one wave picks among
-// them, without a barrier, for as long as the best of them is above every
-// other distance; then all entries take the rows of the picks at once.
-// Where more than kBatch entries share the first bin the scale is refined, and
-// where that many tie exactly the batch takes them by index.
-// A pick must also come before every token outside the pool: its distance is
-// above the round's bound, or equal and earlier in index order.  The round
-// ends where that fails; at K_d picks the kept list is written.
+// The picks.  A step that reduces over the workgroup and then waits for a row
+// of G takes about 2 us, so one workgroup per sample makes them in batches.
+// The entries with the largest distances (at most kBatch: those in the first
+// bins of a scale that starts at the largest) go with their mutual distances
+// to LDS; one wave picks among them, without a barrier, for as long as the
+// best of them is above every other entry; then all entries take the rows of
+// the picks at once.  Where more than kBatch entries share the first bin the
+// scale is refined, and where that many tie exactly the batch takes them by
+// index.  Distances are compared as order-preserving integers (f2key), whose
+// maximum takes one instruction per step of a wave reduction; 0, below every
+// key, marks selected entries.
 // ---------------------------------------------------------------------------
 constexpr int kMaxPool = 4096;  // entries of a pool (four per thread)
 constexpr int kBatch = 64;
-constexpr int kBins = 512;     // of the scale; at most 64 of TREVS_MAX_FPS_N indices each
-constexpr int kZooms = 6;      // refinements of the scale, by 16 each
+constexpr int kBins = 512;      // of the scale; at most 64 of TREVS_MAX_FPS_N indices each
+constexpr int kZooms = 6;       // refinements of the scale, by 16 each
 static_assert(TREVS_MAX_FPS_N <= kBins * kBatch, "a bin of indices fits a batch");
 static_assert(TREVS_MAX_FPS_N / 32 <= kSelThreads, "a word of the kept list per thread");
+static_assert(kBins == 8 * kWave, "eight bins a lane");
 
+struct PickShared {
+  uint32_t red[kSelWaves], red_out[kSelWaves];
+  uint32_t hist[kBins];
+  uint32_t bkey[kBatch];           // the batch: keys, inverse norms, entries
+  float biz[kBatch];
+  int bc[kBatch];
+  uint32_t sub[kBatch][kBatch + 1];  // their mutual distances, as keys
+  int pc[kBatch];                  // the picks: entries, inverse norms, places in the batch
+  float piz[kBatch];
+  int pslot[kBatch];
+  int n_batch, n_new;
+  uint32_t bits[kSelThreads];      // a bit per token
+  int wtot[kSelWaves];
+};
+
+// A distance as a key; not-a-number, which brings nothing nearer, as the largest.
+__device__ __forceinline__ uint32_t dist_key(float d) { return d == d ? f2key(d) : 0xffffffffu; }
+
+__device__ __forceinline__ uint32_t block_max_u32(uint32_t v, uint32_t* red) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  v = wave_max_u32(v);
+  if (lane == 0) red[wave] = v;
+  __syncthreads();
+  return wave_max_u32(lane < kSelWaves ? red[lane] : 0u);
+}
+
+// Bit i of sh.bits: token i is a pivot, or one of the first np picks.
+__device__ __forceinline__ void mark_selected(const PickArgs& a, int b, int np, PickShared& sh) {
+  const int tid = threadIdx.x, N = a.N;
+  if (tid < (N + 31) / 32) sh.bits[tid] = 0u;
+  __syncthreads();
+  for (int p = tid; p < a.K_r; p += kSelThreads) {
+    const int j = min(max(a.pivots[(size_t)b * a.K_r + p], 0), N - 1);
+    atomicOr(&sh.bits[j >> 5], 1u << (j & 31));
+  }
+  for (int p = tid; p < np; p += kSelThreads) {
+    const int j = min(max(a.picks[(size_t)b * a.K_d + p], 0), N - 1);
+    atomicOr(&sh.bits[j >> 5], 1u << (j & 31));
+  }
+  __syncthreads();
+}
+
+// The kept list: pivots and all picks in ascending order, one word of 32
+// tokens per thread.
+__device__ __forceinline__ void write_kept(const PickArgs& a, int b, PickShared& sh) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, K = a.K_r + a.K_d;
+  mark_selected(a, b, a.K_d, sh);
+  uint32_t word = tid < (a.N + 31) / 32 ? sh.bits[tid] : 0u;
+  const int cnt = __popc(word), inc = wave_incl_scan(cnt, lane);
+  if (lane == kWave - 1) sh.wtot[wave] = inc;
+  __syncthreads();
+  const int wt = lane < kSelWaves ? sh.wtot[lane] : 0, wi = wave_incl_scan(wt, lane);
+  int at = __builtin_amdgcn_readlane(wi - wt, wave) + inc - cnt;
+  int32_t* kept = a.kept_idx + (size_t)b * K;
+  while (word) {
+    if (at < K) kept[at] = tid * 32 + __builtin_ctz(word);  // K set; the bound guards memory
+    ++at;
+    word &= word - 1;
+  }
+}
+
+// The scale of a batch.  bin(key, entry): steps below the largest key, kBins
+// past the scale; with ties, the index bin of an entry at the largest key.
+struct BatchScale {
+  uint32_t top;
+  float ftop, scale;
+  bool ties;
+  int ishift, cut;
+  __device__ __forceinline__ int bin(uint32_t key, int c) const {
+    if (ties) return key == top ? c >> ishift : kBins;
+    return key >= top ? 0 : (int)fminf((ftop - key2f(key)) * scale, (float)kBins);
+  }
+};
+
+// The cut: the most bins of the scale that hold at most kBatch entries with
+// key above `floor_key`.  sh.hist holds zeros.  range: width of the scale, refined
+// here.  each(f) calls f(key, entry) for every entry of the thread.
+template <class Each>
+__device__ __forceinline__ void batch_cut(BatchScale& s, float& range, uint32_t floor_key, Each each, PickShared& sh) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  for (int zoom = 0;; ++zoom) {
+    s.ties = zoom >= kZooms || !(range > 0.f);
+    s.scale = (float)kBins / range;
+    each([&](uint32_t key, int c) {
+      if (key > floor_key) {
+        const int bin = s.bin(key, c);
+        if (bin < kBins) atomicAdd(&sh.hist[bin], 1u);
+      }
+    });
+    __syncthreads();
+    int c[8], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sum += c[j] = (int)sh.hist[8 * lane + j];
+    int before = wave_incl_scan(sum, lane) - sum, mine = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      before += c[j];
+      mine += before <= kBatch ? 1 : 0;  // bins 0..8*lane+j hold at most kBatch entries
+    }
+    s.cut = wave_reduce_bits(mine, 0, [](int x, int y) { return x + y; });
+    if (s.cut > 0 || s.ties) return;  // uniform (a bin of indices holds at most kBatch)
+    range *= 1.f / 16.f;
+    __syncthreads();  // hist has been read
+    if (tid < kBins) sh.hist[tid] = 0u;
+    __syncthreads();
+  }
+}
+
+// The picks among the m entries of a batch, by the calling wave (all lanes).
+// limit: most picks; out: the largest key that is not in the batch.  The picks' places in
+// the batch go to lanes 0, 1, ... of `won`; returns their number.
+__device__ __forceinline__ int batch_picks(int m, int limit, uint32_t out, const BatchScale& s, const PickShared& sh,
+                                           int& won) {
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t d = lane < m ? sh.bkey[lane] : 0u;
+  const uint32_t cl = (uint32_t)sh.bc[min(lane, m - 1)];
+  const int n_max = min(m, limit);
+  won = 0;
+  int k = 0;
+  for (; k < n_max; ++k) {
+    const uint32_t vm = wave_max_u32(d);
+    // above every other entry, or the top itself: the first pick, and ties by index
+    if (vm <= out && !(vm == s.top && (s.ties || k == 0))) break;  // uniform
+    unsigned long long bal = __ballot(d == vm);
+    if (bal & (bal - 1)) {  // uniform: a tie goes to the lower index
+      const uint32_t c0 = wave_min_u32(d == vm ? cl : 0xffffffffu);
+      bal = __ballot(d == vm && cl == c0);
+    }
+    const int w = (int)__builtin_ctzll(bal);
+    d = min(d, sh.sub[w][lane]);
+    d = lane == w ? 0u : d;
+    won = lane == k ? w : won;
+  }
+  return k;
+}
+
+// ---------------------------------------------------------------------------
+// Picks of a round, over the pool.  Distances are those of the Gram matrix
+// (its diagonal gives the norms).  Few pairs matter: entry i is brought nearer
+// by pick j only if their distance is below that of i, which the mask of the
+// pool's Gram matrix marks.  So the batch's mask rows go to LDS, mutual
+// distances are read from G for marked pairs, and a pick updates only the
+// marked entries (reading whole rows of G, 9 KB for each pick at 37 GB/s a
+// CU, took 12 us of a batch's 32).
+// A pick must also be farther than every token outside the pool: its distance
+// is above the round's bound and the margin between the two norms.  The round
+// ends where that fails; at K_d picks the kept list is written.
+// ---------------------------------------------------------------------------
+constexpr int kHits = 4096;  // marked (pick, entry) pairs taken at once
+constexpr int kMaxPoolPicks = kMaxPool / 2;
+
+__global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a) {
+  __shared__ PickShared sh;
+  __shared__ uint32_t key[kMaxPool];
+  __shared__ float iz[kMaxPool];
+  __shared__ u32x4 mrow[kBatch][kMaxPool / 128];
+  __shared__ uint32_t hits[kHits];
+  __shared__ int n_hits;
+  __shared__ uint16_t order[kMaxPoolPicks];  // entries picked in this round
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int C = a.p.C, ldc = a.p.ldc, mw4 = a.p.mask_words / 4, K_d = a.K_d, N = a.N;
+  if (picks_done(a, b)) return;
+  int32_t* ctrl = a.ctrl + b * kPickCtrl;
+  const int t0 = ctrl[kCtrlPicks];
+  int t = t0;
+  const float bound = __int_as_float(ctrl[kCtrlBound]);
+  const uint32_t floor_key = bound > -INFINITY ? f2key(bound + kNearMargin) : f2key(-INFINITY);
+  const int32_t* cand = a.cand + (size_t)b * C;
+  const float* G = a.G + (size_t)b * C * ldc;
+  const u32x4* mask = reinterpret_cast<const u32x4*>(a.mask) + (size_t)b * C * mw4;
+  int32_t* picks = a.picks + (size_t)b * K_d;
+  for (int c = tid; c < C; c += kSelThreads) {
+    const float z = 1.f / fmaxf(sqrtf(fmaxf(G[(size_t)c * ldc + c], 0.f)), 1e-12f);
+    const float d = 1.f - a.cand_piv[(size_t)b * C + c] * z, dp = a.cand_pick[(size_t)b * C + c];
+    iz[c] = z;
+    key[c] = dp == -INFINITY ? 0u : f2key(dp < d ? dp : d);
+  }
+  // a round over few candidates is short of NaN and selected entries alike:
+  // keys of NaN distances (above infinity's) never win
+  const uint32_t inf_key = f2key(INFINITY);
+  const float range0 = bound > -INFINITY ? -1.f : 2.f;  // down to the bound (-1), or anywhere (distances: 0..2)
+  float range = range0;
+  BatchScale s;
+  s.ishift = 0;
+  while ((C - 1) >> s.ishift >= kBins) ++s.ishift;
+  auto each = [&](auto f) {
+    for (int c = tid; c < C; c += kSelThreads) f(key[c], c);
+  };
+  __syncthreads();
+  for (int c = tid; c < C; c += kSelThreads)
+    if (key[c] > inf_key) key[c] = 0u;
+  while (t < K_d) {
+    uint32_t v = 0u;
+    each([&](uint32_t k, int) { v = max(v, k); });
+    if (tid == 0) sh.n_batch = n_hits = 0;
+    if (tid < kBins) sh.hist[tid] = 0u;
+    s.top = block_max_u32(v, sh.red);
+    if (s.top <= floor_key) break;  // uniform
+    s.ftop = key2f(s.top);
+    if (range < 0.f) range = s.ftop - bound;
+    batch_cut(s, range, floor_key, each, sh);
+    // ---- the batch, and the largest key outside it
+    uint32_t out = floor_key;
+    each([&](uint32_t k, int c) {
+      if (k > floor_key && s.bin(k, c) < s.cut) {
+        const int at = atomicAdd(&sh.n_batch, 1);
+        if (at < kBatch) {
+          sh.bkey[at] = k;
+          sh.biz[at] = iz[c];
+          sh.bc[at] = c;
+        }
+      } else {
+        out = max(out, k);
+      }
+    });
+    out = block_max_u32(out, sh.red_out);
+    const int m = min(sh.n_batch, kBatch);  // at least the top
+    // ---- its mask rows, then its mutual distances where marked
+    for (int p = tid; p < m * mw4; p += kSelThreads) {
+      const int x = p / mw4, wd = p - x * mw4;
+      mrow[x][wd] = mask[(size_t)sh.bc[x] * mw4 + wd];
+    }
+    __syncthreads();
+    constexpr int SUBS = kBatch * kBatch / kSelThreads;
+    float g[SUBS];
+    bool on[SUBS];
+#pragma unroll
+    for (int k = 0; k < SUBS; ++k) {
+      const int x = min(wave + k * kSelWaves, m - 1), y = min(lane, m - 1), cy = sh.bc[y];
+      on[k] = (reinterpret_cast<const uint32_t*>(mrow[x])[cy >> 5] >> (cy & 31)) & 1u;
+      g[k] = G[on[k] ? (size_t)sh.bc[x] * ldc + cy : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < SUBS; ++k) {
+      const int x = min(wave + k * kSelWaves, m - 1), y = min(lane, m - 1);
+      sh.sub[wave + k * kSelWaves][lane] = on[k] ? dist_key(1.f - g[k] * sh.biz[y] * sh.biz[x]) : 0xffffffffu;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      int won;
+      const int k = batch_picks(m, K_d - t, out, s, sh, won);
+      if (lane == 0) sh.n_new = k;
+      if (lane < k) {
+        const int c = sh.bc[won];
+        sh.pc[lane] = c;
+        sh.piz[lane] = sh.biz[won];
+        sh.pslot[lane] = won;
+        key[c] = 0u;
+        order[t - t0 + lane] = (uint16_t)c;
+      }
+    }
+    __syncthreads();
+    const int np = sh.n_new;
+    if (np == 0) break;  // uniform
+    // ---- marked entries that can still be picked in this round
+    // (marks cluster, so a wave takes a row's nonzero words two at a time, a
+    // lane to a bit)
+    for (int q = wave; q < np; q += kSelWaves) {
+      const uint32_t* row = reinterpret_cast<const uint32_t*>(mrow[sh.pslot[q]]);
+      for (int w0 = 0; w0 < 4 * mw4; w0 += kWave) {
+        unsigned long long words = __ballot(w0 + lane < 4 * mw4 && row[min(w0 + lane, 4 * mw4 - 1)] != 0u);
+        while (words) {  // uniform
+          const int lo = (int)__builtin_ctzll(words);
+          words &= words - 1;
+          int hi = -1;
+          if (words) {
+            hi = (int)__builtin_ctzll(words);
+            words &= words - 1;
+          }
+          const int wl = lane < 32 ? lo : hi, c = (w0 + wl) * 32 + (lane & 31);
+          const bool hit = wl >= 0 && ((row[max(w0 + wl, 0)] >> (lane & 31)) & 1u) && key[max(c, 0)] > floor_key;
+          const unsigned long long bal = __ballot(hit);
+          if (bal) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&n_hits, (int)__popcll(bal));
+            base = __builtin_amdgcn_readfirstlane(base);
+            const int at = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+            if (hit && at < kHits) hits[at] = (uint32_t)q << 16 | (uint32_t)c;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    auto take = [&](int q, int c) {
+      const float gq = G[(size_t)sh.pc[q] * ldc + c];
+      atomicMin(&key[c], dist_key(1.f - gq * iz[c] * sh.piz[q]));
+    };
+    if (n_hits <= kHits) {
+      for (int h = tid; h < n_hits; h += kSelThreads) take(hits[h] >> 16, hits[h] & 0xffffu);
+    } else {  // most pairs marked: whole rows
+#pragma unroll 4
+      for (int q = 0; q < np; ++q)
+        for (int c = tid; c < C; c += kSelThreads) take(q, c);
+    }
+    t += np;
+    // a batch that is far from full asks for a wider scale
+    if (m < kBatch / 2) range = m < kBatch / 8 ? range0 : 2.f * range;
+    __syncthreads();  // the keys, and n_hits
+  }
+  __syncthreads();  // order
+  for (int p = t0 + tid; p < t; p += kSelThreads) {
+    const int c = order[p - t0], tok = cand[c];
+    picks[p] = tok;
+    if (a.div_idx) a.div_idx[(size_t)b * K_d + p] = tok;
+    a.near_pick[(size_t)b * N + tok] = -INFINITY;  // for the next round
+    a.inv_norm[(size_t)b * N + tok] = iz[c];
+  }
+  if (tid == 0) {
+    ctrl[kCtrlPicks] = t;
+    ctrl[kCtrlRound] = t0;
+  }
+  if (t < K_d) return;  // uniform
+  __syncthreads();      // the picks written above
+  write_kept(a, b, sh);
+}
+
+// ---------------------------------------------------------------------------
+// Picks over the Gram matrix of all tokens, from the pivots' partial maxima, or
+// from where the rounds stopped (after_rounds).  The keys stay in registers:
+// element e of thread t is token (e / CH) * CH * 1024 + t * CH + e % CH, so that
+// rows of G load as vectors of CH values, up to U rows at a time.
+// ---------------------------------------------------------------------------
 template <int CH>
 struct Chunk;
 template <>
@@ -197,79 +518,55 @@ struct Chunk<4> {
   }
 };
 
-template <int E, bool FULL>
-__global__ __launch_bounds__(kSelThreads) void pick_kernel(PickArgs a) {
+template <int E>
+__global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
   constexpr int CH = E < 4 ? E : 4;        // entries per vector
   constexpr int NR = E / CH;               // vectors per thread and row
   constexpr int U = E <= 2 ? 16 : 32 / E;  // rows in flight
   typedef typename Chunk<CH>::T Vec;
-  __shared__ float red[kSelWaves], red_out[kSelWaves];
-  __shared__ int wtot[kSelWaves];
-  __shared__ uint32_t hist[kBins];
-  __shared__ float bdist[kBatch], biz[kBatch], piz[kBatch];
-  __shared__ int bc[kBatch], pc[kBatch];
-  __shared__ float sub[kBatch][kBatch + 1];
-  __shared__ int n_batch, n_new;
-  __shared__ uint32_t bits[kSelThreads];
-  static_assert(kBins == 8 * kWave, "eight bins a lane");
+  __shared__ PickShared sh;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int n = FULL ? a.N : a.p.C, ldg = FULL ? a.p.ldg : a.p.ldc, K_d = a.K_d, N = a.N, K_r = a.K_r;
+  const int N = a.N, ldg = a.p.ldg, K_d = a.K_d;
   if (picks_done(a, b)) return;
-  int32_t* ctrl = a.ctrl + b * kPickCtrl;
+  const int32_t* ctrl = a.ctrl + b * kPickCtrl;
+  const bool after_rounds = a.p.rounds > 0;
   const int t0 = ctrl[kCtrlPicks];
   int t = t0;
-  const bool after_rounds = FULL && a.p.rounds > 0;
-  const float bound = FULL ? -INFINITY : __int_as_float(ctrl[kCtrlBound]);
-  const int tie_tok = FULL ? INT_MAX : ctrl[kCtrlTie];
-  const int32_t* cand = FULL ? nullptr : a.cand + (size_t)b * n;
-  const float* G = a.G + (size_t)b * n * ldg;
+  const float* G = a.G + (size_t)b * N * ldg;
+  const float* inv_norm = a.inv_norm + (size_t)b * N;
   int32_t* picks = a.picks + (size_t)b * K_d;
-  const int words = (N + 31) / 32;
   auto entry = [&](int e) { return (e / CH) * CH * kSelThreads + tid * CH + e % CH; };
-  auto token = [&](int c) { return FULL ? c : cand[c]; };
-  // bit i: token i is a pivot, or one of the picks [0, np)
-  auto mark = [&](int np) {
-    if (tid < words) bits[tid] = 0u;
-    __syncthreads();
-    for (int p = tid; p < K_r; p += kSelThreads) {
-      const int j = min(max(a.pivots[(size_t)b * K_r + p], 0), N - 1);
-      atomicOr(&bits[j >> 5], 1u << (j & 31));
-    }
-    for (int p = tid; p < np; p += kSelThreads) {
-      const int j = min(max(picks[p], 0), N - 1);
-      atomicOr(&bits[j >> 5], 1u << (j & 31));
-    }
-    __syncthreads();
-  };
-  // selected entries and those past n hold distance -inf: they never win, and
-  // the row updates (a minimum) keep them there
-  float dist[E], iz[E];
-  if (FULL) mark(0);
+  // selected tokens and those past N hold key 0: they never win, and the row
+  // updates (a minimum) keep them there; so do tokens whose distance is not a number
+  float iz[E];
+  uint32_t key[E];
+  const uint32_t inf_key = f2key(INFINITY);
+  mark_selected(a, b, 0, sh);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int c = entry(e), cc = min(c, n - 1);
-    iz[e] = a.inv_norm[(size_t)b * N + token(cc)];
-    float d;
-    if (!FULL) {
-      d = a.cand_dist[(size_t)b * n + cc];
-    } else if (after_rounds) {
-      d = a.dist[(size_t)b * N + cc];
+    const int c = entry(e), cc = min(c, N - 1);
+    iz[e] = inv_norm[cc];
+    float mx, least = INFINITY;
+    if (after_rounds) {
+      mx = a.near_piv[(size_t)b * N + cc];
+      least = a.near_pick[(size_t)b * N + cc];
     } else {
-      float mx = a.part[(size_t)b * N + cc];
+      mx = a.part[(size_t)b * N + cc];
       for (int sp = 1; sp < a.p.n_psplit; ++sp) mx = fmaxf(mx, a.part[((size_t)sp * a.B + b) * N + cc]);
-      d = 1.f - mx * iz[e];
     }
-    if (c >= n || (FULL && ((bits[cc >> 5] >> (cc & 31)) & 1u))) d = -INFINITY;
-    dist[e] = d;
+    const float d = 1.f - mx * iz[e];
+    const bool sel = c >= N || ((sh.bits[cc >> 5] >> (cc & 31)) & 1u) || least == -INFINITY;
+    const uint32_t k = f2key(least < d ? least : d);
+    key[e] = sel || k > inf_key ? 0u : k;
   }
-  // the rows of picks p[0, np) (entries pc, inverse norms piz), U at a time;
-  // every load of a group is issued before the first is used
+  // the rows of picks p[0, np) (sh.pc, sh.piz); every load of a group is
+  // issued before the first is used
   auto take_rows = [&](int np) {
     for (int q0 = 0; q0 < np; q0 += U) {
       Vec g[U][NR];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const float* row = G + (size_t)__builtin_amdgcn_readfirstlane(pc[min(q0 + u, np - 1)]) * ldg;
+        const float* row = G + (size_t)__builtin_amdgcn_readfirstlane(sh.pc[min(q0 + u, np - 1)]) * ldg;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
           const int c = entry(r * CH);
@@ -279,12 +576,10 @@ __global__ __launch_bounds__(kSelThreads) void pick_kernel(PickArgs a) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const float izw = piz[min(q0 + u, np - 1)];
+        const float izw = sh.piz[min(q0 + u, np - 1)];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const float nd = 1.f - Chunk<CH>::at(g[u][e / CH], e % CH) * iz[e] * izw;
-          dist[e] = nd < dist[e] ? nd : dist[e];
-        }
+        for (int e = 0; e < E; ++e)
+          key[e] = min(key[e], dist_key(1.f - Chunk<CH>::at(g[u][e / CH], e % CH) * iz[e] * izw));
       }
     }
   };
@@ -293,178 +588,94 @@ __global__ __launch_bounds__(kSelThreads) void pick_kernel(PickArgs a) {
       const int np = min(kBatch, t0 - p0);
       __syncthreads();
       if (tid < np) {
-        pc[tid] = min(max(picks[p0 + tid], 0), N - 1);
-        piz[tid] = a.inv_norm[(size_t)b * N + pc[tid]];
+        sh.pc[tid] = min(max(picks[p0 + tid], 0), N - 1);
+        sh.piz[tid] = inv_norm[sh.pc[tid]];
       }
       __syncthreads();
       take_rows(np);
     }
   }
-  auto eligible = [&](float d, int c) { return d > bound || (d == bound && d > -INFINITY && token(c) < tie_tok); };
-  // the scale starts as wide as a pick can lie below the top: down to the
-  // bound (-1), or anywhere (distances lie in 0..2)
-  const float range0 = bound > -INFINITY ? -1.f : 2.f;
-  float range = range0;
-  int ishift = 0;  // a bin of indices
-  while ((n - 1) >> ishift >= kBins) ++ishift;
+  float range = 2.f;
+  BatchScale s;
+  s.ishift = 0;
+  while ((N - 1) >> s.ishift >= kBins) ++s.ishift;
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) f(key[e], entry(e));
+  };
   while (t < K_d) {
-    // ---- the largest distance
-    float v = dist[0];
-#pragma unroll
-    for (int e = 1; e < E; ++e) v = fmaxf(v, dist[e]);
-    v = wave_max(v);
-    if (lane == 0) red[wave] = v;
-    if (tid == 0) n_batch = 0;
-    if (tid < kBins) hist[tid] = 0u;
-    __syncthreads();
-    const float top = wave_max(lane < kSelWaves ? red[lane] : -INFINITY);
-    if (!(top > -INFINITY) || !(top >= bound)) break;  // uniform
-    if (range < 0.f) range = top - bound;
-    // ---- the cut: the most bins of the scale that hold at most kBatch entries
-    bool ties = false;  // the scale is the index, of the entries at the top
-    float scale = 0.f;
-    int cut = 0;
-    auto bin_of = [&](float d, int c) {
-      if (ties) return d == top ? c >> ishift : kBins;
-      return d >= top ? 0 : (int)fminf((top - d) * scale, (float)kBins);
-    };
-    for (int zoom = 0;; ++zoom) {
-      ties = zoom >= kZooms || !(range > 0.f);
-      scale = (float)kBins / range;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int bin = bin_of(dist[e], entry(e));
-        if (bin < kBins && eligible(dist[e], entry(e))) atomicAdd(&hist[bin], 1u);
-      }
-      __syncthreads();
-      int c[8], sum = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sum += c[j] = (int)hist[8 * lane + j];
-      int before = wave_incl_scan(sum, lane) - sum, mine = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        before += c[j];
-        mine += before <= kBatch ? 1 : 0;  // bins 0..8*lane+j hold at most kBatch entries
-      }
-      cut = wave_reduce_bits(mine, 0, [](int x, int y) { return x + y; });
-      if (cut > 0 || ties) break;  // uniform (a bin of indices holds at most kBatch)
-      range *= 1.f / 16.f;
-      __syncthreads();  // hist has been read
-      if (tid < kBins) hist[tid] = 0u;
-      __syncthreads();
-    }
-    // ---- the batch, and the largest distance outside it
-    float out = bound;
+    uint32_t v = 0u;
+    each([&](uint32_t k, int) { v = max(v, k); });
+    if (tid == 0) sh.n_batch = 0;
+    if (tid < kBins) sh.hist[tid] = 0u;
+    s.top = block_max_u32(v, sh.red);
+    if (s.top == 0u) break;  // uniform
+    s.ftop = key2f(s.top);
+    batch_cut(s, range, 0u, each, sh);
+    uint32_t out = 0u;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int c = entry(e);
-      if (bin_of(dist[e], c) < cut && eligible(dist[e], c)) {
-        const int at = atomicAdd(&n_batch, 1);
+      if (key[e] > 0u && s.bin(key[e], c) < s.cut) {
+        const int at = atomicAdd(&sh.n_batch, 1);
         if (at < kBatch) {
-          bdist[at] = dist[e];
-          biz[at] = iz[e];
-          bc[at] = c;
+          sh.bkey[at] = key[e];
+          sh.biz[at] = iz[e];
+          sh.bc[at] = c;
         }
       } else {
-        out = fmaxf(out, dist[e]);
+        out = max(out, key[e]);
       }
     }
-    out = wave_max(out);
-    if (lane == 0) red_out[wave] = out;
-    __syncthreads();
-    const int m = min(n_batch, kBatch);
-    if (m == 0) break;  // uniform: the largest distance ties with an earlier token outside the pool
+    out = block_max_u32(out, sh.red_out);
+    const int m = min(sh.n_batch, kBatch);  // at least the top
     constexpr int SUBS = kBatch * kBatch / kSelThreads;
-    float sv[SUBS];
+    float g[SUBS];
 #pragma unroll
     for (int k = 0; k < SUBS; ++k) {
       const int x = min(wave + k * kSelWaves, m - 1), y = min(lane, m - 1);
-      sv[k] = G[(size_t)bc[x] * ldg + bc[y]];
+      g[k] = G[(size_t)sh.bc[x] * ldg + sh.bc[y]];
     }
 #pragma unroll
     for (int k = 0; k < SUBS; ++k) {
       const int x = min(wave + k * kSelWaves, m - 1), y = min(lane, m - 1);
-      sub[wave + k * kSelWaves][lane] = 1.f - sv[k] * biz[y] * biz[x];
+      sh.sub[wave + k * kSelWaves][lane] = dist_key(1.f - g[k] * sh.biz[y] * sh.biz[x]);
     }
     __syncthreads();
-    // ---- one wave picks among the batch
     if (wave == 0) {
-      const float floor_ = wave_max(lane < kSelWaves ? red_out[lane] : -INFINITY);
-      const int l = min(lane, m - 1);
-      float d = lane < m ? bdist[lane] : -INFINITY;
-      const int cl = bc[l];
-      const int n_max = min(m, K_d - t);
-      int won = 0, k = 0;  // lane k: the batch entry of pick k
-      for (; k < n_max; ++k) {
-        const float vm = wave_max(d);
-        // above every other entry, or the top itself: the first pick, and ties by index
-        if (!(vm > floor_) && !(vm == top && (ties || k == 0))) break;
-        unsigned long long bal = __ballot(d == vm);
-        if (bal & (bal - 1)) {  // uniform: a tie goes to the lower index
-          const uint32_t c0 = wave_min_u32(d == vm ? (uint32_t)cl : 0xffffffffu);
-          bal = __ballot(d == vm && (uint32_t)cl == c0);
-        }
-        const int w = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(bal));
-        const float nd = sub[w][lane];
-        d = nd < d ? nd : d;
-        d = lane == w ? -INFINITY : d;
-        won = lane == k ? w : won;
-      }
-      if (lane == 0) n_new = k;
+      int won;
+      const int k = batch_picks(m, K_d - t, out, s, sh, won);
+      if (lane == 0) sh.n_new = k;
       if (lane < k) {
-        const int c = bc[won], tok = token(c);
-        pc[lane] = c;
-        piz[lane] = biz[won];
-        picks[t + lane] = tok;
-        if (a.div_idx) a.div_idx[(size_t)b * K_d + t + lane] = tok;
+        const int c = sh.bc[won];
+        sh.pc[lane] = c;
+        sh.piz[lane] = sh.biz[won];
+        picks[t + lane] = c;
+        if (a.div_idx) a.div_idx[(size_t)b * K_d + t + lane] = c;
       }
     }
     __syncthreads();
-    const int np = n_new;
+    const int np = sh.n_new;
     if (np == 0) break;  // uniform
     take_rows(np);
     for (int q = 0; q < np; ++q) {
-      const int c = pc[q];
+      const int c = sh.pc[q];
 #pragma unroll
       for (int e = 0; e < E; ++e)
-        if (c == entry(e)) dist[e] = -INFINITY;
+        if (c == entry(e)) key[e] = 0u;
     }
     t += np;
-    // a batch that is far from full asks for a wider scale
-    if (m < kBatch / 2) range = m < kBatch / 8 ? range0 : 2.f * range;
+    if (m < kBatch / 2) range = m < kBatch / 8 ? 2.f : 2.f * range;
   }
   __syncthreads();  // the picks written above
-  if (!FULL) {  // picked tokens leave the distances that the next round reads
-    for (int p = t0 + tid; p < t; p += kSelThreads) a.dist[(size_t)b * N + picks[p]] = -INFINITY;
-    if (tid == 0) {
-      ctrl[kCtrlPicks] = t;
-      ctrl[kCtrlRound] = t0;
-    }
-    if (t < K_d) return;  // uniform
-  }
-  if (t < K_d) {  // only distances that are not numbers are left: token 0 stands in
+  if (t < K_d) {    // only distances that are not numbers are left: token 0 stands in
     for (int p = t + tid; p < K_d; p += kSelThreads) {
       picks[p] = 0;
       if (a.div_idx) a.div_idx[(size_t)b * K_d + p] = 0;
     }
-    t = K_d;
     __syncthreads();
   }
-  // ---- the kept list: pivots and picks in ascending order, one word of 32
-  // tokens per thread
-  mark(t);
-  uint32_t word = tid < words ? bits[tid] : 0u;
-  const int cnt = __popc(word), inc = wave_incl_scan(cnt, lane);
-  if (lane == kWave - 1) wtot[wave] = inc;
-  __syncthreads();
-  const int wt = lane < kSelWaves ? wtot[lane] : 0, wi = wave_incl_scan(wt, lane);
-  int at = __builtin_amdgcn_readlane(wi - wt, wave) + inc - cnt;
-  int32_t* kept = a.kept_idx + (size_t)b * (K_r + K_d);
-  while (word) {
-    if (at < K_r + K_d) kept[at] = tid * 32 + __builtin_ctz(word);  // K_r + K_d set; the bound guards memory
-    ++at;
-    word &= word - 1;
-  }
+  write_kept(a, b, sh);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -486,7 +697,8 @@ static double gram_us256(long wgs) { return 1.72 * ((wgs + 255) / 256); }
 // Pool rounds or the full Gram matrix at once, whichever is estimated to take
 // less.  The pool has room for 9/4 of the picks, and grows from there while its
 // Gram matrix takes no longer: to one workgroup per CU, or to two where pivots
-// are few (below a fifth of the tokens): a pick then leaves many more
+// are few (below a fifth of the tokens; not for fp32, where two take twice as
+// long): a pick then leaves many more
 // candidates behind, and the neediest sample of a batch decides.  Pool tokens that the K_d picks reach down
 // to, over K_d, on features of regions of 24 tokens: 1.2 with pivots 3/8 of
 // the tokens, 1.5 at 1/4, 2.0 at 3/16, 2.5-3.2 at 1/6, 8-11 at 1/12.
@@ -502,21 +714,23 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
   const int R = N - K_r;
   const bool big = gram256_ok(dtype, N, row_bytes);
   const double slabs = up(row_bytes, 128);
+  // stores of G at 4 TB/s, the initial distances; a pick reads a row at 37 GB/s
   const double full = slabs * (big ? gram_us256(B * tri(up(N, 256))) : gram_us128(B * tri(up(N, 128)), dtype)) +
-                      (double)B * N * N * 4 / 4e6 + 15;  // 4 TB/s for the stores, the initial distances
+                      B * 4e-6 * N * N / 4 + 15 + K_d * (0.25 + N * 4 / 37e3);
   long ct = up(9L * K_d / 4, kRoundTile);
-  const long room = 5L * K_r > N ? 256 : 512;
+  const long room = 5L * K_r > N || dtype != 1 ? 256 : 512;
   while (B * tri(ct + 1) <= room) ++ct;
   p.C = (int)std::min({(long)R, ct * kRoundTile, (long)kMaxPool});
   p.ldc = (int)up(p.C, 4) * 4;
   const double r128 = gram_us128(B * up(K_r, 128) * up(R, 128), dtype);
   const double r256 = gram_us256(B * up(K_r, 256) * up(R, 256));
+  p.mask_words = (int)up(p.C, 128) * 4;
   p.row_tile = big && r256 < r128 ? 256 : 128;
-  p.n_mx = (int)std::max(up(K_r, p.row_tile), up(K_d, kRoundTile));
-  const double pool = slabs * ((p.row_tile == 256 ? r256 : r128) + gram_us128(B * tri(up(p.C, 128)), dtype)) + 30;
-  // a round that finds nothing left to do takes about 9 us
-  p.rounds = pool < full && 2 * K_d <= kMaxPool ? (full > 1500 ? 3 : 2) : 0;
-  if (TREVS_PICK_ROUNDS >= 0) p.rounds = TREVS_PICK_ROUNDS;
+  // the pivots' norms, the pool selection, rounds that find nothing left to do
+  const double pool = slabs * ((p.row_tile == 256 ? r256 : r128) + gram_us128(B * tri(up(p.C, 128)), dtype)) +
+                      (dtype == 1 ? 0.3 * slabs : 0) + 10 + R / 700 + (p.C < R ? 27 : 0) + K_d * 0.35;
+  p.rounds = pool < full && K_d <= kMaxPoolPicks ? (full > 1500 ? 3 : 2) : 0;
+  if (TREVS_PICK_ROUNDS >= 0 && K_d <= kMaxPoolPicks) p.rounds = TREVS_PICK_ROUNDS;
   if (p.C >= R) p.rounds = std::min(p.rounds, 1);
   return p;
 }
@@ -541,9 +755,10 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
     g.cols = a.rest;
     g.n_cols = a.R;
     const int tile = round ? kRoundTile : p.row_tile;
+    if (round == 0 && dtype == 1 && (err = launch_gram_norms(g, s)) != hipSuccess) return err;
     if ((err = launch_gram_max(g, tile, dtype, s)) != hipSuccess) return err;
 #define CALL(E_) \
-  case E_: hipLaunchKernelGGL(pool_select_kernel<E_>, dim3(a.B), dim3(kSelThreads), 0, s, a, round, tile); break
+  case E_: hipLaunchKernelGGL(pool_select_kernel<E_>, dim3(a.B), dim3(kSelThreads), 0, s, a, round); break
     switch (select_e(a.R)) {
       CALL(1); CALL(2); CALL(4); CALL(8); CALL(16); CALL(32);
       default: return hipErrorInvalidValue;
@@ -553,14 +768,11 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
     g.n_rows = p.C;
     g.by_round = false;
     g.ldg = p.ldc;
+    g.mask = a.mask;
+    g.mask_words = p.mask_words;
+    g.dist = a.cand_dist;
     if ((err = launch_gram_pool(g, dtype, s)) != hipSuccess) return err;
-#define CALL(E_) \
-  case E_: hipLaunchKernelGGL((pick_kernel<E_, false>), dim3(a.B), dim3(kSelThreads), 0, s, a); break
-    switch (select_e(p.C)) {
-      CALL(1); CALL(2); CALL(4);
-      default: return hipErrorInvalidValue;
-    }
-#undef CALL
+    hipLaunchKernelGGL(pool_pick_kernel, dim3(a.B), dim3(kSelThreads), 0, s, a);
   }
   if (p.rounds > 0 && p.C >= a.R) return hipGetLastError();  // the pool held every token
   g.ldg = p.ldg;
@@ -569,7 +781,7 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
     hipLaunchKernelGGL(fps_init_kernel, dim3((a.N + kFpsInitThreads - 1) / kFpsInitThreads, a.B, p.n_psplit),
                        dim3(kFpsInitThreads), 0, s, a);
 #define CALL(E_) \
-  case E_: hipLaunchKernelGGL((pick_kernel<E_, true>), dim3(a.B), dim3(kSelThreads), 0, s, a); break
+  case E_: hipLaunchKernelGGL(full_pick_kernel<E_>, dim3(a.B), dim3(kSelThreads), 0, s, a); break
   switch (select_e(a.N)) {
     CALL(1); CALL(2); CALL(4); CALL(8); CALL(16); CALL(32);
     default: return hipErrorInvalidValue;

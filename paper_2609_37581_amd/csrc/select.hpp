@@ -352,10 +352,10 @@ __device__ SelMask<E> block_topk_mask(KeyF keyf, int N, int K, SelectShared& sh)
 
 // Writes the indices of the elements set in `mask` (K of them over the
 // workgroup) in ascending order to out[0..K), and, if rest is given, the other
-// indices below N to rest[0..N - K).
+// indices below N to rest[0..N - K) and zeros to rest_zero[0..N - K).
 template <int E>
 __device__ void block_write_mask(SelMask<E> mask, int K, int32_t* out, SelectShared& sh, int N = 0,
-                                 int32_t* rest = nullptr) {
+                                 int32_t* rest = nullptr, uint32_t* rest_zero = nullptr) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   auto lanes_below = [&](unsigned long long bal) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
@@ -373,7 +373,10 @@ __device__ void block_write_mask(SelMask<E> mask, int K, int32_t* out, SelectSha
     const int pos = (int)sh.wcnt[e * kSelWaves + wave] + lanes_below(__ballot(kp));
     const int i = e * kSelThreads + tid;
     if (kp && pos < K) out[pos] = i;  // exactly K kept; the bound guards memory
-    if (rest && !kp && i < N && i - pos < N - K) rest[i - pos] = i;
+    if (rest && !kp && i < N && i - pos < N - K) {
+      rest[i - pos] = i;
+      rest_zero[i - pos] = 0u;
+    }
   }
 }
 
@@ -425,11 +428,12 @@ __device__ __forceinline__ void block_topk_each(const uint32_t (&key)[E], int N,
 }
 
 // Stable top-K written as ascending indices to out[0..K); with REST the other
-// N - K indices go, ascending, to rest.
+// N - K indices go, ascending, to rest, and as many words of rest_zero are zeroed.
 template <int E, bool REST = false>
 __device__ void block_topk_write(const float (&sc)[E], int N, int K, int32_t* out,
                                  SelectShared& sh, bool have_range = false, uint32_t kmin = 0u,
-                                 uint32_t kmax = 0u, int32_t* rest = nullptr) {
+                                 uint32_t kmax = 0u, int32_t* rest = nullptr,
+                                 uint32_t* rest_zero = nullptr) {
   const int tid = threadIdx.x;
   const int nv = thread_rounds<E>(N);
   auto valid = [&](int e) { return e < nv; };
@@ -455,7 +459,10 @@ __device__ void block_topk_write(const float (&sc)[E], int N, int K, int32_t* ou
         if (keep) {
           if (before < K) o[before] = i;  // exactly K kept; the bound guards memory
         } else if (REST && ok) {
-          if (i - before < N - K) rest[i - before] = i;
+          if (i - before < N - K) {
+            rest[i - before] = i;
+            rest_zero[i - before] = 0u;
+          }
         }
       },
       sh, have_range, kmin, kmax);

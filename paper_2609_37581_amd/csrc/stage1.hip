@@ -735,7 +735,8 @@ __global__ __launch_bounds__(kSelThreads) void fuse_topk_kernel(SelArgs a) {
   // in [key(+0), 0xffffffff] and the selection needs no min/max reduction
   // (the bound spans the same 31 bits as the exact range once any score is 0)
   block_topk_write<E, REST>(sc, N, a.K, a.kept_idx + (size_t)b * a.K, sh, a.lam >= 0.f, f2key(0.f),
-                            0xffffffffu, REST ? a.rest + (size_t)b * (N - a.K) : nullptr);
+                            0xffffffffu, REST ? a.rest + (size_t)b * (N - a.K) : nullptr,
+                            REST ? a.rest_mx + (size_t)b * (N - a.K) : nullptr);
   if (a.pick_ctrl && tid < kPickCtrl) a.pick_ctrl[b * kPickCtrl + tid] = 0;
 }
 
@@ -762,7 +763,8 @@ __global__ __launch_bounds__(kSelThreads) void budget_topk_kernel(SelArgs a) {
   const SelMask<E> by_sal = block_topk_mask<E>(
       [&](int e) { return (by_text >> e) & 1u ? 0u : f2key(sv[e]); }, N, a.K - a.K_t, sh);
   block_write_mask<E>(by_text | by_sal, a.K, a.kept_idx + (size_t)b * a.K, sh, N,
-                      a.rest ? a.rest + (size_t)b * (N - a.K) : nullptr);
+                      a.rest ? a.rest + (size_t)b * (N - a.K) : nullptr,
+                      a.rest ? a.rest_mx + (size_t)b * (N - a.K) : nullptr);
   if (a.pick_ctrl && tid < kPickCtrl) a.pick_ctrl[b * kPickCtrl + tid] = 0;
 }
 
