@@ -42,7 +42,7 @@ struct RelArgs {
 
 // Launch shape of the relevance pass for one problem size.
 struct RelPlan {
-  bool stream;           // streaming kernel (rows of whole 128-byte slabs)
+  bool tail;             // rows end inside a 128-byte slab
   int MT;                // text rows per tile (32, 64 or 128)
   int tile_tokens;       // visual tokens per workgroup
   int tiles_per_sample;

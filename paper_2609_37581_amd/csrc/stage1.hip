@@ -151,170 +151,12 @@ __device__ __forceinline__ void tile_saliency(const RelArgs& a, int b, int tok0,
 }
 
 // ---------------------------------------------------------------------------
-// Relevance: one pass over the visual features Z.  A workgroup owns 32*NW
-// consecutive visual tokens of one sample; each wave owns 32 of them and
-// computes C[text j][token i] = t_j . z_i on the matrix cores, streaming the
-// feature dimension in slabs of SB bytes per row: the text slab goes through
-// LDS (shared by the waves), each wave's Z rows go straight from HBM into
-// registers.  Two register/LDS buffers alternate (A computes while B loads);
-// every load is issued unconditionally (out-of-range lanes read an
-// L2-resident dummy row and are masked where the data is used) so that the
-// compiler can wait for exactly the older buffer.  The same Z registers give
-// ||z_i||^2; the epilogue applies the norms, rectifies, squares and averages
-// over the valid text rows (Eq. (4)-(5)).  The workgroup also finishes the
-// head-mean saliency of its tokens from the prep statistics (Eq. (2)-(3)).
-// ---------------------------------------------------------------------------
-#ifndef TREVS_REL_NW
-#define TREVS_REL_NW 4
-#endif
-#ifndef TREVS_REL_SB
-#define TREVS_REL_SB 256
-#endif
-constexpr int kRelNW = TREVS_REL_NW;
-constexpr int kRelSB = TREVS_REL_SB;
-
-template <class In, int MT, int NW, int SB>
-__global__ __launch_bounds__(64 * NW) void relevance_kernel(RelArgs a) {
-  constexpr int MB = MT / 32;
-  constexpr int NT = 64 * NW;
-  constexpr int VT = 32 * NW;
-  constexpr int NF = SB / 128;       // 64-byte fragments per lane per slab
-  constexpr int HS = SB / 2;         // bytes of a slab row carried by one lane half
-  constexpr int LROW = SB + 16;      // padded LDS row stride
-  constexpr int CPR = SB / 16;       // 16-byte vectors per slab row
-  constexpr int TV = MT * CPR;       // 16-byte vectors per text slab
-  constexpr int TVT = (TV + NT - 1) / NT;
-  __shared__ __attribute__((aligned(16))) uint8_t tlds[2][MT * LROW];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, col = lane & 31;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
-  const int b = tile / a.tiles_per_sample;
-  const int tok0 = (tile - b * a.tiles_per_sample) * VT;
-  const int N = a.N, rb = a.row_bytes;
-  const int Mb = text_rows(a.text_len, b, a.M_max);
-  const int n_slabs = (rb + SB - 1) / SB;
-  const int n_pairs = (n_slabs + 1) / 2;
-
-  tile_saliency<In>(a, b, tok0, VT, NT, tid);
-
-  const int tok = tok0 + wave * 32 + col;
-  const bool tok_ok = tok < N;
-  const uint8_t* tbase = reinterpret_cast<const uint8_t*>(a.T) + (size_t)b * a.M_max * rb;
-  const uint8_t* dummy = tbase;  // always valid and hot in L2
-  const uint8_t* zrow = reinterpret_cast<const uint8_t*>(a.Z) +
-                        ((size_t)b * N + (tok_ok ? tok : N - 1)) * rb + half * HS;
-
-  auto load_z = [&](int s, u32x4 (&dst)[NF][4]) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int off = s * SB + f * 64 + q * 16;
-        dst[f][q] = ldg16_stream(off + half * HS < rb ? zrow + off : dummy);
-      }
-  };
-  auto load_t = [&](int s, int j0, u32x4 (&dst)[TVT]) {
-#pragma unroll
-    for (int k = 0; k < TVT; ++k) {
-      const int v = min(tid + k * NT, TV - 1), row = v / CPR, c = v - row * CPR;
-      const int off = s * SB + c * 16;
-      const bool ok = j0 + row < Mb && off < rb;
-      dst[k] = ldg16(ok ? tbase + (size_t)(j0 + row) * rb + off : dummy);
-    }
-  };
-  auto store_t = [&](int buf, int s, int j0, const u32x4 (&src)[TVT]) {
-#pragma unroll
-    for (int k = 0; k < TVT; ++k) {
-      const int v = tid + k * NT;
-      if (v < TV) {
-        const int row = v / CPR, c = v - row * CPR;
-        const bool ok = j0 + row < Mb && s * SB + c * 16 < rb;
-        *reinterpret_cast<u32x4*>(&tlds[buf][row * LROW + c * 16]) = ok ? src[k] : zero4();
-      }
-    }
-  };
-
-  float zsq = 0.f, rsum = 0.f;
-  for (int j0 = 0; j0 < Mb; j0 += MT) {
-    f32x16 acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mb][r] = 0.f;
-    auto compute = [&](const u32x4 (&z)[NF][4], int buf, int s) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const uint8_t* p = &tlds[buf][(mb * 32 + col) * LROW + half * HS];
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          u32x4 af[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) af[q] = *reinterpret_cast<const u32x4*>(p + f * 64 + 16 * q);
-          acc[mb] = mfma_frag(af, z[f], acc[mb], In{});
-        }
-      }
-      if (j0 == 0) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            zsq += (s * SB + half * HS + f * 64 + q * 16 < rb) ? sumsq(z[f][q], In{}) : 0.f;
-      }
-    };
-    u32x4 zA[NF][4], zB[NF][4], tA[TVT], tB[TVT];
-    load_t(0, j0, tA);
-    load_z(0, zA);
-    load_t(1, j0, tB);
-    load_z(1, zB);
-    store_t(0, 0, j0, tA);
-    __syncthreads();
-    for (int pr = 0; pr < n_pairs; ++pr) {
-      const int s = 2 * pr;
-      compute(zA, 0, s);
-      store_t(1, s + 1, j0, tB);
-      __syncthreads();
-      load_t(s + 2, j0, tA);
-      load_z(s + 2, zA);
-      compute(zB, 1, s + 1);
-      store_t(0, s + 2, j0, tA);
-      __syncthreads();
-      load_t(s + 3, j0, tB);
-      load_z(s + 3, zB);
-    }
-    // ---- epilogue of this text chunk: sum_j max(t_j.z_i / ||t_j||, 0)^2
-    const float* itn = a.inv_tnorm + (size_t)b * a.M_max;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      float w[16];  // every norm load before the first use
-#pragma unroll
-      for (int r = 0; r < 16; ++r) w[r] = itn[min(j0 + mb * 32 + mfma_row(r, half), a.M_max - 1)];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int j = j0 + mb * 32 + mfma_row(r, half);
-        if (j < Mb) {
-          const float c = fmaxf(acc[mb][r] * w[r], 0.f);
-          rsum = fmaf(c, c, rsum);
-        }
-      }
-    }
-    __syncthreads();  // the next chunk refills both LDS buffers
-  }
-  const float zz = zsq + __shfl_xor(zsq, 32, 64);
-  const float rr = rsum + __shfl_xor(rsum, 32, 64);
-  const float iz = 1.f / fmaxf(sqrtf(zz), 1e-12f);
-  if (half == 0 && tok_ok) {
-    a.rel[(size_t)b * N + tok] = sqrtf(rr * iz * iz / (float)Mb);
-    if (a.inv_norm) a.inv_norm[(size_t)b * N + tok] = iz;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Relevance, streaming variant for rows made of whole 128-byte slabs (text
-// tiles of 32, 64 or 128 rows).  Same arithmetic as relevance_kernel; a
-// workgroup of 4, 8 or 16 waves owns 256 tokens (12 waves own 192 tokens
-// at 64 text rows).  Stage s is the 128-byte slab s of the tile's Z rows and
-// of the MT text rows.  Every thread loads its share of a
+// Relevance: one pass over the visual features Z, C[text j][token i] = t_j . z_i
+// on the matrix cores (text tiles of 32, 64 or 128 rows).  The same Z fragments
+// give ||z_i||^2; the epilogue applies the norms, rectifies, squares and
+// averages over the valid text rows (Eq. (4)-(5)).  A workgroup of 4, 8 or 16
+// waves owns 256 tokens (12 waves own 192 tokens at 64 text rows).  Stage s is
+// the 128-byte slab s of the tile's Z rows and of the MT text rows.  Every thread loads its share of a
 // stage with coalesced 16-byte loads (8 lanes cover one 128-byte row
 // segment) into a ring of R register buffers, so R stages are in flight; at
 // each step the oldest buffer is written to one of two LDS buffers, the
@@ -323,7 +165,11 @@ __global__ __launch_bounds__(64 * NW) void relevance_kernel(RelArgs a) {
 // direct-to-LDS copies).  Rows are XOR-swizzled in 16-byte chunks so that
 // both the stage writes and the MFMA fragment reads of 16 consecutive rows
 // hit distinct banks.  Saliency (Eq. (2)-(3)) is computed while the first
-// stages load.  With SPLIT the workgroup covers one range of slabs and
+// stages load.  With TAIL rows end inside a slab: chunks past the end load the
+// row's first chunk (in bounds) and are stored as zeros.  (Such rows had a
+// kernel of their own with operands straight from memory: 8,208-byte rows, 74 text
+// rows, 2 x 3221 tokens 169 us a call there, 70 us here; 115 text rows, 6 x 9397
+// tokens 384 and 199 us.)  With SPLIT the workgroup covers one range of slabs and
 // writes raw partial products and ||z||^2 for relevance_merge_kernel.
 // ---------------------------------------------------------------------------
 constexpr int kStreamWaves = 8;
@@ -369,7 +215,7 @@ struct StreamTiling {
 };
 
 // (two waves per SIMD at four waves a workgroup: two workgroups per CU)
-template <class In, int MT, int R, int NW, bool SPLIT, int VB = 8>
+template <class In, int MT, int R, int NW, bool SPLIT, bool TAIL, int VB = 8>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_kernel(RelArgs a) {
   constexpr int NT = 64 * NW;
   constexpr int VT = 32 * VB;
@@ -400,7 +246,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
   const int N = a.N, rb = a.row_bytes;
   const int Mb = text_rows(a.text_len, b, a.M_max);
   const int s_begin = split * a.split_slabs;  // first slab of this split
-  const int n_slabs = SPLIT ? min(rb >> 7, s_begin + a.split_slabs) - s_begin : rb >> 7;
+  const int row_slabs = (rb + 127) >> 7;
+  const int n_slabs = SPLIT ? min(row_slabs, s_begin + a.split_slabs) - s_begin : row_slabs;
   const int n_iter = (n_slabs + U - 1) / U;  // stages padded to the unroll
 
   const float* itn = a.inv_tnorm + (size_t)b * a.M_max;
@@ -421,6 +268,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
   }
   const int sdst = cr * 128 + slab_swizzle(cr, cc) * 16;
   const uint8_t* tbase = reinterpret_cast<const uint8_t*>(a.T) + (size_t)b * a.M_max * rb;
+  // this thread's chunk of slab s (of the split) lies past the row's end
+  auto past_end = [&](int s) { return (s_begin + s) * 128 + cc * 16 >= rb; };
   const int tgi = wave % NTG, xg = wave / NTG;  // token group, text group
   // this lane's Z rows in the stage (token block zb): tgi*32*ZB + zb*32 + col
 
@@ -451,19 +300,28 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
     // re-read the last slab (still in L2) and are never multiplied
     u32x4 g[R][ZPT + TPT];
     auto load = [&](int s, u32x4 (&dst)[ZPT + TPT]) {
-      const int off = min(s, n_slabs - 1) * 128;
+      int off = min(s, n_slabs - 1) * 128;
+      if (TAIL && past_end(min(s, n_slabs - 1))) off = -(s_begin * 128 + cc * 16);
 #pragma unroll
       for (int k = 0; k < ZPT; ++k) dst[k] = ldg16_stream(zsrc[k] + off);
 #pragma unroll
       for (int k = 0; k < TPT; ++k) dst[ZPT + k] = ldg16(tsrc[k] + off);
     };
-    auto store = [&](uint8_t* st, const u32x4 (&src)[ZPT + TPT]) {
+    auto store = [&](uint8_t* st, const u32x4 (&src)[ZPT + TPT], int s) {
 #pragma unroll
       for (int k = 0; k < ZPT; ++k) *reinterpret_cast<u32x4*>(st + sdst + k * (NT / 8) * 128) = src[k];
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
         if (TEXT_EXACT || cr + (NT / 8) * k < MT)
           *reinterpret_cast<u32x4*>(st + ZBYTES + sdst + k * (NT / 8) * 128) = src[ZPT + k];
+      if (TAIL && s == n_slabs - 1 && past_end(s)) {  // (a select on the loaded vectors would wait for all of them)
+#pragma unroll
+        for (int k = 0; k < ZPT; ++k) *reinterpret_cast<u32x4*>(st + sdst + k * (NT / 8) * 128) = zero4();
+#pragma unroll
+        for (int k = 0; k < TPT; ++k)
+          if (TEXT_EXACT || cr + (NT / 8) * k < MT)
+            *reinterpret_cast<u32x4*>(st + ZBYTES + sdst + k * (NT / 8) * 128) = zero4();
+      }
     };
     f32x16 acc[ZB][MBW];
 #pragma unroll
@@ -512,7 +370,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
         uint8_t* st = c % 2 ? l1 : l0;
         // buffer (s % 2) was last read at step s - 2, before every wave
         // passed the barrier of step s - 1
-        store(st, g[c % R]);
+        store(st, g[c % R], s);
         load(s + R, g[c % R]);
         __syncthreads();
         if (s < n_slabs) compute(st);
@@ -829,17 +687,18 @@ RelPlan relevance_plan(int B, int N, int M_max, int row_bytes) {
   p.N = N;
   p.M_max = M_max;
   p.MT = M_max <= 32 ? 32 : (M_max <= 64 ? 64 : 128);
-  p.stream = row_bytes % 128 == 0;
-  p.tile_tokens = p.stream ? kStreamTokens : 32 * kRelNW;
+  p.tail = row_bytes % 128 != 0;
+  p.tile_tokens = kStreamTokens;
   p.tiles_per_sample = (N + p.tile_tokens - 1) / p.tile_tokens;
   p.n_split = 1;
-  p.split_slabs = row_bytes / 128;
+  const int slabs = (row_bytes + 127) / 128;
+  p.split_slabs = slabs;
   const long tiles = (long)B * p.tiles_per_sample;
   const long resident = (long)kNumCUs * (p.MT == 32 ? 2 : 1);
   // At 64 text rows a 192-token tile is taken when it streams fewer rows per
   // CU (tile rows times resident rounds): 576 = 3 x 192 tokens leave no
   // half-empty tile, and LLaVA-1.5 batch 64 ran 74.6 -> 69.0 us.
-  if (p.stream && p.MT == 64 && 2 * tiles > resident) {
+  if (p.MT == 64 && 2 * tiles > resident) {
     const long t192 = (long)B * ((N + kTile192 - 1) / kTile192);
     const long rows256 = kStreamTokens * ((tiles + resident - 1) / resident);
     const long rows192 = kTile192 * ((t192 + resident - 1) / resident);
@@ -848,8 +707,7 @@ RelPlan relevance_plan(int B, int N, int M_max, int row_bytes) {
       p.tiles_per_sample = (N + kTile192 - 1) / kTile192;
     }
   }
-  if (p.stream && 2 * tiles <= resident) {
-    const int slabs = row_bytes / 128;
+  if (2 * tiles <= resident) {
     const int want = (int)std::min<long>(kSplitRounds * resident / tiles, std::max(slabs / kSplitMinSlabs, 1));
     if (want > 1) {
       p.split_slabs = (slabs + want - 1) / want;
@@ -863,59 +721,49 @@ RelPlan relevance_plan(int B, int N, int M_max, int row_bytes) {
   return p;
 }
 
-template <class In>
-static void launch_rel_t(const RelArgs& a, int MT, hipStream_t s) {
-  const dim3 grid(a.B * a.tiles_per_sample), block(64 * kRelNW);
-  if (MT == 32)
-    hipLaunchKernelGGL((relevance_kernel<In, 32, kRelNW, kRelSB>), grid, block, 0, s, a);
-  else if (MT == 64)
-    hipLaunchKernelGGL((relevance_kernel<In, 64, kRelNW, kRelSB>), grid, block, 0, s, a);
-  else
-    hipLaunchKernelGGL((relevance_kernel<In, 128, kRelNW, kRelSB>), grid, block, 0, s, a);
-}
-
-template <class In, bool SPLIT>
+template <class In, bool SPLIT, bool TAIL>
 static void launch_rel_stream_t(const RelArgs& a, const RelPlan& p, hipStream_t s) {
   const dim3 grid(a.B * a.tiles_per_sample * a.n_split);
   constexpr int NW128 = TREVS_STREAM_NW128;
   const int MT = p.MT;
   if constexpr (!SPLIT) {  // the split runs on 256-token tiles only
     if (MT == 64 && p.tile_tokens == kTile192) {
-      hipLaunchKernelGGL((relevance_stream_kernel<In, 64, 2, 12, false, 6>), grid, dim3(64 * 12), 0, s, a);
+      hipLaunchKernelGGL((relevance_stream_kernel<In, 64, 2, 12, false, TAIL, 6>), grid, dim3(64 * 12), 0, s, a);
       return;
     }
   }
   if (MT == 32)
-    hipLaunchKernelGGL((relevance_stream_kernel<In, 32, kStreamR32, 4, SPLIT>), grid, dim3(64 * 4), 0, s, a);
+    hipLaunchKernelGGL((relevance_stream_kernel<In, 32, kStreamR32, 4, SPLIT, TAIL>), grid, dim3(64 * 4), 0, s, a);
   else if (MT == 64)
-    hipLaunchKernelGGL((relevance_stream_kernel<In, 64, kStreamR64, kStreamWaves, SPLIT>), grid,
+    hipLaunchKernelGGL((relevance_stream_kernel<In, 64, kStreamR64, kStreamWaves, SPLIT, TAIL>), grid,
                        dim3(64 * kStreamWaves), 0, s, a);
   else
-    hipLaunchKernelGGL((relevance_stream_kernel<In, 128, kStreamR128, NW128, SPLIT>), grid,
-                       dim3(64 * NW128), 0, s, a);
+    hipLaunchKernelGGL((relevance_stream_kernel<In, 128, kStreamR128, NW128, SPLIT, TAIL>), grid, dim3(64 * NW128),
+                       0, s, a);
+}
+
+template <class In, bool SPLIT>
+static void launch_rel_split_t(const RelArgs& a, const RelPlan& p, hipStream_t s) {
+  if (p.tail)
+    launch_rel_stream_t<In, SPLIT, true>(a, p, s);
+  else
+    launch_rel_stream_t<In, SPLIT, false>(a, p, s);
 }
 
 hipError_t launch_relevance(const RelArgs& a, const RelPlan& p, int dtype, hipStream_t s) {
-  if (!p.stream) {
-    if (dtype == 1)
-      launch_rel_t<BF16>(a, p.MT, s);
-    else
-      launch_rel_t<F32>(a, p.MT, s);
-    return hipGetLastError();
-  }
   if (p.n_split > 1) {
     if (dtype == 1)
-      launch_rel_stream_t<BF16, true>(a, p, s);
+      launch_rel_split_t<BF16, true>(a, p, s);
     else
-      launch_rel_stream_t<F32, true>(a, p, s);
+      launch_rel_split_t<F32, true>(a, p, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 grid((a.N + kMergeTokens - 1) / kMergeTokens, a.B);
     hipLaunchKernelGGL(relevance_merge_kernel, grid, dim3(kMergeTokens * kMergeGroups), 0, s, a);
   } else if (dtype == 1) {
-    launch_rel_stream_t<BF16, false>(a, p, s);
+    launch_rel_split_t<BF16, false>(a, p, s);
   } else {
-    launch_rel_stream_t<F32, false>(a, p, s);
+    launch_rel_split_t<F32, false>(a, p, s);
   }
   return hipGetLastError();
 }
