@@ -4,6 +4,7 @@
 // relevance within the top-K saliency set.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "select.hpp"
 
 namespace trevs {
 
@@ -344,6 +345,212 @@ __global__ __launch_bounds__(64) void spearman_final_kernel(SpearmanArgs a) {
                                         : (double)s_vt / sqrt((double)s_vv * (double)s_tt);
 }
 
+// ---------------------------------------------------------------------------
+// The same for sets of kBinRanksMin to kBinRanks tokens, in one launch with the
+// selection of the set: one workgroup per sample, entries 4 t .. 4 t + 3 with
+// thread t.  A token's ranks follow from the number of values below it and
+// equal to it, which need only be counted among its neighbours: the values are
+// spread over as many bins as there are values, between the smallest and the
+// largest; the bins that hold more than kBinScan are spread again over as many
+// bins as they hold, and so on (three times at most); then a token compares
+// itself with the values of its bin, unless they are all equal.  Counting all
+// pairs instead costs 8 K^2 lane operations: the top 4096 of 16,384 tokens,
+// 4 samples, took 42 us in three launches (selection 12, pairs 25, final 4.5)
+// and take 34 here; a bitonic sort and binary searches in one workgroup took 70.
+// Larger sets, which do not fit a workgroup's registers, keep the pairs, and so do
+// those below kBinRanksMin, whose pairs are few (a call with both questions of
+// the text sensitivity: top 3888 77.8 -> 72.8 us, top 2326 75.2 -> 74.1, top 1586
+// 80.8 -> 82.6, top 607 46.0 -> 52.4).
+// ---------------------------------------------------------------------------
+constexpr int kBinRanks = 4096, kBinRanksMin = 2048;
+constexpr int kRankPerThread = kBinRanks / kSelThreads;
+constexpr int kBinScan = 16, kBinLevels = 4;
+static_assert(kRankPerThread == 4, "four entries per thread");
+
+// Value not counted by any other: past the set, and not-a-number.
+constexpr uint32_t kNoRank = 0xffffffffu;
+
+struct RankShared {
+  uint32_t cnt[kBinRanks], mn[kBinRanks], mx[kBinRanks], val[kBinRanks];
+  uint32_t red_mn[kSelWaves], red_mx[kSelWaves];
+};
+
+// below[e], equal[e]: how many of the workgroup's keys lie below key[e] and how
+// many equal it (itself included); 0 for kNoRank, which no key counts.
+__device__ void block_ranks(const uint32_t (&key)[4], int (&below)[4], int (&equal)[4], RankShared& rs,
+                            SelectShared& sh) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  uint32_t lo = 0xffffffffu, hi = 0u;
+  int n_mine = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (key[e] != kNoRank) {
+      lo = min(lo, key[e]);
+      hi = max(hi, key[e]);
+      ++n_mine;
+    }
+  int n_all;
+  (void)block_excl_scan(n_mine, sh, n_all);
+  lo = wave_min_u32(lo);
+  hi = wave_max_u32(hi);
+  if (lane == 0) {
+    rs.red_mn[wave] = lo;
+    rs.red_mx[wave] = hi;
+  }
+  __syncthreads();
+  lo = wave_min_u32(lane < kSelWaves ? rs.red_mn[lane] : 0xffffffffu);
+  hi = wave_max_u32(lane < kSelWaves ? rs.red_mx[lane] : 0u);
+  // entry e lies in the bin of n[e] values that starts at place s[e]
+  int s[4], n[4];
+  uint32_t mn[4], mx[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    s[e] = 0;
+    n[e] = key[e] != kNoRank ? n_all : 0;
+    mn[e] = lo;
+    mx[e] = hi;
+  }
+  for (int level = 0;; ++level) {
+    int at[4];
+    *reinterpret_cast<u32x4*>(&rs.cnt[4 * tid]) = zero4();
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      at[e] = s[e];
+      if (n[e] > kBinScan && mn[e] != mx[e])  // the same steps for every key of the bin: order is kept
+        at[e] += min((int)((float)(key[e] - mn[e]) * ((float)(n[e] - 1) / (float)(mx[e] - mn[e]))), n[e] - 1);
+      if (n[e]) atomicAdd(&rs.cnt[at[e]], 1u);
+    }
+    __syncthreads();
+    const u32x4 c = *reinterpret_cast<const u32x4*>(&rs.cnt[4 * tid]);
+    int tot;
+    uint32_t run = (uint32_t)block_excl_scan((int)(c[0] + c[1] + c[2] + c[3]), sh, tot);
+    u32x4 st;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      st[j] = run;
+      run += c[j];
+    }
+    *reinterpret_cast<u32x4*>(&rs.val[4 * tid]) = st;  // (the starts, until the values take their place)
+    *reinterpret_cast<u32x4*>(&rs.mn[4 * tid]) = u32x4{~0u, ~0u, ~0u, ~0u};
+    *reinterpret_cast<u32x4*>(&rs.mx[4 * tid]) = zero4();
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n[e]) {
+        s[e] = (int)rs.val[at[e]];
+        n[e] = (int)rs.cnt[at[e]];
+        if (n[e] > kBinScan) {
+          atomicMin(&rs.mn[s[e]], key[e]);
+          atomicMax(&rs.mx[s[e]], key[e]);
+        }
+      }
+    __syncthreads();
+    bool more = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n[e] > kBinScan) {
+        mn[e] = rs.mn[s[e]];
+        mx[e] = rs.mx[s[e]];
+        more |= mn[e] != mx[e];
+      }
+    if (!__syncthreads_or(more) || level + 1 == kBinLevels) break;  // uniform
+  }
+  // the values, bin by bin (cnt counts them in again)
+  *reinterpret_cast<u32x4*>(&rs.cnt[4 * tid]) = zero4();
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (n[e]) rs.val[s[e] + (int)atomicAdd(&rs.cnt[s[e]], 1u)] = key[e];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    below[e] = s[e];
+    equal[e] = n[e];
+    if (n[e] <= kBinScan || mn[e] != mx[e]) {
+      equal[e] = 0;
+      for (int j = 0; j < n[e]; ++j) {
+        const uint32_t v = rs.val[s[e] + j];
+        below[e] += v < key[e] ? 1 : 0;
+        equal[e] += v == key[e] ? 1 : 0;
+      }
+    }
+  }
+  __syncthreads();  // rs is used again
+}
+
+template <int E>
+__global__ __launch_bounds__(kSelThreads) void topk_spearman_kernel(const float* sv_all, const float* st_all, int N,
+                                                                    int K, int32_t* idx_all, double* rho) {
+  __shared__ SelectShared sh;
+  __shared__ __attribute__((aligned(16))) RankShared rs;
+  __shared__ long long red[3][kSelWaves];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const float* sv = sv_all + (size_t)b * N;
+  const float* st = st_all + (size_t)b * N;
+  int32_t* idx = idx_all + (size_t)b * K;
+  {
+    float sc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) sc[e] = sv[min(e * kSelThreads + tid, N - 1)];  // unconditional loads
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (e * kSelThreads + tid >= N) sc[e] = 0.f;
+    block_topk_write<E>(sc, N, K, idx, sh);
+  }
+  __syncthreads();  // the set is written
+  int ii[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) ii[e] = min(max(idx[min(tid * 4 + e, K - 1)], 0), N - 1);
+  float x[2][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    x[0][e] = sv[ii[e]];
+    x[1][e] = st[ii[e]];
+  }
+  // twice the centred rank: 2 #below + #equal + 1 - (K + 1)
+  int c[2][4];
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    uint32_t key[4];
+    int below[4], equal[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[e] = tid * 4 + e < K && x[v][e] == x[v][e] ? f2key(x[v][e]) : kNoRank;
+    block_ranks(key, below, equal, rs, sh);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c[v][e] = 2 * below[e] + equal[e] - K;
+  }
+  long long s_vt = 0, s_vv = 0, s_tt = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (tid * 4 + e < K) {
+      s_vt += (long long)c[0][e] * c[1][e];
+      s_vv += (long long)c[0][e] * c[0][e];
+      s_tt += (long long)c[1][e] * c[1][e];
+    }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    s_vt += __shfl_xor(s_vt, o, 64);
+    s_vv += __shfl_xor(s_vv, o, 64);
+    s_tt += __shfl_xor(s_tt, o, 64);
+  }
+  if (lane == 0) {
+    red[0][wave] = s_vt;
+    red[1][wave] = s_vv;
+    red[2][wave] = s_tt;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    s_vt = s_vv = s_tt = 0;
+    for (int w = 0; w < kSelWaves; ++w) {
+      s_vt += red[0][w];
+      s_vv += red[1][w];
+      s_tt += red[2][w];
+    }
+    rho[b] = (s_vv == 0 || s_tt == 0) ? __builtin_nan("") : (double)s_vt / sqrt((double)s_vv * (double)s_tt);
+  }
+}
+
 // ---------------------------------------------------------------- launchers
 static int profile_waves(int T_max) {
   const int qb = (T_max + 31) / 32;
@@ -383,9 +590,27 @@ hipError_t launch_sensitivity(const SensitivityArgs& a, int B, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_spearman(const SpearmanArgs& a, int B, hipStream_t s) {
+static hipError_t launch_spearman(const SpearmanArgs& a, int B, hipStream_t s) {
   hipLaunchKernelGGL(spearman_rank_kernel, dim3(a.n_tiles, B), dim3(kRankThreads), 0, s, a);
   hipLaunchKernelGGL(spearman_final_kernel, dim3(B), dim3(64), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_topk_spearman(const SpearmanArgs& a, int B, int32_t* idx, hipStream_t s) {
+  if (a.K > kBinRanks || a.K < kBinRanksMin) {
+    const hipError_t e = launch_topk(a.sv, B, a.N, a.K, idx, s);
+    return e == hipSuccess ? launch_spearman(a, B, s) : e;
+  }
+#define CALL(E_)                                                                                               \
+  case E_:                                                                                                     \
+    hipLaunchKernelGGL(topk_spearman_kernel<E_>, dim3(B), dim3(kSelThreads), 0, s, a.sv, a.st, a.N, a.K, idx, \
+                       a.rho);                                                                                 \
+    break
+  switch (select_e(a.N)) {
+    CALL(1); CALL(2); CALL(4); CALL(8); CALL(16); CALL(32); CALL(64);
+    default: return hipErrorInvalidValue;
+  }
+#undef CALL
   return hipGetLastError();
 }
 

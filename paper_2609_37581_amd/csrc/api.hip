@@ -806,7 +806,6 @@ trevs_status trevs_topk_spearman(const float* sv, const float* st, int32_t B, in
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   uint8_t* w = reinterpret_cast<uint8_t*>(ws);
   int32_t* idx = kept_idx ? kept_idx : reinterpret_cast<int32_t*>(w);
-  TREVS_HIP(launch_topk(sv, B, N, K, idx, s));
   SpearmanArgs pa;
   pa.sv = sv;
   pa.st = st;
@@ -816,7 +815,7 @@ trevs_status trevs_topk_spearman(const float* sv, const float* st, int32_t B, in
   pa.n_tiles = (int)spearman_tiles(K);
   pa.part = reinterpret_cast<long long*>(w + spearman_ws_part(B, K));
   pa.rho = rho;
-  TREVS_HIP(launch_spearman(pa, B, s));
+  TREVS_HIP(launch_topk_spearman(pa, B, idx, s));
   return TREVS_OK;
 }
 

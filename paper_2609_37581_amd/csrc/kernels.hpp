@@ -233,7 +233,8 @@ constexpr int kRankTile = 64;  // tokens ranked per workgroup (one per lane)
 // head between two questions, and the rank correlation within a top-K set.
 hipError_t launch_profile(const ProfileArgs& a, int dtype, int dh, hipStream_t s);
 hipError_t launch_sensitivity(const SensitivityArgs& a, int B, hipStream_t s);
-hipError_t launch_spearman(const SpearmanArgs& a, int B, hipStream_t s);
+// The top-K set (to idx, which a.idx also names) and its rank correlation.
+hipError_t launch_topk_spearman(const SpearmanArgs& a, int B, int32_t* idx, hipStream_t s);
 
 // ---------------------------------------------------------------- gather
 constexpr int kGatherMaxTensors = 4;

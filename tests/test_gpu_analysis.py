@@ -161,6 +161,25 @@ def test_spearman_random_with_ties(N, K):
         assert np.isnan(rho).all()
 
 
+@pytest.mark.parametrize("N,K", [(4096, 2047), (2048, 2048), (5000, 2049), (9000, 4095), (4097, 4096), (8000, 4097)])
+def test_spearman_skewed_values(N, K):
+    """Sets around the sizes that are ranked by bins, with values that fall into
+    few bins: clusters a few ulp wide, large exact ties, many magnitudes,
+    negative values and infinities."""
+    print(f"[spearman-skew] N={N} K={K}", flush=True)
+    rng = np.random.default_rng(N + K)
+    sv = rng.random((4, N)).astype(np.float32)
+    st = sv.copy()
+    sv[0] = 1.0 + np.float32(2.0 ** -23) * rng.integers(0, 40, N)          # a cluster of ulps
+    st[0] = np.exp2(rng.uniform(-120, 120, N)) * rng.choice([-1.0, 1.0], N)  # every magnitude, both signs
+    sv[1, : N // 2] = 0.0
+    st[1] = np.where(rng.random(N) < 0.9, 0.25, st[1])                    # one large tie
+    st[2] = np.float32(0.5) + np.float32(2.0 ** -24) * rng.integers(0, 3, N)
+    st[2, :3] = np.inf, -np.inf, 1e30
+    st[3] = np.where(rng.random(N) < 0.5, 1e-30, 1e30) * (1 + np.float32(2.0 ** -20) * rng.integers(0, 9, N))
+    check_spearman(sv, st.astype(np.float32), K)
+
+
 def test_spearman_monotone_and_constant_cases():
     N = 300
     x = np.random.default_rng(5).random(N).astype(np.float32)

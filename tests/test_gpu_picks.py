@@ -1,0 +1,93 @@
+"""Diversity set by pools (Sec. 4.1) on the GPU where the pool's rounds end
+early: every pick against float64 distances to the GPU's own selected set."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_37581_amd import trevs
+from parity import assert_scores_close, check_fps_picks
+
+pytestmark = pytest.mark.gpu
+
+
+def clustered(rng, N, d, clusters, dup, zeros):
+    """Rows of N tokens: `clusters` tight clusters (size, spread), `dup` copies of
+    one row, `zeros` zero rows, the rest independent; and which are independent."""
+    Z = rng.standard_normal((N, d))
+    order = rng.permutation(N)
+    at = 0
+    for size, spread in clusters:
+        Z[order[at:at + size]] = rng.standard_normal(d) + spread * rng.standard_normal((size, d))
+        at += size
+    Z[order[at:at + dup]] = rng.standard_normal(d)
+    at += dup
+    Z[order[at:at + zeros]] = 0.0
+    at += zeros
+    return Z, np.sort(order[at:])
+
+
+# (N, d, K, K_d, dtype, per sample: clusters, copies, zero rows).  Pools hold at
+# most 4096 tokens, so a cluster of 5000 far tokens fills one and ends its round
+# after the first pick; three of them leave picks for the full Gram matrix.
+CASES = {
+    "second-round-bf16": (8192, 256, 768, 192, "bf16", [([(5000, 0.05)], 0, 0), ([], 0, 0)]),
+    "unfinished-bf16": (20000, 64, 1024, 256, "bf16", [([(5000, 0.02)] * 3, 0, 0), ([(300, 0.02)] * 9, 0, 0)]),
+    "unfinished-odd-f32": (16387, 20, 600, 150, "f32", [([(4500, 0.02)] * 3, 0, 0)]),
+    "copies-and-zeros-bf16": (6000, 128, 640, 160, "bf16", [([], 2500, 0), ([], 300, 900)]),
+    "pool-of-all-bf16": (2304, 1024, 1152, 288, "bf16", [([(500, 0.1)], 100, 3)] * 2),
+    "pool-tail-f32": (3000, 1028, 700, 175, "f32", [([(200, 0.1)] * 4, 50, 1)]),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_picks_of_clustered_tokens(name):
+    N, d, K, k_div, dtype, samples = CASES[name]
+    rng = np.random.default_rng(sum(map(ord, name)))
+    B, H, M = len(samples), 4, 8
+    print(f"[picks] {name}: B={B} N={N} d={d} K={K} K_d={k_div}", flush=True)
+    Z = np.empty((B, N, d), dtype=np.float32)
+    cls = rng.standard_normal((B, H, N)).astype(np.float32)
+    for b, (clusters, dup, zeros) in enumerate(samples):
+        Z[b], free = clustered(rng, N, d, clusters, dup, zeros)
+        cls[b][:, rng.choice(free, K - k_div, replace=False)] += 8.0  # the pivots: no cluster holds one
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Zt = torch.from_numpy(Z).to(dt)
+    T = torch.from_numpy(rng.standard_normal((B, M, d)).astype(np.float32)).to(dt).cuda()
+    call = trevs.Prellm(torch.from_numpy(cls).to(dt).cuda(), Zt.cuda(), T, k_keep=K, k_div=k_div,
+                        textual_ratio=0.0, want_scores=True)
+    call()
+    torch.cuda.synchronize()
+    kept, picks = call.kept_idx.cpu().numpy(), call.div_idx.cpu().numpy()
+    score = call.score.cpu().numpy()
+    assert torch.equal(call.kept_feats.cpu(), torch.stack([Zt[b][torch.from_numpy(kept[b]).long()] for b in range(B)]))
+    for b in range(B):
+        pivots = np.setdiff1d(kept[b], picks[b])
+        assert pivots.size == K - k_div and np.unique(picks[b]).size == k_div, b
+        assert np.array_equal(pivots, oracle.topk_ascending(score[b].astype(np.float64), K - k_div)), b
+        assert np.array_equal(kept[b], np.sort(np.concatenate([pivots, picks[b]]))), b
+        check_fps_picks(Zt[b].double().numpy(), pivots, picks[b])
+    again = call.div_idx.clone()
+    call()
+    assert torch.equal(again, call.div_idx)
+
+
+@pytest.mark.parametrize("d,dtype", [(1032, "bf16"), (1024, "bf16"), (1028, "f32")])
+def test_relevance_text_lengths_at_block_edges(d, dtype):
+    """Question lengths around the 32-row text blocks (the blocks past the last
+    row are skipped), one and two text chunks, whole and partial last slabs."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for M in (32, 64, 128, 160):
+        rng = np.random.default_rng(M + d)
+        Zt = torch.from_numpy(rng.standard_normal((6, 200, d)).astype(np.float32)).to(dt)
+        T = torch.from_numpy(rng.standard_normal((6, M, d)).astype(np.float32)).to(dt)
+        cls = torch.from_numpy(rng.standard_normal((6, 4, 200)).astype(np.float32)).to(dt)
+        lens = np.array([1, M // 2 - 1, M // 2, M // 2 + 1, M - 1, M], dtype=np.int32)
+        call = trevs.Prellm(cls.cuda(), Zt.cuda(), T.cuda(), torch.from_numpy(lens).cuda(), k_keep=20,
+                            want_scores=True)
+        call()
+        z = torch.nn.functional.normalize(Zt.double(), dim=2)
+        t = torch.nn.functional.normalize(T.double(), dim=2)
+        c = (z @ t.transpose(1, 2)).clamp_min(0.0).square()
+        want = torch.stack([c[b, :, :int(lens[b])].mean(1).sqrt() for b in range(6)])
+        assert_scores_close(call.rel.cpu().numpy(), want.numpy(), f"s^t M={M}")
