@@ -125,7 +125,7 @@ PrellmLayout prellm_layout(const trevs_prellm_args* a) {
   off = align_up(off + (size_t)a->B * a->N * sizeof(float));
   L.stats = off;
   off = align_up(off + (size_t)a->B * 4 * sizeof(float));
-  L.rel_plan = relevance_plan(a->B, a->N, a->M_max, a->d * elem_bytes(a->dtype));
+  L.rel_plan = relevance_plan(a->B, a->N, a->M_max, a->d * elem_bytes(a->dtype), a->H_v, a->n_seg);
   L.rel_part = off;  // partial products of a feature-dimension split
   off = align_up(off + L.rel_plan.part_floats() * sizeof(float));
   L.inv_norm = L.pivots = L.ctrl = L.picks = L.gram = L.pick_part = off;
@@ -448,7 +448,7 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
   pa.cls_vec16 = aligned(a->cls_logits, 16) && ((size_t)a->N * e) % 16 == 0 &&
                  ((size_t)(a->N / a->n_seg) * e) % 16 == 0;
   TREVS_TRY(record(a->events, 0, s));
-  TREVS_HIP(launch_prep(pa, a->dtype, s));
+  if (!L.rel_plan.fused_stats) TREVS_HIP(launch_prep(pa, a->dtype, s));
   TREVS_TRY(record(a->events, 1, s));
 
   RelArgs ra;
@@ -461,6 +461,8 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
   ra.T = a->text_emb;
   ra.text_len = a->text_len;
   ra.inv_tnorm = inv_tnorm;
+  ra.cls_vec16 = pa.cls_vec16;
+  ra.fused_stats = L.rel_plan.fused_stats;
   ra.B = a->B;
   ra.N = a->N;
   ra.M_max = a->M_max;
@@ -473,6 +475,7 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
   ra.split_slabs = rp.split_slabs;
   ra.part = reinterpret_cast<float*>(w + L.rel_part);
   ra.zpart = ra.part + (size_t)rp.n_split * a->B * a->M_max * a->N;
+  ra.tpart = ra.zpart + (size_t)rp.n_split * a->B * a->N;
   ra.inv_norm = L.picks_plan.rounds > 0 ? reinterpret_cast<float*>(w + L.inv_norm) : nullptr;
   TREVS_TRY(record(a->events, 2, s));
   TREVS_HIP(launch_relevance(ra, rp, a->dtype, s));

@@ -27,16 +27,20 @@ struct RelArgs {
   const void* T;             // [B,M_max,d]
   const int32_t* text_len;
   const float* inv_tnorm;
+  int cls_vec16;             // every [CLS] segment row starts 16-byte aligned
+  bool fused_stats;          // no prep: the launch forms row statistics and text norms itself
   int B, N, M_max, row_bytes, tiles_per_sample;
   float* sal;                // [B,N]
   float* rel;                // [B,N]
   // feature-dimension split (n_split > 1): workgroup (tile, split) covers
   // the 128-byte slabs [split*split_slabs, ...) and writes its partial dot
-  // products t_j.z_i to part [B,n_split,M_max,N] and its partial ||z_i||^2
-  // to zpart [B,n_split,N]; a merge pass finishes Eq. (4)-(5)
+  // products t_j.z_i to part [B,n_split,M_max,N], its partial ||z_i||^2 to zpart
+  // [B,n_split,N] and (first tile) ||t_j||^2 to tpart [B,n_split,M_max]; a merge
+  // pass finishes Eq. (4)-(5)
   int n_split, split_slabs;
   float* part;
   float* zpart;
+  float* tpart;
   float* inv_norm;           // [B,N] 1 / max(||z_i||, 1e-12), or null
 };
 
@@ -47,7 +51,8 @@ struct RelPlan {
   int tile_tokens;       // visual tokens per workgroup
   int tiles_per_sample;
   int n_split, split_slabs;
-  size_t part_floats() const;  // floats of part + zpart (0 without a split)
+  bool fused_stats;
+  size_t part_floats() const;  // floats of part + zpart + tpart (0 without a split)
   int B, N, M_max;
 };
 
@@ -267,7 +272,7 @@ inline int select_e(int N) {
 }
 
 hipError_t launch_prep(const PrepArgs& a, int dtype, hipStream_t s);
-RelPlan relevance_plan(int B, int N, int M_max, int row_bytes);
+RelPlan relevance_plan(int B, int N, int M_max, int row_bytes, int H, int n_seg);
 hipError_t launch_relevance(const RelArgs& a, const RelPlan& p, int dtype, hipStream_t s);
 hipError_t launch_norm_stats(const NormArgs& a, int B, hipStream_t s);
 hipError_t launch_prellm_select(const SelArgs& a, int B, hipStream_t s);

@@ -12,7 +12,8 @@ namespace trevs {
 // Prep.  Blocks [0, n_cls_blocks) take one ([CLS] head, segment) row each and
 // reduce it in one pass to its softmax statistics (max and sum of exp, log2
 // units, Eq. (2)); every later block takes 8 text rows, one per wave, and
-// stores the inverse L2 norm of each (Sec. 4.1, before Eq. (4)).
+// stores the inverse L2 norm of each (Sec. 4.1, before Eq. (4)).  Small grids do
+// both inside the relevance launch (RelPlan::fused_stats).
 // ---------------------------------------------------------------------------
 constexpr int kPrepThreads = 512;
 
@@ -119,31 +120,105 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(PrepArgs a) {
   if (lane == 0) a.inv_tnorm[r] = inv;
 }
 
+// Softmax statistics of the [CLS] rows that the tokens [tok0, tok0 + VT) of
+// sample b belong to: heads 0..H-1 of segments seg0..seg0+ns-1 (row h * ns + s
+// to st), as prep_kernel computes them.  A wave takes four rows at a time, two
+// 16-byte vectors (or eight values) of each in flight.
+constexpr int kStatRows = 128;      // rows per workgroup, at most
+constexpr int kStatValues = 65536;  // and values: about 5 us of a workgroup
+// (two rows with 16 waves, whose registers are few)
+template <class In, int NW>
+__device__ __forceinline__ void tile_stats(const RelArgs& a, int b, int seg0, int ns, float2* st) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rows = a.H * ns;
+  constexpr int R = NW == 16 ? 2 : 4;
+  for (int r0 = wave * R; r0 < rows; r0 += NW * R) {
+    const uint8_t* p[R];
+    float m[R], s[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int row = min(r0 + r, rows - 1), h = row / ns, seg = seg0 + row - h * ns;
+      p[r] = reinterpret_cast<const uint8_t*>(a.cls) +
+             (((size_t)b * a.H + h) * a.N + (size_t)seg * a.seg_len) * In::kBytes;
+      m[r] = -INFINITY;
+      s[r] = 0.f;
+    }
+    if (a.cls_vec16) {
+      constexpr int U = 2;
+      const int nvec = a.seg_len * In::kBytes / 16;
+      for (int v = lane; v < nvec; v += U * 64) {
+        u32x4 w[R][U];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int u = 0; u < U; ++u) w[r][u] = ldg16(p[r] + (size_t)min(v + u * 64, nvec - 1) * 16);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (v + u * 64 < nvec) online_vec<In>(m[r], s[r], w[r][u]);
+      }
+    } else {
+      constexpr int U = NW == 16 ? 4 : 8;
+      for (int i = lane; i < a.seg_len; i += U * 64) {
+        float x[R][U];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int u = 0; u < U; ++u) x[r][u] = load_scalar(p[r], min(i + u * 64, a.seg_len - 1), In{}) * kLog2e;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          float vm = m[r];
+#pragma unroll
+          for (int u = 0; u < U; ++u) vm = i + u * 64 < a.seg_len ? fmaxf(vm, x[r][u]) : vm;
+          float acc = s[r] * __builtin_amdgcn_exp2f(m[r] - vm);
+#pragma unroll
+          for (int u = 0; u < U; ++u) acc += i + u * 64 < a.seg_len ? __builtin_amdgcn_exp2f(x[r][u] - vm) : 0.f;
+          s[r] = acc;
+          m[r] = vm;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float mm = wave_max(m[r]);
+      const float ss = wave_sum(m[r] > -INFINITY ? s[r] * __builtin_amdgcn_exp2f(m[r] - mm) : 0.f);
+      if (lane == 0 && r0 + r < rows) st[r0 + r] = make_float2(mm, 1.f / ss);
+    }
+  }
+}
+
 // Saliency (Eq. (2)-(3)) of the tokens [tok0, tok0 + VT) of sample b: the
 // head mean of each [CLS] logit's softmax within its segment, from the
-// per-(head, segment) max and 1/sum written by prep_kernel.  The head loop
-// is unrolled by 8 with all loads of a group issued before the first use,
-// so a tile pays about H/8 memory round trips instead of H.
-template <class In>
-__device__ __forceinline__ void tile_saliency(const RelArgs& a, int b, int tok0, int VT, int NT, int tid) {
+// per-(head, segment) max and 1/sum (st: of tile_stats, else of prep_kernel).
+// The head loop is unrolled by 8 with all loads of a group issued before the
+// first use, so a tile pays about H/8 memory round trips instead of H.
+// (the whole workgroup calls it)
+template <class In, int NW, bool STATS>
+__device__ __forceinline__ void tile_saliency(const RelArgs& a, int b, int tok0, int VT, int tid, float2* st) {
+  constexpr int NT = 64 * NW;
   const int N = a.N, H = a.H;
+  const int seg0 = tok0 / a.seg_len, ns = min(tok0 + VT - 1, N - 1) / a.seg_len - seg0 + 1;
+  if (STATS) {
+    tile_stats<In, NW>(a, b, seg0, ns, st);
+    __syncthreads();
+  }
   for (int t = tid; t < VT; t += NT) {
     const int i = tok0 + t;
     if (i < N) {
       const int seg = i / a.seg_len;
       float acc = 0.f;
       for (int h0 = 0; h0 < H; h0 += 8) {
-        float2 st[8];
+        float2 rs[8];
         float x[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int h = min(h0 + u, H - 1);
-          st[u] = a.row_stats[((size_t)b * H + h) * a.n_seg + seg];
+          rs[u] = STATS ? st[h * ns + seg - seg0] : a.row_stats[((size_t)b * H + h) * a.n_seg + seg];
           x[u] = load_scalar(a.cls, ((size_t)b * H + h) * N + i, In{});
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          if (h0 + u < H) acc = fmaf(__builtin_amdgcn_exp2f(fmaf(x[u], kLog2e, -st[u].x)), st[u].y, acc);
+          if (h0 + u < H) acc = fmaf(__builtin_amdgcn_exp2f(fmaf(x[u], kLog2e, -rs[u].x)), rs[u].y, acc);
       }
       a.sal[(size_t)b * N + i] = acc / (float)H;
     }
@@ -170,7 +245,9 @@ __device__ __forceinline__ void tile_saliency(const RelArgs& a, int b, int tok0,
 // kernel of their own with operands straight from memory: 8,208-byte rows, 74 text
 // rows, 2 x 3221 tokens 169 us a call there, 70 us here; 115 text rows, 6 x 9397
 // tokens 384 and 199 us.)  With SPLIT the workgroup covers one range of slabs and
-// writes raw partial products and ||z||^2 for relevance_merge_kernel.
+// writes raw partial products and ||z||^2 for relevance_merge_kernel (SPLIT 1),
+// and the text rows' squares too, beside workgroups that do the saliency
+// (SPLIT 2, see RelPlan::fused_stats).
 // ---------------------------------------------------------------------------
 constexpr int kStreamWaves = 8;
 constexpr int kStreamTokens = 32 * kStreamWaves;
@@ -215,8 +292,9 @@ struct StreamTiling {
 };
 
 // (two waves per SIMD at four waves a workgroup: two workgroups per CU)
-template <class In, int MT, int R, int NW, bool SPLIT, bool TAIL, int VB = 8>
+template <class In, int MT, int R, int NW, int SPLIT, bool TAIL, int VB = 8>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_kernel(RelArgs a) {
+  constexpr bool FUSED = SPLIT == 2;  // no prep before this launch
   constexpr int NT = 64 * NW;
   constexpr int VT = 32 * VB;
   constexpr int TG = StreamTiling<MT, NW, VB>::TG;
@@ -232,13 +310,20 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
   static_assert(ZPT * NT * 16 == ZBYTES && (NT / 8) % 16 == 0, "stage split");
   __shared__ __attribute__((aligned(1024))) uint8_t l0[STAGE], l1[STAGE];
   __shared__ float tn[MT];
+  __shared__ float2 cls_stats[FUSED ? kStatRows : 1];
   __shared__ float rpart[TG][VT];  // per-text-group row sums of Eq. (5)
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   // the splits of one token tile are consecutive workgroups (one XCD, so
   // they share the text slabs in its L2)
-  const int wid = xcd_remap(blockIdx.x, gridDim.x);
+  const int n_main = a.B * a.tiles_per_sample * (SPLIT ? a.n_split : 1);
+  if (FUSED && (int)blockIdx.x >= n_main) {  // the saliency of a tile
+    const int t = blockIdx.x - n_main, sb = t / a.tiles_per_sample;
+    tile_saliency<In, NW, FUSED>(a, sb, (t - sb * a.tiles_per_sample) * VT, VT, tid, cls_stats);
+    return;
+  }
+  const int wid = xcd_remap(blockIdx.x, n_main);
   const int tile = SPLIT ? wid / a.n_split : wid;
   const int split = SPLIT ? wid - tile * a.n_split : 0;
   const int b = tile / a.tiles_per_sample;
@@ -250,8 +335,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
   const int n_slabs = SPLIT ? min(row_slabs, s_begin + a.split_slabs) - s_begin : row_slabs;
   const int n_iter = (n_slabs + U - 1) / U;  // stages padded to the unroll
 
-  const float* itn = a.inv_tnorm + (size_t)b * a.M_max;
   auto stage_norms = [&](int j0) {  // inverse text norms of a chunk, zero past the text
+    const float* itn = a.inv_tnorm + (size_t)b * a.M_max;
     if (tid < MT) tn[tid] = j0 + tid < Mb ? itn[j0 + tid] : 0.f;
   };
 
@@ -360,9 +445,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
 #pragma unroll
     for (int c = 0; c < R; ++c) load(c, g[c]);
     if (first) {
-      if (split == 0) tile_saliency<In>(a, b, tok0, VT, NT, tid);
+      if (!FUSED && split == 0) tile_saliency<In, NW, false>(a, b, tok0, VT, tid, nullptr);
       if (!SPLIT) stage_norms(0);
     }
+    float tsq[TPT];  // FUSED: sums of squares of this thread's text chunks
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) tsq[k] = 0.f;
     for (int it = 0; it < n_iter; ++it) {
 #pragma unroll
       for (int c = 0; c < U; ++c) {
@@ -370,10 +458,27 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void relevance_stream_ker
         uint8_t* st = c % 2 ? l1 : l0;
         // buffer (s % 2) was last read at step s - 2, before every wave
         // passed the barrier of step s - 1
+        if (FUSED && s < n_slabs) {
+#pragma unroll
+          for (int k = 0; k < TPT; ++k)
+            if (!TAIL || !past_end(s)) tsq[k] += sumsq(g[c % R][ZPT + k], In{});
+        }
         store(st, g[c % R], s);
         load(s + R, g[c % R]);
         __syncthreads();
         if (s < n_slabs) compute(st);
+      }
+    }
+    if constexpr (FUSED) {  // ||t_j||^2 over this split: the eight threads of a row add their chunks
+#pragma unroll
+      for (int k = 0; k < TPT; ++k) {
+        float v = tsq[k];
+        v += __shfl_xor(v, 1, 64);
+        v += __shfl_xor(v, 2, 64);
+        v += __shfl_xor(v, 4, 64);
+        const int row = cr + (NT / 8) * k;
+        if (cc == 0 && row < MT && tok0 == 0 && j0 + row < Mb)
+          a.tpart[((size_t)b * a.n_split + split) * a.M_max + j0 + row] = v;
       }
     }
     __syncthreads();  // the LDS buffers are refilled by the next text chunk
@@ -459,10 +564,13 @@ __global__ __launch_bounds__(kMergeTokens * kMergeGroups, 8) void relevance_merg
   // address from scalar registers
   const size_t sstride = (size_t)a.M_max * N;
   const float* pb = a.part + (size_t)b * S * sstride;
-  const float* itn = a.inv_tnorm + (size_t)b * a.M_max;
+  const float* tp = a.tpart + (size_t)b * S * a.M_max;
   float r = 0.f;
   for (int j = g; j < Mb; j += kMergeGroups) {
     const int off = j * N + ic;
+    float tt = 0.f;  // ||t_j||^2 where prep did not form the norms: the row's 32 threads add the splits
+    if (a.fused_stats)
+      for (int sp = t; sp < S; sp += kMergeTokens) tt += tp[(size_t)sp * a.M_max + j];
     float c = 0.f;
     for (int s0 = 0; s0 < S; s0 += 16) {  // 16 loads in flight, added in split order
       float v[16];
@@ -471,7 +579,15 @@ __global__ __launch_bounds__(kMergeTokens * kMergeGroups, 8) void relevance_merg
 #pragma unroll
       for (int k = 0; k < 16; ++k) c += s0 + k < S ? v[k] : 0.f;
     }
-    c = fmaxf(c * itn[j], 0.f);
+    float itn;
+    if (a.fused_stats) {
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) tt += __shfl_xor(tt, o, 32);
+      itn = 1.f / fmaxf(sqrtf(tt), 1e-12f);
+    } else {
+      itn = a.inv_tnorm[(size_t)b * a.M_max + j];
+    }
+    c = fmaxf(c * itn, 0.f);
     r = fmaf(c, c, r);
   }
   float z = 0.f;  // ||z_i||^2: split sp goes to row group sp % 32
@@ -678,10 +794,10 @@ constexpr size_t kSplitMaxBytes = size_t(256) << 20;  // cap on the partial prod
 constexpr int kStreamR32 = TREVS_STREAM_R32;
 
 size_t RelPlan::part_floats() const {
-  return n_split > 1 ? (size_t)n_split * B * ((size_t)M_max + 1) * N : 0;
+  return n_split > 1 ? (size_t)n_split * B * (((size_t)M_max + 1) * N + M_max) : 0;
 }
 
-RelPlan relevance_plan(int B, int N, int M_max, int row_bytes) {
+RelPlan relevance_plan(int B, int N, int M_max, int row_bytes, int H, int n_seg) {
   RelPlan p;
   p.B = B;
   p.N = N;
@@ -718,17 +834,26 @@ RelPlan relevance_plan(int B, int N, int M_max, int row_bytes) {
       }
     }
   }
+  // With a split, and room for one more workgroup per tile beside the others,
+  // that workgroup computes the tile's saliency, and reduces the [CLS] rows of
+  // the segments it touches itself if they are short: one launch less (3 to 5 us; 1 x 576 fp32
+  // tokens 38.1 -> 35.9 us a call, 3 x 1890 bf16 36.2 -> 32.7).  Without a split the
+  // tiles' own workgroups would have to, which gains nothing (64 x 576 tokens
+  // 116.0 us a call either way) or costs registers (4 x 16,384: 156 -> 169 us).
+  const int seg_len = N / n_seg;
+  const long ns = std::min<long>(n_seg, (p.tile_tokens - 1) / seg_len + 2);
+  p.fused_stats = p.n_split > 1 && tiles * (p.n_split + 1) <= resident && H * ns <= kStatRows && H * ns * seg_len <= kStatValues;
   return p;
 }
 
-template <class In, bool SPLIT, bool TAIL>
+template <class In, int SPLIT, bool TAIL>
 static void launch_rel_stream_t(const RelArgs& a, const RelPlan& p, hipStream_t s) {
-  const dim3 grid(a.B * a.tiles_per_sample * a.n_split);
+  const dim3 grid(a.B * a.tiles_per_sample * (SPLIT ? a.n_split + (SPLIT == 2 ? 1 : 0) : 1));
   constexpr int NW128 = TREVS_STREAM_NW128;
   const int MT = p.MT;
-  if constexpr (!SPLIT) {  // the split runs on 256-token tiles only
+  if constexpr (SPLIT == 0) {  // the split runs on 256-token tiles only
     if (MT == 64 && p.tile_tokens == kTile192) {
-      hipLaunchKernelGGL((relevance_stream_kernel<In, 64, 2, 12, false, TAIL, 6>), grid, dim3(64 * 12), 0, s, a);
+      hipLaunchKernelGGL((relevance_stream_kernel<In, 64, 2, 12, 0, TAIL, 6>), grid, dim3(64 * 12), 0, s, a);
       return;
     }
   }
@@ -742,7 +867,7 @@ static void launch_rel_stream_t(const RelArgs& a, const RelPlan& p, hipStream_t 
                        0, s, a);
 }
 
-template <class In, bool SPLIT>
+template <class In, int SPLIT>
 static void launch_rel_split_t(const RelArgs& a, const RelPlan& p, hipStream_t s) {
   if (p.tail)
     launch_rel_stream_t<In, SPLIT, true>(a, p, s);
@@ -750,21 +875,25 @@ static void launch_rel_split_t(const RelArgs& a, const RelPlan& p, hipStream_t s
     launch_rel_stream_t<In, SPLIT, false>(a, p, s);
 }
 
+template <class In>
+static void launch_rel_t(const RelArgs& a, const RelPlan& p, hipStream_t s) {
+  if (p.n_split == 1)
+    launch_rel_split_t<In, 0>(a, p, s);
+  else if (!p.fused_stats)
+    launch_rel_split_t<In, 1>(a, p, s);
+  else
+    launch_rel_split_t<In, 2>(a, p, s);
+}
+
 hipError_t launch_relevance(const RelArgs& a, const RelPlan& p, int dtype, hipStream_t s) {
-  if (p.n_split > 1) {
-    if (dtype == 1)
-      launch_rel_split_t<BF16, true>(a, p, s);
-    else
-      launch_rel_split_t<F32, true>(a, p, s);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const dim3 grid((a.N + kMergeTokens - 1) / kMergeTokens, a.B);
-    hipLaunchKernelGGL(relevance_merge_kernel, grid, dim3(kMergeTokens * kMergeGroups), 0, s, a);
-  } else if (dtype == 1) {
-    launch_rel_split_t<BF16, false>(a, p, s);
-  } else {
-    launch_rel_split_t<F32, false>(a, p, s);
-  }
+  if (dtype == 1)
+    launch_rel_t<BF16>(a, p, s);
+  else
+    launch_rel_t<F32>(a, p, s);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || p.n_split == 1) return e;
+  const dim3 grid((a.N + kMergeTokens - 1) / kMergeTokens, a.B);
+  hipLaunchKernelGGL(relevance_merge_kernel, grid, dim3(kMergeTokens * kMergeGroups), 0, s, a);
   return hipGetLastError();
 }
 
