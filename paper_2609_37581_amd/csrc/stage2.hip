@@ -377,7 +377,7 @@ __global__ __launch_bounds__(64 * QW * ScoreTile<DH * In::kBytes>::WPB) void t2v
   __shared__ __attribute__((aligned(16))) uint8_t qlds[2][QR * LROW];
   __shared__ __attribute__((aligned(16))) float llds[2][QR];
   __shared__ float pmax[QW][V];
-  __shared__ float u_lds[kMaxHeads];
+  __shared__ __attribute__((aligned(16))) float u_lds[kMaxHeads];
   __shared__ int sel_lds[kMaxHeads];
   __shared__ int heads[kMaxHeads];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -391,22 +391,27 @@ __global__ __launch_bounds__(64 * QW * ScoreTile<DH * In::kBytes>::WPB) void t2v
   const int h_lo = hs * a.hps, h_hi = min(nk, h_lo + a.hps);  // selected-head indices of this split
 
   // ---- high-variance head set H*: the rank of head h under (u desc, h asc)
-  // counts the heads before it, 64 comparisons per ballot (wave w ranks heads
-  // w, w + QW, ...); wave 0 then writes the selected heads in ascending order
-  for (int h = tid; h < Hq; h += NT) {
-    u_lds[h] = a.head_var[(size_t)b * Hq + h];
+  // counts the heads before it, a thread to a head (a wave to a head, ranked by
+  // ballots, takes as long with eight waves and 2.5 us longer with one); wave
+  // 0 then writes the selected heads in ascending order
+  const int Hq4 = (Hq + 3) & ~3;
+  for (int h = tid; h < Hq4; h += NT) {
+    u_lds[h] = h < Hq ? a.head_var[(size_t)b * Hq + h] : -INFINITY;
     heads[h] = 0;
   }
   __syncthreads();
-  for (int h = wv; h < Hq; h += QW * WPB) {
+  for (int h = tid; h < Hq; h += NT) {
     const float u = u_lds[h];
     int rank = 0;
-    for (int c0 = 0; c0 < Hq; c0 += 64) {
-      const int h2 = c0 + lane;
-      const float u2 = h2 < Hq ? u_lds[h2] : 0.f;
-      rank += (int)__popcll(__ballot(h2 < Hq && (u2 > u || (u2 == u && h2 < h))));
+#pragma unroll 4
+    for (int c = 0; c < Hq4; c += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(&u_lds[c]);
+      rank += v.x > u || (v.x == u && c < h) ? 1 : 0;
+      rank += v.y > u || (v.y == u && c + 1 < h) ? 1 : 0;
+      rank += v.z > u || (v.z == u && c + 2 < h) ? 1 : 0;
+      rank += v.w > u || (v.w == u && c + 3 < h) ? 1 : 0;
     }
-    if (lane == 0) sel_lds[h] = rank < nk;
+    sel_lds[h] = rank < nk;
   }
   __syncthreads();
   if (wv == 0) {
