@@ -225,21 +225,24 @@ trevs_status validate_inllm(const trevs_inllm_args* a) {
 
 // Split of the visual keys for the statistics pass: enough workgroups to fill
 // the GPU (>= 2 per CU), each split at least 64 keys, lengths multiples of 64
-// (the pass consumes key tiles in pairs of 32).
+// (two key tiles of 32).  fp32 tiles take 1.8 us of multiplies each, so splits
+// of one tile pay while they still leave CUs idle (1 x 192 keys, 32 heads: 32.1 ->
+// 30.0 us a call; with 252 workgroups already, 28 x 141 keys, 131 -> 140).
 struct StatsPlan {
   int n_split, split_len, n_rgroups;
   int rest_len;  // causal non-visual keys per split, multiple of 32 (0: visual-only softmax)
 };
-StatsPlan stats_plan(int B, int K_in, int T_max, int H_q, int H_kv, int softmax, int P) {
+StatsPlan stats_plan(int dtype, int B, int K_in, int T_max, int H_q, int H_kv, int softmax, int P) {
   StatsPlan p;
   const int G = H_q / H_kv;
   const int nrb = (G * T_max + 31) / 32;
   const int nw = stats_waves(G, T_max);
   p.n_rgroups = (nrb + nw - 1) / nw;
   const int64_t base_wgs = (int64_t)B * H_kv * p.n_rgroups;
-  int n_split = (int)std::min<int64_t>((512 + base_wgs - 1) / base_wgs, (K_in + 63) / 64);
+  const int unit = dtype == TREVS_F32 && base_wgs * ((K_in + 63) / 64) <= 128 ? 32 : 64;
+  int n_split = (int)std::min<int64_t>((512 + base_wgs - 1) / base_wgs, (K_in + unit - 1) / unit);
   n_split = std::max(n_split, 1);
-  p.split_len = ((K_in + n_split - 1) / n_split + 63) / 64 * 64;
+  p.split_len = ((K_in + n_split - 1) / n_split + unit - 1) / unit * unit;
   p.n_split = (K_in + p.split_len - 1) / p.split_len;
   // the causal non-visual keys (P prefix + T_max text) shared evenly by the splits
   p.rest_len = softmax == TREVS_SOFTMAX_CAUSAL ? ((P + T_max + p.n_split - 1) / p.n_split + 31) / 32 * 32 : 0;
@@ -250,7 +253,7 @@ size_t lse_rows_padded(int T_max) { return (size_t)(T_max + 31) / 32 * 32; }
 
 InllmPlan inllm_plan(const trevs_inllm_args* a) {
   InllmPlan p;
-  const StatsPlan sp = stats_plan(a->B, a->K_in, a->T_max, a->H_q, a->H_kv,
+  const StatsPlan sp = stats_plan(a->dtype, a->B, a->K_in, a->T_max, a->H_q, a->H_kv,
                                   a->row_stats ? TREVS_SOFTMAX_VISUAL : a->softmax, a->P);
   p.n_split = sp.n_split;
   p.split_len = sp.split_len;
@@ -327,7 +330,7 @@ struct SensitivityLayout {
 
 SensitivityLayout sensitivity_layout(const trevs_sensitivity_args* a) {
   SensitivityLayout L;
-  L.sp = stats_plan(a->B, a->K_in, a->T_max, a->H_q, a->H_kv, a->softmax, a->P);
+  L.sp = stats_plan(a->dtype, a->B, a->K_in, a->T_max, a->H_q, a->H_kv, a->softmax, a->P);
   const size_t heads = (size_t)a->B * a->H_q;
   size_t off = 0;
   for (int c = 0; c < 2; ++c) {

@@ -347,13 +347,16 @@ constexpr int kMaxHeads = 256;
 
 // Waves per 32-row text block: with 64-token tiles two waves split the keys
 // (32 each) and share the staged Q rows, two waves per SIMD (23 us against
-// 26 us with one wave per text block at the 16,384-token workload).
+// 26 us with one wave per text block at the 16,384-token workload).  Rows of 512
+// bytes (fp32, 128 per head) leave room for one workgroup a CU, whose two
+// waves at 32-token tiles used two of its four SIMDs: 12 x 1091 tokens, 121 text
+// rows, 385 -> 298 us a call.  1 KB rows do not fit twice.
 #ifndef TREVS_SCORE_WPB
 #define TREVS_SCORE_WPB 2
 #endif
 template <int ROWB>
 struct ScoreTile {
-  static constexpr int VB = ROWB <= 256 ? 2 : 1;  // 32-token blocks per workgroup
+  static constexpr int VB = ROWB <= 512 ? 2 : 1;  // 32-token blocks per workgroup
   static constexpr int V = 32 * VB;
   static constexpr int WPB = VB == 2 ? TREVS_SCORE_WPB : 1;  // waves per 32-row text block
 };
@@ -709,7 +712,7 @@ int score_qblocks(int T_max, int row_bytes) {
 
 int score_tile_tokens(int dtype, int dh) {
   const int rowb = dh * (dtype == 1 ? 2 : 4);
-  return rowb <= 256 ? 64 : 32;
+  return rowb <= 512 ? 64 : 32;
 }
 
 template <class In, int DH>
