@@ -146,12 +146,12 @@ __device__ __forceinline__ const int32_t* gram_list_rows(const GramArgs& a, int 
   return rows;
 }
 
-// kGramMax output of a tile of T x T products held as MB x NB blocks by 2 x 2
+// kGramMax output of a tile of T x TC products held as MB x NB blocks by 2 x 2
 // waves.  All rows: max G_ij / ||z_j||, from which the distance follows as
 // 1 - max / ||z_i||.  By round: minus the least distance, formed per product as
-// the picks form it.  izr: the rows' inverse norms (LDS); red: 2 T floats of LDS
+// the picks form it.  izr: the rows' inverse norms (LDS); red: 2 TC floats of LDS
 // that nothing reads any more.
-template <int T, int MB, int NB>
+template <int T, int TC, int MB, int NB>
 __device__ __forceinline__ void gram_max_store(const GramArgs& a, const f32x16 (&acc)[MB][NB], const float* izr,
                                                float* red, int b, int tc, int wj, int wi) {
   const int tid = threadIdx.x, half = (tid >> 5) & 1, col = tid & 31;
@@ -160,7 +160,7 @@ __device__ __forceinline__ void gram_max_store(const GramArgs& a, const f32x16 (
 #pragma unroll
   for (int n = 0; n < NB; ++n) {
     mx[n] = -INFINITY;
-    const int c = min(tc * T + wi * (T / 2) + n * 32 + col, a.n_cols - 1);
+    const int c = min(tc * TC + wi * (TC / 2) + n * 32 + col, a.n_cols - 1);
     const float izc = a.by_round ? a.inv_norm[(size_t)b * a.N + cols[c]] : 0.f;
 #pragma unroll
     for (int m = 0; m < MB; ++m)
@@ -174,11 +174,11 @@ __device__ __forceinline__ void gram_max_store(const GramArgs& a, const f32x16 (
   }
 #pragma unroll
   for (int n = 0; n < NB; ++n)
-    if (half == 0) red[wj * T + wi * (T / 2) + n * 32 + col] = mx[n];
+    if (half == 0) red[wj * TC + wi * (TC / 2) + n * 32 + col] = mx[n];
   __syncthreads();
-  for (int c = tid; c < T; c += blockDim.x)
-    if (tc * T + c < a.n_cols)
-      atomicMax(&a.mx[(size_t)b * a.n_cols + tc * T + c], f2key(fmaxf(red[c], red[T + c])));
+  for (int c = tid; c < TC; c += blockDim.x)
+    if (tc * TC + c < a.n_cols)
+      atomicMax(&a.mx[(size_t)b * a.n_cols + tc * TC + c], f2key(fmaxf(red[c], red[TC + c])));
 }
 
 __device__ __forceinline__ int gram_swizzle(int r, int c) { return c ^ ((r >> 1) & 7); }
@@ -314,7 +314,7 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   }
   if constexpr (MODE == kGramMax) {
     __syncthreads();  // the operand slabs are no longer read
-    gram_max_store<T, 2, 2>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
+    gram_max_store<T, T, 2, 2>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
     return;
   }
   // output: register r of block (m, n) is row wj*64 + m*32 + mfma_row(r),
@@ -446,16 +446,19 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
 constexpr int kGram256Threads = 256;
 constexpr int kGram256MinN = 2048;
 
-template <int MODE>
+template <int MODE, int TC = 256>
 __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
+  static_assert(TC == 256 || (TC == 192 && MODE == kGramMax), "tile columns");
   constexpr int T = 256;
   constexpr int SLAB = T * 128;                     // bytes of one operand's 128-byte stage
   constexpr int VPT = SLAB / 16 / kGram256Threads;  // 8 vectors per thread per operand
+  constexpr int NB = TC / 64;                       // 32-column blocks per wave
+  constexpr int SLABB = TC * 128, VPB = VPT * TC / T;  // the column operand's
   constexpr int RSTEP = kGram256Threads / 8;        // rows per load pass (8 lanes a row)
   constexpr int TA = T + 8, TB = 33, PR = 32;       // output staging (see below)
-  constexpr int LDS_OPS = 4 * SLAB;
+  constexpr int LDS_OPS = 2 * (SLAB + SLABB);
   constexpr int LDS_OUT = (PR * TA + T * TB) * 4;
-  constexpr int LDS = LDS_OPS > LDS_OUT ? LDS_OPS : LDS_OUT;
+  constexpr int LDS = MODE == kGramMax || LDS_OPS > LDS_OUT ? LDS_OPS : LDS_OUT;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
@@ -481,11 +484,11 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   const int cr = tid >> 3, cc = tid & 7;
   // the thread loads chunk cc of rows cr + RSTEP * k of both operands
   const uint32_t rowA = (uint32_t)(tj * T + cr) * rb + cc * 16;
-  const uint32_t rowB = (uint32_t)(ti * T + cr) * rb + cc * 16;
+  const uint32_t rowB = (uint32_t)(ti * TC + cr) * rb + cc * 16;
   const uint32_t kstride = (uint32_t)RSTEP * rb;
   // listed tokens: an offset per row (rows past the last re-read it)
   __shared__ float izr[MODE == kGramMax ? T : 1];
-  uint32_t offA[VPT], offB[VPT];
+  uint32_t offA[VPT], offB[VPB];
   if constexpr (MODE == kGramMax) {
     int nj;
     const int32_t* rows = gram_list_rows(a, b, nj);
@@ -493,45 +496,44 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
     const int32_t* cols = a.cols + (size_t)b * a.n_cols;
     if (tid < T) izr[tid] = a.inv_norm[(size_t)b * N + rows[min(tj * T + tid, nj - 1)]];
 #pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-      offA[k] = (uint32_t)rows[min(tj * T + cr + RSTEP * k, nj - 1)] * rb + cc * 16;
-      offB[k] = (uint32_t)cols[min(ti * T + cr + RSTEP * k, a.n_cols - 1)] * rb + cc * 16;
-    }
+    for (int k = 0; k < VPT; ++k) offA[k] = (uint32_t)rows[min(tj * T + cr + RSTEP * k, nj - 1)] * rb + cc * 16;
+#pragma unroll
+    for (int k = 0; k < VPB; ++k) offB[k] = (uint32_t)cols[min(ti * TC + cr + RSTEP * k, a.n_cols - 1)] * rb + cc * 16;
   } else {
 #pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-      offA[k] = rowA + k * kstride;
-      offB[k] = rowB + k * kstride;
-    }
+    for (int k = 0; k < VPT; ++k) offA[k] = rowA + k * kstride;
+#pragma unroll
+    for (int k = 0; k < VPB; ++k) offB[k] = rowB + k * kstride;
   }
   // LDS: operand A of buffers 0 and 1, then operand B of buffers 0 and 1
   // (every fragment address is one register per k-step and operand plus an
   // immediate offset)
   const int sdst = cr * 128 + gram_swizzle(cr, cc) * 16;  // rows RSTEP apart share the swizzle
-  u32x4 g[2][2 * VPT];
+  u32x4 g[2][VPT + VPB];
   // stage P; a chunk past the row's end (and every chunk past the last
   // stage) takes an offset outside the buffer and reads zeros
-  auto load = [&](int P, u32x4 (&dst)[2 * VPT]) {
+  auto load = [&](int P, u32x4 (&dst)[VPT + VPB]) {
     const uint32_t so = P * 128 + cc * 16 < rb ? (uint32_t)P * 128u : 0x80000000u;
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
       dst[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(zs, offA[k] + so, 0, 0));
-      dst[VPT + k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(zs, offB[k] + so, 0, 0));
+      if (k < VPB)
+        dst[VPT + k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(zs, offB[k] + so, 0, 0));
     }
   };
-  auto store = [&](int c, const u32x4 (&v)[2 * VPT]) {
+  auto store = [&](int c, const u32x4 (&v)[VPT + VPB]) {
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
       *reinterpret_cast<u32x4*>(lds + c * SLAB + sdst + k * RSTEP * 128) = v[k];
-      *reinterpret_cast<u32x4*>(lds + 2 * SLAB + c * SLAB + sdst + k * RSTEP * 128) = v[VPT + k];
+      if (k < VPB) *reinterpret_cast<u32x4*>(lds + 2 * SLAB + c * SLABB + sdst + k * RSTEP * 128) = v[VPT + k];
     }
   };
   const int wj = wave >> 1, wi = wave & 1;  // rows wj*128.., columns wi*128.. of the tile
-  f32x16 acc[4][4];
+  f32x16 acc[4][NB];
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
-    for (int n = 0; n < 4; ++n)
+    for (int n = 0; n < NB; ++n)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
   // fragments of k-step q of a stage: half h holds logical chunk 2q + h.
@@ -541,19 +543,19 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     fqa[q] = (wj * 128 + col) * 128 + ((2 * q + half) ^ sw) * 16;
-    fqb[q] = 2 * SLAB + (wi * 128 + col) * 128 + ((2 * q + half) ^ sw) * 16;
+    fqb[q] = 2 * SLAB + (wi * (TC / 2) + col) * 128 + ((2 * q + half) ^ sw) * 16;
   }
-  auto frag = [&](int c, int q, u32x4 (&fa)[4][1], u32x4 (&fb)[4][1]) {
+  auto frag = [&](int c, int q, u32x4 (&fa)[4][1], u32x4 (&fb)[NB][1]) {
 #pragma unroll
     for (int m = 0; m < 4; ++m) fa[m][0] = *reinterpret_cast<const u32x4*>(lds + fqa[q] + c * SLAB + m * 32 * 128);
 #pragma unroll
-    for (int n = 0; n < 4; ++n) fb[n][0] = *reinterpret_cast<const u32x4*>(lds + fqb[q] + c * SLAB + n * 32 * 128);
+    for (int n = 0; n < NB; ++n) fb[n][0] = *reinterpret_cast<const u32x4*>(lds + fqb[q] + c * SLABB + n * 32 * 128);
   };
-  auto mfma16 = [&](const u32x4 (&fa)[4][1], const u32x4 (&fb)[4][1]) {
+  auto mfma16 = [&](const u32x4 (&fa)[4][1], const u32x4 (&fb)[NB][1]) {
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
-      for (int n = 0; n < 4; ++n) acc[m][n] = mfma_frag(fa[m], fb[n], acc[m][n], BF16{});
+      for (int n = 0; n < NB; ++n) acc[m][n] = mfma_frag(fa[m], fb[n], acc[m][n], BF16{});
   };
   // an MFMA group of `n` multiplies, each followed by `r` LDS reads, `w` LDS
   // writes and `l` global loads (the compiler's scheduler fills the groups
@@ -569,7 +571,11 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
+  using I3 = std::integral_constant<int, 3>;
+  using I5 = std::integral_constant<int, 5>;
+  using I7 = std::integral_constant<int, 7>;
   using I8 = std::integral_constant<int, 8>;
+  using I9 = std::integral_constant<int, 9>;
   // stage P sits in register stage P % 2 and LDS buffer P % 2
   load(0, g[0]);
   __builtin_amdgcn_sched_barrier(0);
@@ -578,7 +584,7 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   store(0, g[0]);
   load(2, g[0]);
   __syncthreads();
-  u32x4 fa0[4][1], fb0[4][1], fa1[4][1], fb1[4][1];
+  u32x4 fa0[4][1], fb0[NB][1], fa1[4][1], fb1[NB][1];
   frag(0, 0, fa0, fb0);
   const int n_iter = (n_stages + 1) / 2;
   for (int it = 0; it < n_iter; ++it) {
@@ -593,10 +599,17 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
       load(P + 3, g[1 - c]);
       frag(c, 2, fa0, fb0);
       mfma16(fa1, fb1);
-      interleave(I8{}, I1{}, I0{}, I0{});
-      interleave(I8{}, I0{}, I1{}, I1{});  // the stores spread over 16 multiplies (8 cost 2% more)
-      interleave(I8{}, I0{}, I1{}, I1{});
-      interleave(I8{}, I1{}, I0{}, I0{});
+      if constexpr (NB == 4) {
+        interleave(I8{}, I1{}, I0{}, I0{});
+        interleave(I8{}, I0{}, I1{}, I1{});  // the stores spread over 16 multiplies (8 cost 2% more)
+        interleave(I8{}, I0{}, I1{}, I1{});
+        interleave(I8{}, I1{}, I0{}, I0{});
+      } else {
+        interleave(I7{}, I1{}, I0{}, I0{});
+        interleave(I5{}, I0{}, I1{}, I1{});
+        interleave(I9{}, I0{}, I1{}, I1{});
+        interleave(I3{}, I3{}, I0{}, I0{});
+      }
       __syncthreads();
       // second half: k-steps 2 and 3; stage P + 1's first fragments
       __builtin_amdgcn_sched_barrier(0);
@@ -604,17 +617,25 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
       mfma16(fa0, fb0);
       frag(1 - c, 0, fa0, fb0);
       mfma16(fa1, fb1);
-      interleave(I8{}, I1{}, I0{}, I0{});
-      interleave(I8{}, I0{}, I0{}, I0{});
-      interleave(I8{}, I1{}, I0{}, I0{});
-      interleave(I8{}, I0{}, I0{}, I0{});
+      if constexpr (NB == 4) {
+        interleave(I8{}, I1{}, I0{}, I0{});
+        interleave(I8{}, I0{}, I0{}, I0{});
+        interleave(I8{}, I1{}, I0{}, I0{});
+        interleave(I8{}, I0{}, I0{}, I0{});
+      } else {
+        interleave(I7{}, I1{}, I0{}, I0{});
+        interleave(I5{}, I0{}, I0{}, I0{});
+        interleave(I7{}, I1{}, I0{}, I0{});
+        interleave(I5{}, I0{}, I0{}, I0{});
+      }
       __syncthreads();
     }
   }
   if constexpr (MODE == kGramMax) {  // (the loop ended on a barrier)
-    gram_max_store<T, 4, 4>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
+    gram_max_store<T, TC, 4, NB>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
     return;
   }
+  if constexpr (MODE != kGramMax) {
   // register r of block (m, n) is row wj*128 + m*32 + mfma_row(r), column
   // wi*128 + n*32 + col of the tile
   if (MODE == kGramFull && tj == ti) {  // the diagonal tile holds ||z_i||^2
@@ -691,6 +712,7 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
       }
     }
   }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -744,9 +766,9 @@ template <class In, int MODE>
 __global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
   gram_tile<In, MODE>(a, blockIdx.x);
 }
-template <int MODE>
+template <int MODE, int TC = 256>
 __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a) {
-  gram256_tile<MODE>(a, blockIdx.x);
+  gram256_tile<MODE, TC>(a, blockIdx.x);
 }
 
 // The full Gram matrix of the samples that the pool rounds left unfinished,
@@ -821,13 +843,15 @@ hipError_t launch_gram_pool(const GramArgs& g0, int dtype, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_gram_max(const GramArgs& g0, int tile, int dtype, hipStream_t s) {
+hipError_t launch_gram_max(const GramArgs& g0, int tile, int ctile, int dtype, hipStream_t s) {
   GramArgs g = g0;
   g.natural = gram256_ok(dtype, g.N, g.row_bytes);
   g.n_rtiles = (g.n_rows + tile - 1) / tile;
-  g.n_ctiles = (g.n_cols + tile - 1) / tile;
+  g.n_ctiles = (g.n_cols + ctile - 1) / ctile;
   const dim3 grid(gram_grid(g.n_rtiles * g.n_ctiles, g.B));
-  if (tile == 256)
+  if (ctile == 192)
+    hipLaunchKernelGGL((gram256_kernel<kGramMax, 192>), grid, dim3(kGram256Threads), 0, s, g);
+  else if (tile == 256)
     hipLaunchKernelGGL(gram256_kernel<kGramMax>, grid, dim3(kGram256Threads), 0, s, g);
   else if (dtype == 1)
     hipLaunchKernelGGL((gram_kernel<BF16, kGramMax>), grid, dim3(kGramThreads), 0, s, g);

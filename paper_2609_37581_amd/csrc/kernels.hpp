@@ -166,8 +166,8 @@ bool gram256_ok(int dtype, int N, int row_bytes);  // 256-row tiles can be used
 hipError_t launch_gram_full(const GramArgs& g, int dtype, hipStream_t s);
 // G of the listed tokens (rows).
 hipError_t launch_gram_pool(const GramArgs& g, int dtype, hipStream_t s);
-// Maxima, by tiles of `tile` rows and columns (128, or 256 where gram256_ok).
-hipError_t launch_gram_max(const GramArgs& g, int tile, int dtype, hipStream_t s);
+// Maxima, by tiles of 128 x 128, or, where gram256_ok, 256 x 256 or 256 x 192.
+hipError_t launch_gram_max(const GramArgs& g, int rtile, int ctile, int dtype, hipStream_t s);
 // inv_norm of the listed bf16 tokens (rows), as launch_gram_full would set it.
 hipError_t launch_gram_norms(const GramArgs& g, hipStream_t s);
 
@@ -176,7 +176,7 @@ struct PickPlan {
   int rounds;                // pool rounds before the full Gram matrix (0: none)
   int C, ldc;                // pool size, row stride of its Gram matrix
   int mask_words;            // 32-bit words of a row of its mask, a multiple of 4
-  int row_tile;              // row tile of the first round's distances
+  int row_tile, col_tile;    // tile of the first round's distances
   int ldg;                   // row stride of the full Gram matrix
   int n_psplit;              // pivot splits of the initial distances over the full Gram matrix
   size_t gram_floats(int N) const;  // floats of a sample's Gram matrix, full or of the pool

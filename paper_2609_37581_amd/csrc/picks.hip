@@ -692,7 +692,7 @@ static double gram_us128(long wgs, int dtype) {
   const double one = dtype == 1 ? 0.9 : 1.8, two = dtype == 1 ? 1.45 : 3.5;
   return wgs <= 256 ? one : (wgs <= 512 ? two : two * (wgs / 512.0 + 0.5));
 }
-static double gram_us256(long wgs) { return 1.72 * ((wgs + 255) / 256); }
+static double gram_us256(long wgs, int cols = 256) { return (cols == 256 ? 1.72 : 1.5) * ((wgs + 255) / 256); }
 
 // Pool rounds or the full Gram matrix at once, whichever is estimated to take
 // less.  The pool has room for 9/4 of the picks, and grows from there while its
@@ -723,9 +723,12 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
   p.C = (int)std::min({(long)R, ct * kRoundTile, (long)kMaxPool});
   p.ldc = (int)up(p.C, 4) * 4;
   const double r128 = gram_us128(B * up(K_r, 128) * up(R, 128), dtype);
-  const double r256 = gram_us256(B * up(K_r, 256) * up(R, 256));
+  const double r256w = gram_us256(B * up(K_r, 256) * up(R, 256));
+  const double r256n = gram_us256(B * up(K_r, 256) * up(R, 192), 192);
+  const double r256 = std::min(r256w, r256n);
   p.mask_words = (int)up(p.C, 128) * 4;
   p.row_tile = big && r256 < r128 ? 256 : 128;
+  p.col_tile = p.row_tile == 128 ? 128 : (r256n < r256w ? 192 : 256);
   // the pivots' norms, the pool selection, rounds that find nothing left to do
   const double pool = slabs * ((p.row_tile == 256 ? r256 : r128) + gram_us128(B * tri(up(p.C, 128)), dtype)) +
                       (dtype == 1 ? 0.3 * slabs : 0) + 10 + R / 700 + (p.C < R ? 27 : 0) + K_d * 0.35;
@@ -754,9 +757,10 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
     g.by_round = round > 0;
     g.cols = a.rest;
     g.n_cols = a.R;
-    const int tile = round ? kRoundTile : p.row_tile;
     if (round == 0 && dtype == 1 && (err = launch_gram_norms(g, s)) != hipSuccess) return err;
-    if ((err = launch_gram_max(g, tile, dtype, s)) != hipSuccess) return err;
+    if ((err = launch_gram_max(g, round ? kRoundTile : p.row_tile, round ? kRoundTile : p.col_tile, dtype, s)) !=
+        hipSuccess)
+      return err;
 #define CALL(E_) \
   case E_: hipLaunchKernelGGL(pool_select_kernel<E_>, dim3(a.B), dim3(kSelThreads), 0, s, a, round); break
     switch (select_e(a.R)) {
