@@ -240,7 +240,8 @@ typedef struct trevs_sensitivity_args {
   float* ts;                 /* OUT [B,H_q] text sensitivity */
   float* profile[2];         /* OPTIONAL OUT per question [B,H_q,K_in] s^c_h */
   float* head_var[2];        /* OPTIONAL OUT per question [B,H_q] u_h */
-  void* const* events;       /* OPTIONAL [2*TREVS_SENSITIVITY_NUM_KERNELS] hipEvent_t */
+  void* const* events;       /* OPTIONAL [2*TREVS_SENSITIVITY_NUM_KERNELS] hipEvent_t; both questions run
+                                in one launch each, bracketed by the first question's slots */
   int32_t softmax;           /* trevs_softmax, as in trevs_inllm_args (0 = VISUAL) */
 } trevs_sensitivity_args;
 

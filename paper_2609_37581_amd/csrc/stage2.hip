@@ -50,6 +50,7 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   constexpr int TV = 32 * ROWB / 16;           // 16-byte vectors of one key tile
   constexpr int TVT = (TV + NT - 1) / NT;
   __shared__ __attribute__((aligned(16))) uint8_t klds[2][32 * LROW];
+  const int question = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
 
   u32x4 qf[NF][4];
   {
-    const uint8_t* qp = reinterpret_cast<const uint8_t*>(a.q) +
+    const uint8_t* qp = reinterpret_cast<const uint8_t*>(a.q[question]) +
                         (((size_t)b * a.S + a.P + a.K_in + q) * a.H_q + h) * ROWB + half * HALFB;
 #pragma unroll
     for (int f = 0; f < NF; ++f)
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   const int j_end = CAUSAL ? min(a.P + a.T_max, j_begin + a.rest_len) : 0;
   const int n_tiles = nv + (j_end - j_begin + 31) / 32;
   const int climit = a.P + q;  // last non-visual key index this lane's row attends
-  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(a.k) +
+  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(a.k[question]) +
                          (size_t)b * a.S * a.H_kv * ROWB + (size_t)g * ROWB;
   const size_t kstride = (size_t)a.H_kv * ROWB;
   // tile t into registers: rows past a range (and tiles past the last) re-read
@@ -201,10 +202,10 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   };
   const size_t slot = (((size_t)b * a.H_q + h) * a.T_max + q) * a.n_split + split;
   const float4 vs = merge_halves(m, l, l2);
-  if (half == 0 && rvalid) a.part[slot] = vs;
+  if (half == 0 && rvalid) a.part[question][slot] = vs;
   if constexpr (CAUSAL) {
     const float4 rs = merge_halves(mr, lr, l2r);
-    if (half == 0 && rvalid) a.part_rest[slot] = rs;
+    if (half == 0 && rvalid) a.part_rest[question][slot] = rs;
   }
 }
 
@@ -220,13 +221,13 @@ constexpr int kHeadThreads = 128;
 __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
   __shared__ float red[kHeadThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int h = blockIdx.x, b = blockIdx.y;
-  const int Tb = text_rows(a.text_len, b, a.T_max);
+  const int h = blockIdx.x, b = blockIdx.y, question = blockIdx.z;
+  const int Tb = text_rows(a.text_len[question], b, a.T_max);
   const float invK = 1.f / (float)a.K_in;
   float vs = 0.f;
   for (int q = tid; q < a.T_max; q += kHeadThreads) {
     const size_t row = ((size_t)b * a.H_q + h) * a.T_max + q;
-    const float4* pp = a.part + row * a.n_split;
+    const float4* pp = a.part[question] + row * a.n_split;
     const size_t lrow = ((size_t)b * a.H_q + h) * a.T_pad + q;
     // the splits' partials 8 at a time, every load issued before the merge
     float m = -INFINITY, l = 0.f, l2 = 0.f;
@@ -247,10 +248,10 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
       }
     }
     float lse2 = m + log2f(l);
-    if (a.lse_rest || a.part_rest) {
+    if (a.lse_rest[question] || a.part_rest[question]) {
       float r2;
-      if (a.part_rest) {
-        const float4* pr = a.part_rest + row * a.n_split;
+      if (a.part_rest[question]) {
+        const float4* pr = a.part_rest[question] + row * a.n_split;
         float mr = -INFINITY, lr = 0.f;
         for (int s0 = 0; s0 < a.n_split; s0 += 8) {
           float4 pv[8];
@@ -268,12 +269,12 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
         }
         r2 = mr + log2f(lr);
       } else {
-        r2 = a.lse_rest[row] * kLog2e;
+        r2 = a.lse_rest[question][row] * kLog2e;
       }
       const float mx = fmaxf(lse2, r2);
       lse2 = mx + log2f(fast_exp2(lse2 - mx) + fast_exp2(r2 - mx));
     }
-    a.lse2[lrow] = lse2;
+    a.lse2[question][lrow] = lse2;
     if (q < Tb) {
       const float f = fast_exp2(m - lse2);
       vs += f * f * (l2 - l * l * invK) * invK;
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
   if (tid == 0) {
     float t = 0.f;
     for (int w = 0; w < kHeadThreads / 64; ++w) t += red[w];
-    a.head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
+    a.head_var[question][(size_t)b * a.H_q + h] = t / (float)Tb;
   }
 }
 
@@ -299,14 +300,14 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
 __global__ __launch_bounds__(kHeadThreads) void heads_given_kernel(const float* row_stats, HeadArgs a) {
   __shared__ float red[kHeadThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int h = blockIdx.x, b = blockIdx.y;
-  const int Tb = text_rows(a.text_len, b, a.T_max);
+  const int h = blockIdx.x, b = blockIdx.y, question = blockIdx.z;
+  const int Tb = text_rows(a.text_len[question], b, a.T_max);
   const float invK = 1.f / (float)a.K_in;
   float vs = 0.f;
   for (int q = tid; q < a.T_max; q += kHeadThreads) {
     const size_t row = ((size_t)b * a.H_q + h) * a.T_max + q;
     const float lse = row_stats[3 * row], s1 = row_stats[3 * row + 1], s2 = row_stats[3 * row + 2];
-    a.lse2[((size_t)b * a.H_q + h) * a.T_pad + q] = lse * kLog2e;
+    a.lse2[question][((size_t)b * a.H_q + h) * a.T_pad + q] = lse * kLog2e;
     if (q < Tb) {
       const float mean = s1 * invK;
       vs += s2 * invK - mean * mean;
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(kHeadThreads) void heads_given_kernel(const float* 
   if (tid == 0) {
     float t = 0.f;
     for (int w = 0; w < kHeadThreads / 64; ++w) t += red[w];
-    a.head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
+    a.head_var[question][(size_t)b * a.H_q + h] = t / (float)Tb;
   }
 }
 
@@ -657,7 +658,7 @@ int stats_waves(int G, int T_max) {
 
 template <class In, int DH, bool CAUSAL>
 static void launch_stats_c(const StatsArgs& a, hipStream_t s) {
-  const dim3 grid(a.n_split * a.n_rgroups * a.H_kv * a.B);
+  const dim3 grid(a.n_split * a.n_rgroups * a.H_kv * a.B, a.n_questions);
   switch (stats_waves(a.G, a.T_max)) {
     case 8: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 8, CAUSAL>), grid, dim3(512), 0, s, a); break;
     case 4: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 4, CAUSAL>), grid, dim3(256), 0, s, a); break;
@@ -693,7 +694,7 @@ hipError_t launch_stats(const StatsArgs& a, int dtype, int dh, hipStream_t s) {
 }
 
 hipError_t launch_heads(const HeadArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(t2v_heads_kernel, dim3(a.H_q, a.B), dim3(kHeadThreads), 0, s, a);
+  hipLaunchKernelGGL(t2v_heads_kernel, dim3(a.H_q, a.B, a.n_questions), dim3(kHeadThreads), 0, s, a);
   return hipGetLastError();
 }
 
