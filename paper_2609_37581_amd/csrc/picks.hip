@@ -702,6 +702,7 @@ static double gram_us256(long wgs, int cols = 256) { return (cols == 256 ? 1.72 
 // candidates behind, and the neediest sample of a batch decides.  Pool tokens that the K_d picks reach down
 // to, over K_d, on features of regions of 24 tokens: 1.2 with pivots 3/8 of
 // the tokens, 1.5 at 1/4, 2.0 at 3/16, 2.5-3.2 at 1/6, 8-11 at 1/12.
+// (TREVS_PICK_ROUNDS: a number of rounds for measurements, whatever the estimate)
 #ifndef TREVS_PICK_ROUNDS
 #define TREVS_PICK_ROUNDS -1
 #endif
