@@ -49,7 +49,7 @@ __global__ __launch_bounds__(64 * QW) void t2v_profile_kernel(ProfileArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t klds[2][32 * LROW];
   __shared__ float red[2][QW][32];
   __shared__ float colsum[kProfileSplitMax];
-  const int question = blockIdx.y;
+  const bool second = blockIdx.y != 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(64 * QW) void t2v_profile_kernel(ProfileArgs a) {
   const int n_tiles = (i_end - i_begin + 31) / 32;
   for (int t = tid; t < n_tiles * 32; t += NT) colsum[t] = 0.f;
 
-  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(a.k[question]) + (seq0 + a.P) * a.H_kv * ROWB +
+  const uint8_t* kbase = reinterpret_cast<const uint8_t*>((second ? a.k[1] : a.k[0])) + (seq0 + a.P) * a.H_kv * ROWB +
                          (size_t)g * ROWB;
   const size_t kstride = (size_t)a.H_kv * ROWB;
   // one key tile (rows ib..ib+31) into registers; rows past the split re-read
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(64 * QW) void t2v_profile_kernel(ProfileArgs a) {
     }
   };
 
-  const int Tb = text_rows(a.text_len[question], b, a.T_max);
+  const int Tb = text_rows((second ? a.text_len[1] : a.text_len[0]), b, a.T_max);
   const int n_qblk = (Tb + 31) / 32;
   const int n_pass = (n_qblk + QW - 1) / QW;  // uniform over the workgroup (barriers below)
   const int n_iter = (n_tiles + RING - 1) / RING;
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * QW) void t2v_profile_kernel(ProfileArgs a) {
     const int qb = pass * QW + wave;
     const int qbc = min(qb, n_qblk - 1);
     const int qrow = min(qbc * 32 + col, a.T_max - 1);
-    const uint8_t* qp = reinterpret_cast<const uint8_t*>(a.q[question]) +
+    const uint8_t* qp = reinterpret_cast<const uint8_t*>((second ? a.q[1] : a.q[0])) +
                         ((seq0 + a.P + a.K_in + qrow) * a.H_q + h) * ROWB + half * HALFB;
     u32x4 qf[NF][4];
 #pragma unroll
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(64 * QW) void t2v_profile_kernel(ProfileArgs a) {
       for (int j = 0; j < 4; ++j) qf[f][j] = ldg16(qp + f * 64 + j * 16);
     // rows of lse2 are padded to a multiple of 32: the block's reads stay in
     // the row; entries past T_b are masked below
-    const float* lrow = a.lse2[question] + ((size_t)b * a.H_q + h) * a.T_pad + qbc * 32 + 4 * half;
+    const float* lrow = (second ? a.lse2[1] : a.lse2[0]) + ((size_t)b * a.H_q + h) * a.T_pad + qbc * 32 + 4 * half;
     float nl[16];  // minus the row log-sum-exp, or -inf for a masked row
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(64 * QW) void t2v_profile_kernel(ProfileArgs a) {
     __syncthreads();
   }
   const float inv_t = 1.f / (float)Tb;
-  float* out = a.profile[question] + ((size_t)b * a.H_q + h) * a.K_in;
+  float* out = (second ? a.profile[1] : a.profile[0]) + ((size_t)b * a.H_q + h) * a.K_in;
   for (int t = tid; t < i_end - i_begin; t += NT) out[i_begin + t] = colsum[t] * inv_t;
 }
 

@@ -568,9 +568,14 @@ __global__ __launch_bounds__(kMergeTokens * kMergeGroups, 8) void relevance_merg
   float r = 0.f;
   for (int j = g; j < Mb; j += kMergeGroups) {
     const int off = j * N + ic;
-    float tt = 0.f;  // ||t_j||^2 where prep did not form the norms: the row's 32 threads add the splits
-    if (a.fused_stats)
+    // the row's norm, loaded ahead of its products; where prep did not form it
+    // the row's 32 threads add the splits' squares
+    float tt = 0.f, itn = 0.f;
+    if (a.fused_stats) {
       for (int sp = t; sp < S; sp += kMergeTokens) tt += tp[(size_t)sp * a.M_max + j];
+    } else {
+      itn = a.inv_tnorm[(size_t)b * a.M_max + j];
+    }
     float c = 0.f;
     for (int s0 = 0; s0 < S; s0 += 16) {  // 16 loads in flight, added in split order
       float v[16];
@@ -579,13 +584,10 @@ __global__ __launch_bounds__(kMergeTokens * kMergeGroups, 8) void relevance_merg
 #pragma unroll
       for (int k = 0; k < 16; ++k) c += s0 + k < S ? v[k] : 0.f;
     }
-    float itn;
     if (a.fused_stats) {
 #pragma unroll
       for (int o = 16; o > 0; o >>= 1) tt += __shfl_xor(tt, o, 32);
       itn = 1.f / fmaxf(sqrtf(tt), 1e-12f);
-    } else {
-      itn = a.inv_tnorm[(size_t)b * a.M_max + j];
     }
     c = fmaxf(c * itn, 0.f);
     r = fmaf(c, c, r);

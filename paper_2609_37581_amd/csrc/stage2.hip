@@ -50,7 +50,8 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   constexpr int TV = 32 * ROWB / 16;           // 16-byte vectors of one key tile
   constexpr int TVT = (TV + NT - 1) / NT;
   __shared__ __attribute__((aligned(16))) uint8_t klds[2][32 * LROW];
-  const int question = blockIdx.y;
+  // (both pointers load with the other arguments; an index would wait for them)
+  const bool second = blockIdx.y != 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
@@ -66,7 +67,7 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
 
   u32x4 qf[NF][4];
   {
-    const uint8_t* qp = reinterpret_cast<const uint8_t*>(a.q[question]) +
+    const uint8_t* qp = reinterpret_cast<const uint8_t*>((second ? a.q[1] : a.q[0])) +
                         (((size_t)b * a.S + a.P + a.K_in + q) * a.H_q + h) * ROWB + half * HALFB;
 #pragma unroll
     for (int f = 0; f < NF; ++f)
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   const int j_end = CAUSAL ? min(a.P + a.T_max, j_begin + a.rest_len) : 0;
   const int n_tiles = nv + (j_end - j_begin + 31) / 32;
   const int climit = a.P + q;  // last non-visual key index this lane's row attends
-  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(a.k[question]) +
+  const uint8_t* kbase = reinterpret_cast<const uint8_t*>((second ? a.k[1] : a.k[0])) +
                          (size_t)b * a.S * a.H_kv * ROWB + (size_t)g * ROWB;
   const size_t kstride = (size_t)a.H_kv * ROWB;
   // tile t into registers: rows past a range (and tiles past the last) re-read
@@ -202,10 +203,10 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   };
   const size_t slot = (((size_t)b * a.H_q + h) * a.T_max + q) * a.n_split + split;
   const float4 vs = merge_halves(m, l, l2);
-  if (half == 0 && rvalid) a.part[question][slot] = vs;
+  if (half == 0 && rvalid) (second ? a.part[1] : a.part[0])[slot] = vs;
   if constexpr (CAUSAL) {
     const float4 rs = merge_halves(mr, lr, l2r);
-    if (half == 0 && rvalid) a.part_rest[question][slot] = rs;
+    if (half == 0 && rvalid) (second ? a.part_rest[1] : a.part_rest[0])[slot] = rs;
   }
 }
 
@@ -221,13 +222,20 @@ constexpr int kHeadThreads = 128;
 __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
   __shared__ float red[kHeadThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int h = blockIdx.x, b = blockIdx.y, question = blockIdx.z;
-  const int Tb = text_rows(a.text_len[question], b, a.T_max);
+  const int h = blockIdx.x, b = blockIdx.y;
+  const bool second = blockIdx.z != 0;
+  const int32_t* const q_text_len = second ? a.text_len[1] : a.text_len[0];
+  const float4* const q_part = second ? a.part[1] : a.part[0];
+  const float4* const q_part_rest = second ? a.part_rest[1] : a.part_rest[0];
+  const float* const q_lse_rest = second ? a.lse_rest[1] : a.lse_rest[0];
+  float* const q_lse2 = second ? a.lse2[1] : a.lse2[0];
+  float* const q_head_var = second ? a.head_var[1] : a.head_var[0];
+  const int Tb = text_rows(q_text_len, b, a.T_max);
   const float invK = 1.f / (float)a.K_in;
   float vs = 0.f;
   for (int q = tid; q < a.T_max; q += kHeadThreads) {
     const size_t row = ((size_t)b * a.H_q + h) * a.T_max + q;
-    const float4* pp = a.part[question] + row * a.n_split;
+    const float4* pp = q_part + row * a.n_split;
     const size_t lrow = ((size_t)b * a.H_q + h) * a.T_pad + q;
     // the splits' partials 8 at a time, every load issued before the merge
     float m = -INFINITY, l = 0.f, l2 = 0.f;
@@ -248,10 +256,10 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
       }
     }
     float lse2 = m + log2f(l);
-    if (a.lse_rest[question] || a.part_rest[question]) {
+    if (q_lse_rest || q_part_rest) {
       float r2;
-      if (a.part_rest[question]) {
-        const float4* pr = a.part_rest[question] + row * a.n_split;
+      if (q_part_rest) {
+        const float4* pr = q_part_rest + row * a.n_split;
         float mr = -INFINITY, lr = 0.f;
         for (int s0 = 0; s0 < a.n_split; s0 += 8) {
           float4 pv[8];
@@ -269,12 +277,12 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
         }
         r2 = mr + log2f(lr);
       } else {
-        r2 = a.lse_rest[question][row] * kLog2e;
+        r2 = q_lse_rest[row] * kLog2e;
       }
       const float mx = fmaxf(lse2, r2);
       lse2 = mx + log2f(fast_exp2(lse2 - mx) + fast_exp2(r2 - mx));
     }
-    a.lse2[question][lrow] = lse2;
+    q_lse2[lrow] = lse2;
     if (q < Tb) {
       const float f = fast_exp2(m - lse2);
       vs += f * f * (l2 - l * l * invK) * invK;
@@ -286,7 +294,7 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
   if (tid == 0) {
     float t = 0.f;
     for (int w = 0; w < kHeadThreads / 64; ++w) t += red[w];
-    a.head_var[question][(size_t)b * a.H_q + h] = t / (float)Tb;
+    q_head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
   }
 }
 
@@ -300,14 +308,18 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
 __global__ __launch_bounds__(kHeadThreads) void heads_given_kernel(const float* row_stats, HeadArgs a) {
   __shared__ float red[kHeadThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int h = blockIdx.x, b = blockIdx.y, question = blockIdx.z;
-  const int Tb = text_rows(a.text_len[question], b, a.T_max);
+  const int h = blockIdx.x, b = blockIdx.y;
+  const bool second = blockIdx.z != 0;
+  const int32_t* const q_text_len = second ? a.text_len[1] : a.text_len[0];
+  float* const q_lse2 = second ? a.lse2[1] : a.lse2[0];
+  float* const q_head_var = second ? a.head_var[1] : a.head_var[0];
+  const int Tb = text_rows(q_text_len, b, a.T_max);
   const float invK = 1.f / (float)a.K_in;
   float vs = 0.f;
   for (int q = tid; q < a.T_max; q += kHeadThreads) {
     const size_t row = ((size_t)b * a.H_q + h) * a.T_max + q;
     const float lse = row_stats[3 * row], s1 = row_stats[3 * row + 1], s2 = row_stats[3 * row + 2];
-    a.lse2[question][((size_t)b * a.H_q + h) * a.T_pad + q] = lse * kLog2e;
+    q_lse2[((size_t)b * a.H_q + h) * a.T_pad + q] = lse * kLog2e;
     if (q < Tb) {
       const float mean = s1 * invK;
       vs += s2 * invK - mean * mean;
@@ -319,7 +331,7 @@ __global__ __launch_bounds__(kHeadThreads) void heads_given_kernel(const float* 
   if (tid == 0) {
     float t = 0.f;
     for (int w = 0; w < kHeadThreads / 64; ++w) t += red[w];
-    a.head_var[question][(size_t)b * a.H_q + h] = t / (float)Tb;
+    q_head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
   }
 }
 
