@@ -227,19 +227,21 @@ trevs_status validate_inllm(const trevs_inllm_args* a) {
 // the GPU (>= 2 per CU), each split at least 64 keys, lengths multiples of 64
 // (two key tiles of 32).  fp32 tiles take 1.8 us of multiplies each, so splits
 // of one tile pay while they still leave CUs idle (1 x 192 keys, 32 heads: 32.1 ->
-// 30.0 us a call; with 252 workgroups already, 28 x 141 keys, 131 -> 140).
+// 30.0 us a call; with 252 workgroups already, 28 x 141 keys, 131 -> 140);
+// `coarse` keeps two tiles.
 struct StatsPlan {
   int n_split, split_len, n_rgroups;
   int rest_len;  // causal non-visual keys per split, multiple of 32 (0: visual-only softmax)
 };
-StatsPlan stats_plan(int dtype, int B, int K_in, int T_max, int H_q, int H_kv, int softmax, int P) {
+StatsPlan stats_plan(int dtype, int B, int K_in, int T_max, int H_q, int H_kv, int softmax, int P,
+                     bool coarse = false) {
   StatsPlan p;
   const int G = H_q / H_kv;
   const int nrb = (G * T_max + 31) / 32;
   const int nw = stats_waves(G, T_max);
   p.n_rgroups = (nrb + nw - 1) / nw;
   const int64_t base_wgs = (int64_t)B * H_kv * p.n_rgroups;
-  const int unit = dtype == TREVS_F32 && base_wgs * ((K_in + 63) / 64) <= 128 ? 32 : 64;
+  const int unit = !coarse && dtype == TREVS_F32 && base_wgs * ((K_in + 63) / 64) <= 128 ? 32 : 64;
   int n_split = (int)std::min<int64_t>((512 + base_wgs - 1) / base_wgs, (K_in + unit - 1) / unit);
   n_split = std::max(n_split, 1);
   p.split_len = ((K_in + n_split - 1) / n_split + unit - 1) / unit * unit;
@@ -251,10 +253,12 @@ StatsPlan stats_plan(int dtype, int B, int K_in, int T_max, int H_q, int H_kv, i
 
 size_t lse_rows_padded(int T_max) { return (size_t)(T_max + 31) / 32 * 32; }
 
-InllmPlan inllm_plan(const trevs_inllm_args* a) {
+// `coarse`: the splits that 32-token score tiles and two-tile key splits give,
+// with less workspace.
+InllmPlan inllm_plan_of(const trevs_inllm_args* a, bool coarse) {
   InllmPlan p;
   const StatsPlan sp = stats_plan(a->dtype, a->B, a->K_in, a->T_max, a->H_q, a->H_kv,
-                                  a->row_stats ? TREVS_SOFTMAX_VISUAL : a->softmax, a->P);
+                                  a->row_stats ? TREVS_SOFTMAX_VISUAL : a->softmax, a->P, coarse);
   p.n_split = sp.n_split;
   p.split_len = sp.split_len;
   p.n_rgroups = sp.n_rgroups;
@@ -275,7 +279,9 @@ InllmPlan inllm_plan(const trevs_inllm_args* a) {
   off = align_up(off + (size_t)a->B * a->K_in * sizeof(float));
   const int vt = score_tile_tokens(a->dtype, a->d_head);
   p.n_vtiles = (a->K_in + vt - 1) / vt;
-  const int hs = score_head_splits(a->B, p.n_vtiles, a->n_keep_heads);
+  // rows over 256 bytes: 64-token tiles halve the tiles and so double the splits
+  const int st = coarse && a->d_head * elem_bytes(a->dtype) > 256 ? 32 : vt;
+  const int hs = score_head_splits(a->B, (a->K_in + st - 1) / st, a->n_keep_heads);
   p.hps = (a->n_keep_heads + hs - 1) / hs;
   p.n_hsplit = (a->n_keep_heads + p.hps - 1) / p.hps;  // no split is empty
   if ((size_t)a->B * p.n_hsplit * a->T_max * a->K_in * sizeof(float) > (size_t(256) << 20)) {
@@ -286,6 +292,16 @@ InllmPlan inllm_plan(const trevs_inllm_args* a) {
   off = align_up(off + (p.n_hsplit > 1 ? (size_t)a->B * p.n_hsplit * a->T_max * a->K_in * sizeof(float) : 0));
   p.total = off;
   return p;
+}
+
+// The finer splits, unless the coarser ones fit the static array of
+// trevs_inllm_prune_noalloc and the finer do not (a call that it can serve is
+// not refused for a faster split), or the finer ones' head sums are so large
+// that the split was given up.
+InllmPlan inllm_plan(const trevs_inllm_args* a) {
+  const InllmPlan fine = inllm_plan_of(a, false), coarse = inllm_plan_of(a, true);
+  const size_t room = TREVS_NOALLOC_SCRATCH_BYTES;
+  return (fine.total > room) != (coarse.total > room) || fine.n_hsplit < coarse.n_hsplit ? coarse : fine;
 }
 
 // ------------------------------------------------------------------ analysis

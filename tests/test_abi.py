@@ -267,3 +267,27 @@ def test_inllm_row_stats_rejections():
     plain = _inllm()
     # no statistics pass: its split partials leave the workspace
     assert 0 < L.trevs_inllm_workspace_size(ctypes.byref(ok)) < L.trevs_inllm_workspace_size(ctypes.byref(plain))
+
+
+
+@pytest.mark.parametrize("dtype,B,H_q,H_kv,K,T,d", [
+    (trevs.TREVS_F32, 1, 56, 8, 998, 340, 128),
+    (trevs.TREVS_F32, 4, 16, 4, 1761, 289, 128),
+    (trevs.TREVS_BF16, 2, 28, 4, 1172, 333, 256),
+    (trevs.TREVS_BF16, 10, 56, 8, 300, 343, 256),
+])
+def test_noalloc_room_holds_the_coarse_head_splits(dtype, B, H_q, H_kv, K, T, d):
+    """Rows of 512 bytes: the head splits of 32-token score tiles fit the static
+    array here (2 to 12 MB), those of 64-token tiles need 17 to 25 MB; the call
+    must be planned with the former and not be refused."""
+    a = _inllm(dtype=dtype, B=B, S=K + T, P=0, K_in=K, T_max=T, H_q=H_q, H_kv=H_kv, d_head=d,
+               n_keep_heads=H_q // 2, k_keep=1)
+    assert 0 < trevs.lib().trevs_inllm_workspace_size(ctypes.byref(a)) <= 16 << 20
+
+
+def test_very_long_text_keeps_its_head_split():
+    """1 x 2000 keys, 6000 text rows, fp32: the head sums of the finer split pass
+    256 MiB, those of the coarser do not (192 MB), so heads stay split."""
+    a = _inllm(dtype=trevs.TREVS_F32, B=1, S=8000, P=0, K_in=2000, T_max=6000, H_q=32, H_kv=8, n_keep_heads=16,
+               k_keep=1)
+    assert trevs.lib().trevs_inllm_workspace_size(ctypes.byref(a)) > 4 * 6000 * 2000 * 4 - 1

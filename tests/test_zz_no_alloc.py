@@ -40,3 +40,12 @@ def test_noalloc_matches_the_workspace_entry_point():
         for key in ref:
             assert np.array_equal(got[key], ref[key]), (w.name, key)
         s2.check(inp, w, got)
+
+
+def test_noalloc_with_the_coarse_head_splits():
+    # fp32, 1 x 998 keys, 340 text rows: the finer head splits would not fit the array
+    w = WORKLOADS["qwen25vl-b4-bf16"].with_(B=1, dtype="f32", H_q=56, H_kv=8, P=0, N=998, M_max=340, K1=998, K2=300, n_keep=28)
+    print(f"[noalloc] coarse splits K1={w.K1} T={w.T_max}", flush=True)
+    inp = stage2_inputs(w)
+    got = _run(inp, w, noalloc=True)
+    s2.check(inp, w, got)
