@@ -84,7 +84,9 @@ typedef enum trevs_dtype { TREVS_F32 = 0, TREVS_BF16 = 1 } trevs_dtype;
  * K_d more tokens are added by farthest point sampling (context
  * preservation, Sec. 4.1 after Eq. (7)): one at a time, the token outside
  * the selected set whose cosine distance 1 - zbar_i . zbar_j to its nearest
- * selected token is largest (ties to the lower index).  The workspace has
+ * selected token is largest (ties to the lower index).  Tokens whose distance
+ * is not a number (the squares of a row overflow fp32) follow after all others,
+ * in index order.  The workspace has
  * room for the Gram matrix Z Z^T of every sample, which is formed where the
  * picks need all of it (B*N*N floats and some MB beyond the k_div = 0 size,
  * e.g. 4.3 GB at B = 4, N = 16,384; 85 MB at B = 64, N = 576);

@@ -217,23 +217,47 @@ __device__ __forceinline__ void mark_selected(const PickArgs& a, int b, int np, 
   __syncthreads();
 }
 
-// The kept list: pivots and all picks in ascending order, one word of 32
-// tokens per thread.
-__device__ __forceinline__ void write_kept(const PickArgs& a, int b, PickShared& sh) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, K = a.K_r + a.K_d;
-  mark_selected(a, b, a.K_d, sh);
-  uint32_t word = tid < (a.N + 31) / 32 ? sh.bits[tid] : 0u;
+// f(rank, token) for every set bit of the workgroup's words (32 tokens a
+// thread), in token order.
+template <class F>
+__device__ __forceinline__ void each_token(uint32_t word, PickShared& sh, F f) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int cnt = __popc(word), inc = wave_incl_scan(cnt, lane);
   if (lane == kWave - 1) sh.wtot[wave] = inc;
   __syncthreads();
   const int wt = lane < kSelWaves ? sh.wtot[lane] : 0, wi = wave_incl_scan(wt, lane);
   int at = __builtin_amdgcn_readlane(wi - wt, wave) + inc - cnt;
-  int32_t* kept = a.kept_idx + (size_t)b * K;
   while (word) {
-    if (at < K) kept[at] = tid * 32 + __builtin_ctz(word);  // K set; the bound guards memory
+    f(at, tid * 32 + __builtin_ctz(word));
     ++at;
     word &= word - 1;
   }
+}
+
+// Picks t.. of a sample whose other tokens have no distance (a row whose
+// squares overflow is infinitely long, and its products times 1/infinity are
+// not numbers): the unselected tokens in index order.
+__device__ __forceinline__ void fill_picks(const PickArgs& a, int b, int t, PickShared& sh) {
+  const int first = threadIdx.x * 32, N = a.N;
+  mark_selected(a, b, t, sh);
+  const uint32_t valid = first + 32 <= N ? ~0u : (first < N ? (1u << (N - first)) - 1u : 0u);
+  each_token(valid ? ~sh.bits[threadIdx.x] & valid : 0u, sh, [&](int at, int tok) {
+    if (t + at < a.K_d) {
+      a.picks[(size_t)b * a.K_d + t + at] = tok;
+      if (a.div_idx) a.div_idx[(size_t)b * a.K_d + t + at] = tok;
+    }
+  });
+  __syncthreads();
+}
+
+// The kept list: pivots and all picks in ascending order.
+__device__ __forceinline__ void write_kept(const PickArgs& a, int b, PickShared& sh) {
+  const int K = a.K_r + a.K_d;
+  mark_selected(a, b, a.K_d, sh);
+  int32_t* kept = a.kept_idx + (size_t)b * K;
+  each_token(threadIdx.x < (a.N + 31) / 32 ? sh.bits[threadIdx.x] : 0u, sh, [&](int at, int tok) {
+    if (at < K) kept[at] = tok;  // K set; the bound guards memory
+  });
 }
 
 // The scale of a batch.  bin(key, entry): steps below the largest key, kBins
@@ -487,8 +511,9 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a) {
     ctrl[kCtrlPicks] = t;
     ctrl[kCtrlRound] = t0;
   }
-  if (t < K_d) return;  // uniform
-  __syncthreads();      // the picks written above
+  if (t < K_d && C < a.R) return;  // uniform
+  __syncthreads();                 // the picks written above
+  if (t < K_d) fill_picks(a, b, t, sh);  // the pool held every token: no round follows
   write_kept(a, b, sh);
 }
 
@@ -668,13 +693,7 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
     if (m < kBatch / 2) range = m < kBatch / 8 ? 2.f : 2.f * range;
   }
   __syncthreads();  // the picks written above
-  if (t < K_d) {    // only distances that are not numbers are left: token 0 stands in
-    for (int p = t + tid; p < K_d; p += kSelThreads) {
-      picks[p] = 0;
-      if (a.div_idx) a.div_idx[(size_t)b * K_d + p] = 0;
-    }
-    __syncthreads();
-  }
+  if (t < K_d) fill_picks(a, b, t, sh);
   write_kept(a, b, sh);
 }
 

@@ -72,6 +72,48 @@ def test_picks_of_clustered_tokens(name):
     assert torch.equal(again, call.div_idx)
 
 
+@pytest.mark.parametrize("N,d,K,k_div,dtype,huge", [
+    (2304, 1024, 2304, 288, "bf16", 3),     # a pool of all tokens, every token kept
+    (2304, 1024, 1152, 288, "bf16", 1200),  # a pool of all tokens, fewer distances than picks
+    (3000, 1028, 3000, 175, "f32", 1),
+    (300, 64, 300, 40, "bf16", 33),         # the full Gram matrix at once
+    (9000, 64, 400, 256, "bf16", 8700),     # rounds that find too little, then the full Gram matrix
+])
+def test_tokens_without_a_distance(N, d, K, k_div, dtype, huge):
+    """Finite rows whose products overflow have no distance (infinity times 1/infinity).
+    The tokens that have one are picked first; then the others fill the set in
+    index order, and the kept list is complete."""
+    print(f"[picks-overflow] N={N} d={d} K={K} K_d={k_div} {dtype} huge={huge}", flush=True)
+    rng = np.random.default_rng(N + huge)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Z = rng.standard_normal((2, N, d)).astype(np.float32)
+    cls = rng.standard_normal((2, 4, N)).astype(np.float32)
+    rows = np.sort(rng.permutation(N)[:huge])
+    usable = np.setdiff1d(np.arange(N), rows)
+    Z[0, rows] = 3e38 * np.where(rng.random((huge, d)) < 0.5, -1.0, 1.0)  # sample 1 has none
+    for b in range(2):
+        cls[b][:, rng.choice(usable, min(K - k_div, usable.size), replace=False)] += 8.0
+    Zt = torch.from_numpy(Z).to(dt)
+    T = torch.from_numpy(rng.standard_normal((2, 8, d)).astype(np.float32)).to(dt).cuda()
+    call = trevs.Prellm(torch.from_numpy(cls).to(dt).cuda(), Zt.cuda(), T, k_keep=K, k_div=k_div,
+                        textual_ratio=0.0, ratio_mode="budget", want_scores=True)
+    call()
+    torch.cuda.synchronize()
+    kept, picks, sal = call.kept_idx.cpu().numpy(), call.div_idx.cpu().numpy(), call.sal.cpu().numpy()
+    for b in range(2):
+        pivots = oracle.topk_ascending(sal[b].astype(np.float64), K - k_div)
+        assert np.array_equal(kept[b], np.unique(np.concatenate([pivots, picks[b]]))), b
+        assert kept[b].size == K and kept[b][0] >= 0 and kept[b][-1] < N, b
+        have = usable if b == 0 else np.arange(N)
+        with_distance = np.setdiff1d(have, pivots)
+        n = min(k_div, with_distance.size)
+        assert np.isin(picks[b][:n], with_distance).all(), b
+        check_fps_picks(Zt[b][torch.from_numpy(have)].double().numpy(), np.searchsorted(have, np.intersect1d(pivots, have)),
+                        np.searchsorted(have, picks[b][:n]))
+        left = np.setdiff1d(np.arange(N), np.concatenate([pivots, picks[b][:n]]))
+        assert np.array_equal(picks[b][n:], left[:k_div - n]), b
+
+
 @pytest.mark.parametrize("d,dtype", [(1032, "bf16"), (1024, "bf16"), (1028, "f32")])
 def test_relevance_text_lengths_at_block_edges(d, dtype):
     """Question lengths around the 32-row text blocks (the blocks past the last
