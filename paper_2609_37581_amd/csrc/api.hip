@@ -54,7 +54,7 @@ trevs_status record(void* const* events, int slot, hipStream_t s) {
 struct PrellmLayout {
   size_t row_stats, inv_tnorm, sal, rel, stats, rel_part, total;
   size_t inv_norm, pivots, ctrl, picks, gram, pick_part, rest, mx, near_piv, near_pick, cand, cand_piv, cand_pick,
-      cand_dist, mask;  // diversity set
+      cand_cos, mask;  // diversity set
   RelPlan rel_plan;
   PickPlan picks_plan;
 };
@@ -129,7 +129,7 @@ PrellmLayout prellm_layout(const trevs_prellm_args* a) {
   L.rel_part = off;  // partial products of a feature-dimension split
   off = align_up(off + L.rel_plan.part_floats() * sizeof(float));
   L.inv_norm = L.pivots = L.ctrl = L.picks = L.gram = L.pick_part = off;
-  L.rest = L.mx = L.near_piv = L.near_pick = L.cand = L.cand_piv = L.cand_pick = L.cand_dist = L.mask = off;
+  L.rest = L.mx = L.near_piv = L.near_pick = L.cand = L.cand_piv = L.cand_pick = L.cand_cos = L.mask = off;
   L.picks_plan = PickPlan{};
   if (a->k_div > 0) {
     const int K_r = a->k_keep - a->k_div;
@@ -155,7 +155,7 @@ PrellmLayout prellm_layout(const trevs_prellm_args* a) {
       take(L.cand, B * p.C);
       take(L.cand_piv, B * p.C);
       take(L.cand_pick, B * p.C);
-      take(L.cand_dist, B * p.C);
+      take(L.cand_cos, B * p.C);
       take(L.mask, B * p.C * p.mask_words);
     }
   }
@@ -548,6 +548,7 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
     pa.K_r = K_r;
     pa.K_d = a->k_div;
     pa.R = a->N - K_r;
+    pa.gap = norm_gap(a->d);
     pa.pivots = pivots;
     pa.rest = reinterpret_cast<const int32_t*>(w + L.rest);
     pa.inv_norm = reinterpret_cast<float*>(w + L.inv_norm);
@@ -561,7 +562,7 @@ trevs_status trevs_prellm_prune(const trevs_prellm_args* a, void* ws, size_t ws_
     pa.mask = reinterpret_cast<uint32_t*>(w + L.mask);
     pa.ctrl = reinterpret_cast<int32_t*>(w + L.ctrl);
     pa.cand = reinterpret_cast<int32_t*>(w + L.cand);
-    pa.cand_dist = reinterpret_cast<float*>(w + L.cand_dist);
+    pa.cand_cos = reinterpret_cast<float*>(w + L.cand_cos);
     pa.picks = reinterpret_cast<int32_t*>(w + L.picks);
     pa.kept_idx = a->kept_idx;
     pa.div_idx = a->div_idx;

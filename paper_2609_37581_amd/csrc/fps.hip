@@ -207,15 +207,16 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   const int rb = a.row_bytes;
   int nj = a.N, ni = a.N;  // tokens along the rows and columns
   const int32_t *rows = nullptr, *cols = nullptr;
-  __shared__ float izr[MODE == kGramFull ? 1 : T], izc[MODE == kGramPool ? T : 1], dr[MODE == kGramPool ? T : 1],
-      dc[MODE == kGramPool ? T : 1];
+  __shared__ float izr[MODE == kGramFull ? 1 : T], izc[MODE == kGramPool ? T : 1], xr[MODE == kGramPool ? T : 1],
+      xc[MODE == kGramPool ? T : 1];
   if (MODE != kGramFull) {
     rows = cols = gram_list_rows(a, b, nj);
     ni = nj;
-    if (MODE == kGramPool) {  // tokens past the list have distance -inf: nothing is nearer
+    if (MODE == kGramPool) {  // nothing is nearer to tokens past the list, nor to selected ones (infinity)
       const int i = (tid < T ? tj * T : ti * T - T) + tid, ic = min(i, nj - 1);
+      const float x = a.nearest[(size_t)b * nj + ic];
       (tid < T ? izr : izc)[tid & (T - 1)] = a.inv_norm[(size_t)b * a.N + rows[ic]];
-      (tid < T ? dr : dc)[tid & (T - 1)] = i < nj ? a.dist[(size_t)b * nj + ic] + kNearMargin : -INFINITY;
+      (tid < T ? xr : xc)[tid & (T - 1)] = i < nj ? x * (x > 0.f ? 1.f - a.margin : 1.f + a.margin) : INFINITY;
     }
     if (MODE == kGramMax) {
       if (tj * T >= nj) return;
@@ -342,16 +343,16 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
         const int c = wi * 64 + n * 32 + col;
-        const float iz = izc[c], d = dc[c];
+        const float iz = izc[c], x = xc[c];
         uint32_t wrow = 0u, wcol = 0u;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = mfma_row(r, half), j = wj * 64 + m * 32 + row;
-          const float nd = 1.f - acc[m][n][r] * iz * izr[j];
-          const unsigned long long bal = __ballot(nd < d);
+          const float cosine = acc[m][n][r] * iz * izr[j];
+          const unsigned long long bal = __ballot(cosine > x);
           wrow = lane == mfma_row(r, 0) ? (uint32_t)bal : wrow;
           wrow = lane == mfma_row(r, 1) ? (uint32_t)(bal >> 32) : wrow;
-          wcol |= nd < dr[j] ? 1u << row : 0u;
+          wcol |= cosine > xr[j] ? 1u << row : 0u;
         }
         wcol |= __shfl_xor(wcol, 32, 64);
         const int j = tj * T + wj * 64 + m * 32 + lane, i = ti * T + c;

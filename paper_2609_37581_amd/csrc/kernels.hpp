@@ -135,8 +135,8 @@ struct ScoreArgs {
 // ---------------------------------------------------------------- diversity set
 // Control words of one sample's picks, zeroed by the pivot selection.
 // kCtrlPicks: tokens picked so far; kCtrlRound: picks before the last round;
-// kCtrlBound: distance (float bits) that no token outside the round's pool
-// exceeds by more than kNearMargin.
+// kCtrlBound: the largest distance (float bits) outside the round's pool, as
+// the pool was selected (see norm_gap).
 constexpr int kPickCtrl = 4;
 enum { kCtrlPicks = 0, kCtrlRound = 1, kCtrlBound = 2 };
 
@@ -159,15 +159,30 @@ struct GramArgs {
   float* inv_norm;           // [B,N] 1 / max(||z_i||, 1e-12); set from G by launch_gram_full
   uint32_t* mx;              // [B,n_cols] maxima, as keys (f2key), over 0 or what is there
   // pool: bit i of row j of mask [B,n_rows,mask_words] is set where token j may
-  // bring token i nearer than dist [B,n_rows] (see kNearMargin)
+  // bring token i nearer: its cosine to i is above that of the nearest selected
+  // token, nearest [B,n_rows], less the share `margin` of it (see norm_gap)
   uint32_t* mask;
   int mask_words;
-  const float* dist;
+  const float* nearest;
+  float margin;
 };
-// Distances formed with inverse norms of the relevance pass are within this of
-// those formed with the norms of the Gram matrix: the two sums of d squares
-// differ by less than 1e-5 of the norm, and a distance by that times the cosine.
-constexpr float kNearMargin = 2e-5f;
+// A token's inverse norm as the relevance pass forms it is within this share of
+// the one from the Gram diagonal.  A sum of positive terms that pass n
+// fp32 roundings each is within n 2^-24 of the exact one: at most d + 1 on the
+// diagonal (a multiply of n products rounds at most n times, an fp32 product once
+// more), d / 8 + 56 in the relevance pass (chunks of 16 bytes, one half-row a lane,
+// 32 groups of splits).  The inverse norm has half of both, and four
+// roundings of its own each; the rest is room for the few that cosines add.
+// (Rows of equal magnitudes come to a tenth of this: their rounding errors
+// have one sign.)
+// Distances 1 - x, 1 - x' with x' within the share e of x: a token outside
+// the pool, at most `bound` far by the relevance pass's norms, is at most
+// bound + e |1 - bound| far by the Gram matrix's.  And pick j brings token i
+// nearer only if their cosine c, off by 2 e |c|, is above i's, off by e |x|: if
+// c > x - 3 e |x| / (1 - 2 e) by the relevance pass's norms.
+inline float norm_gap(int d) { return (0.6f * d + 64.f) * 5.9604645e-8f; }
+constexpr int kNormGapMaxD = 1 << 18;  // a gap of 0.01
+constexpr float kMaskMargin = 3.1f;    // 3 / (1 - 2 e)
 bool gram256_ok(int dtype, int N, int row_bytes);  // 256-row tiles can be used
 // G of all N tokens; with ctrl, of the samples that are not finished.
 hipError_t launch_gram_full(const GramArgs& g, int dtype, hipStream_t s);
@@ -193,6 +208,7 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes);
 struct PickArgs {
   PickPlan p;
   int B, N, K_r, K_d, R;     // R = N - K_r
+  float gap;                 // norm_gap of the rows
   const int32_t* pivots;     // [B,K_r] ascending
   const int32_t* rest;       // [B,R] ascending, the other tokens (pool rounds)
   float* inv_norm;           // [B,N]
@@ -206,7 +222,7 @@ struct PickArgs {
   int32_t* cand;             // [B,C] pool tokens, ascending
   float* cand_piv;           // [B,C] their near_piv,
   float* cand_pick;          // [B,C] near_pick
-  float* cand_dist;          // [B,C] and distance, from the relevance pass's norms
+  float* cand_cos;           // [B,C] and cosine to the nearest, from the relevance pass's norms
   uint32_t* mask;            // [B,C,mask_words]
   int32_t* picks;            // [B,K_d]
   int32_t* kept_idx;         // [B,K_r+K_d] ascending

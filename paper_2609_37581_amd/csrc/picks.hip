@@ -78,8 +78,7 @@ __global__ __launch_bounds__(kFpsInitThreads) void fps_init_kernel(PickArgs a) {
 // products left (round 0: over the pivots; later: over the last round's
 // picks, as minus the least distance), and keeps the C farthest, in index
 // order.  The distances here are formed with the norms of the relevance pass,
-// which every token has; no token outside the pool is farther than the C-th
-// largest of them (the bound) by more than the two norms differ.
+// which every token has; the C-th largest of them is the bound (see norm_gap).
 // ---------------------------------------------------------------------------
 template <int E>
 __global__ __launch_bounds__(kSelThreads) void pool_select_kernel(PickArgs a, int round) {
@@ -130,14 +129,15 @@ __global__ __launch_bounds__(kSelThreads) void pool_select_kernel(PickArgs a, in
 #pragma unroll
   for (int e = 0; e < E; ++e) key[e] = f2key(d[e]);
   int32_t* cand = a.cand + (size_t)b * C;
-  float* cand_dist = a.cand_dist + (size_t)b * C;
+  float* cand_cos = a.cand_cos + (size_t)b * C;
   float* cand_piv = a.cand_piv + (size_t)b * C;
   float* cand_pick = a.cand_pick + (size_t)b * C;
   auto put = [&](int at, int e) {
+    const float piv = near_piv[tok[e]], pick = near_pick[tok[e]];
     cand[at] = tok[e];
-    cand_dist[at] = d[e];
-    cand_piv[at] = near_piv[tok[e]];
-    cand_pick[at] = near_pick[tok[e]];
+    cand_cos[at] = fmaxf(piv * a.inv_norm[(size_t)b * a.N + tok[e]], 1.f - pick);
+    cand_piv[at] = piv;
+    cand_pick[at] = pick;
   };
   float bound = -INFINITY;
   if (C >= R) {
@@ -344,8 +344,8 @@ __device__ __forceinline__ int batch_picks(int m, int limit, uint32_t out, const
 // marked entries (reading whole rows of G, 9 KB for each pick at 37 GB/s a
 // CU, took 12 us of a batch's 32).
 // A pick must also be farther than every token outside the pool: its distance
-// is above the round's bound and the margin between the two norms.  The round
-// ends where that fails; at K_d picks the kept list is written.
+// is above the round's bound and what the norms may differ by.  The round ends
+// where that fails; at K_d picks the kept list is written.
 // ---------------------------------------------------------------------------
 constexpr int kHits = 4096;  // marked (pick, entry) pairs taken at once
 constexpr int kMaxPoolPicks = kMaxPool / 2;
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a) {
   const int t0 = ctrl[kCtrlPicks];
   int t = t0;
   const float bound = __int_as_float(ctrl[kCtrlBound]);
-  const uint32_t floor_key = bound > -INFINITY ? f2key(bound + kNearMargin) : f2key(-INFINITY);
+  const uint32_t floor_key = bound > -INFINITY ? f2key(bound + a.gap * fabsf(1.f - bound)) : f2key(-INFINITY);
   const int32_t* cand = a.cand + (size_t)b * C;
   const float* G = a.G + (size_t)b * C * ldc;
   const u32x4* mask = reinterpret_cast<const u32x4*>(a.mask) + (size_t)b * C * mw4;
@@ -733,6 +733,7 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
   p.n_psplit = std::min(std::max(K_r / 256, 1), 8);  // about 256 pivots each
   const int R = N - K_r;
   const bool big = gram256_ok(dtype, N, row_bytes);
+  const int d = row_bytes / (dtype == 1 ? 2 : 4);
   const double slabs = up(row_bytes, 128);
   // stores of G at 4 TB/s, the initial distances; a pick reads a row at 37 GB/s
   const double full = slabs * (big ? gram_us256(B * tri(up(N, 256))) : gram_us128(B * tri(up(N, 128)), dtype)) +
@@ -752,7 +753,7 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
   // the pivots' norms, the pool selection, rounds that find nothing left to do
   const double pool = slabs * ((p.row_tile == 256 ? r256 : r128) + gram_us128(B * tri(up(p.C, 128)), dtype)) +
                       (dtype == 1 ? 0.3 * slabs : 0) + 10 + R / 700 + (p.C < R ? 27 : 0) + K_d * 0.35;
-  p.rounds = pool < full && K_d <= kMaxPoolPicks ? (full > 1500 ? 3 : 2) : 0;
+  p.rounds = pool < full && K_d <= kMaxPoolPicks && d <= kNormGapMaxD ? (full > 1500 ? 3 : 2) : 0;
   if (TREVS_PICK_ROUNDS >= 0 && K_d <= kMaxPoolPicks) p.rounds = TREVS_PICK_ROUNDS;
   if (p.C >= R) p.rounds = std::min(p.rounds, 1);
   return p;
@@ -794,7 +795,8 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
     g.ldg = p.ldc;
     g.mask = a.mask;
     g.mask_words = p.mask_words;
-    g.dist = a.cand_dist;
+    g.nearest = a.cand_cos;
+    g.margin = kMaskMargin * a.gap;
     if ((err = launch_gram_pool(g, dtype, s)) != hipSuccess) return err;
     hipLaunchKernelGGL(pool_pick_kernel, dim3(a.B), dim3(kSelThreads), 0, s, a);
   }

@@ -114,6 +114,53 @@ def test_tokens_without_a_distance(N, d, K, k_div, dtype, huge):
         assert np.array_equal(picks[b][n:], left[:k_div - n]), b
 
 
+@pytest.mark.parametrize("d", [4096, 16384])
+def test_picks_do_not_depend_on_nearer_tokens(d):
+    """fp32 rows of equal magnitudes, whose sums of squares collect rounding errors
+    of one sign: the relevance pass's norms and those of the Gram matrix differ
+    most here (about 1.5e-5 and 6e-5 of the norm).  Thousands of tokens nearer to the
+    pivot than the picks must not change the picks, whatever their norms decide
+    about the pool.  Distances are 0.1 and a few 1e-5 steps, set by one extra
+    coordinate; magnitudes of a power of two have exact norms (the pivot, the
+    nearer tokens and some others)."""
+    rng = np.random.default_rng(d)
+    m = d - 4
+    sign = rng.choice([-1.0, 1.0], m)
+    flips = m // 20
+
+    def row(c, y):  # at distance 0.1 + y
+        s = sign.copy()
+        s[rng.permutation(m)[:flips]] *= -1.0
+        x = 1.0 - 2.0 * flips / m
+        z = np.zeros(d, dtype=np.float32)
+        z[:m] = np.float32(c) * s
+        z[m] = np.float32(c) * np.sqrt(m * ((x / (x - y)) ** 2 - 1.0))
+        return z
+
+    near, unit = 1e-4, 2.0 ** -7
+    few = [row(unit, near) for _ in range(3)]
+    picked = [row(unit, near + 3e-5 + 1e-7 * i) for i in range(8)]
+    for c in unit * rng.uniform(1.0, 2.0, 16):
+        picked += [row(c, near + y) for y in np.arange(-8e-5, 8e-5, 8e-6)]
+    pivot = np.zeros(d, dtype=np.float32)
+    pivot[:m] = unit * sign
+    small = np.stack([pivot] + picked + few)
+    rest = np.stack([row(unit, near) for _ in range(512)])[np.arange(5000) % 512]
+    order = []
+    for Z, k_div in ((small, len(picked) + 2), (np.concatenate([small, rest]), 256)):
+        N = Z.shape[0]
+        print(f"[picks-norms] d={d} N={N} K_d={k_div}", flush=True)
+        cls = torch.zeros((1, 1, N))
+        cls[0, 0, 0] = 8.0
+        call = trevs.Prellm(cls.cuda(), torch.from_numpy(Z)[None].cuda(), torch.ones((1, 1, d)).cuda(),
+                            k_keep=k_div + 1, k_div=k_div, textual_ratio=0.0, ratio_mode="budget")
+        call()
+        order.append(call.div_idx.cpu().numpy()[0])
+    n = int(np.argmax(order[0] > len(picked)))  # up to the first of the nearer tokens
+    assert 8 < n < 250, n
+    assert np.array_equal(order[0][:n], order[1][:n]), (order[0][:n], order[1][:n])
+
+
 @pytest.mark.parametrize("d,dtype", [(1032, "bf16"), (1024, "bf16"), (1028, "f32")])
 def test_relevance_text_lengths_at_block_edges(d, dtype):
     """Question lengths around the 32-row text blocks (the blocks past the last
