@@ -104,14 +104,17 @@ __host__ __device__ constexpr int gram_grid(int per_b, int B) {
 // token of one list (a.cols) the maximum over another (a.rows), so that the
 // products themselves are never written; row tiles meet in integer atomics, one
 // for each column of a tile (a partial maximum for each row tile had to be read back
-// by the one workgroup that selects the pool).
-enum { kGramFull = 0, kGramPool = 1, kGramMax = 2 };
+// by the one workgroup that selects the pool).  kGramNext: the same over the last
+// round's picks only, as distances; the columns' norms are formed on the way,
+// each wave multiplying 32 columns by themselves (a quarter more multiplies,
+// in place of a launch that is empty in most calls).
+enum { kGramFull = 0, kGramPool = 1, kGramMax = 2, kGramNext = 3 };
 
 __device__ __forceinline__ bool gram_done(const GramArgs& a, int b) {
   return a.ctrl && a.ctrl[b * kPickCtrl + kCtrlPicks] >= a.K_d;
 }
 
-// kGramMax: workgroup -> (sample, row tile, column tile), false for a padding
+// kGramMax, kGramNext: workgroup -> (sample, row tile, column tile), false for a padding
 // workgroup.  Tiles are walked in groups of four column tiles, so that the
 // workgroups of one XCD share about as many rows as columns in its L2; with
 // 64 tiles or more a sample's are striped over the XCDs as above.
@@ -133,12 +136,13 @@ __device__ __forceinline__ bool gram_list_work(const GramArgs& a, int w, int& b,
   return true;
 }
 
-// kGramMax: the rows of this launch for sample b: all of a.rows, or the picks
-// of the last round.
+// The listed rows of this launch for sample b: all of a.rows, or the picks of
+// the last round.
+template <int MODE>
 __device__ __forceinline__ const int32_t* gram_list_rows(const GramArgs& a, int b, int& count) {
   const int32_t* rows = a.rows + (size_t)b * a.n_rows;
   count = a.n_rows;
-  if (a.by_round) {
+  if (MODE == kGramNext) {
     const int begin = a.ctrl[b * kPickCtrl + kCtrlRound];
     count = a.ctrl[b * kPickCtrl + kCtrlPicks] - begin;
     rows += begin;
@@ -147,28 +151,26 @@ __device__ __forceinline__ const int32_t* gram_list_rows(const GramArgs& a, int 
 }
 
 // kGramMax output of a tile of T x TC products held as MB x NB blocks by 2 x 2
-// waves.  All rows: max G_ij / ||z_j||, from which the distance follows as
-// 1 - max / ||z_i||.  By round: minus the least distance, formed per product as
-// the picks form it.  izr: the rows' inverse norms (LDS); red: 2 TC floats of LDS
-// that nothing reads any more.
-template <int T, int TC, int MB, int NB>
+// waves: max G_ij / ||z_j||, from which the distance follows as 1 - max / ||z_i||.
+// kGramNext: minus the least distance, formed per product as the picks form it.
+// izr, izc: the rows' and columns' inverse norms (LDS; the latter for kGramNext);
+// red: 2 TC floats of LDS that nothing reads any more.
+template <int MODE, int T, int TC, int MB, int NB>
 __device__ __forceinline__ void gram_max_store(const GramArgs& a, const f32x16 (&acc)[MB][NB], const float* izr,
-                                               float* red, int b, int tc, int wj, int wi) {
+                                               const float* izc, float* red, int b, int tc, int wj, int wi) {
   const int tid = threadIdx.x, half = (tid >> 5) & 1, col = tid & 31;
-  const int32_t* cols = a.cols + (size_t)b * a.n_cols;
   float mx[NB];
 #pragma unroll
   for (int n = 0; n < NB; ++n) {
     mx[n] = -INFINITY;
-    const int c = min(tc * TC + wi * (TC / 2) + n * 32 + col, a.n_cols - 1);
-    const float izc = a.by_round ? a.inv_norm[(size_t)b * a.N + cols[c]] : 0.f;
+    const float zc = MODE == kGramNext ? izc[wi * (TC / 2) + n * 32 + col] : 0.f;
 #pragma unroll
     for (int m = 0; m < MB; ++m)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float iz = izr[wj * (T / 2) + m * 32 + mfma_row(r, half)];
         const float g = acc[m][n][r];
-        mx[n] = fmaxf(mx[n], a.by_round ? fmaf(g * izc, iz, -1.f) : g * iz);
+        mx[n] = fmaxf(mx[n], MODE == kGramNext ? fmaf(g * zc, iz, -1.f) : g * iz);
       }
     mx[n] = fmaxf(mx[n], __shfl_xor(mx[n], 32, 64));
   }
@@ -195,22 +197,24 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int nT = a.n_tiles;
+  constexpr bool LISTS = MODE == kGramMax || MODE == kGramNext;
   int b, t, tj, ti;
   // (every return below is the whole workgroup's: no barrier has run)
-  if (MODE == kGramMax) {
+  if (LISTS) {
     if (!gram_list_work(a, w, b, tj, ti)) return;
   } else {
     if (!gram_work(w, gram_tiles(nT), a.B, b, t)) return;
   }
   if (gram_done(a, b)) return;
-  if (MODE != kGramMax) gram_tile_of(t, nT, tj, ti);
+  if (!LISTS) gram_tile_of(t, nT, tj, ti);
   const int rb = a.row_bytes;
   int nj = a.N, ni = a.N;  // tokens along the rows and columns
   const int32_t *rows = nullptr, *cols = nullptr;
-  __shared__ float izr[MODE == kGramFull ? 1 : T], izc[MODE == kGramPool ? T : 1], xr[MODE == kGramPool ? T : 1],
+  bool none = false;
+  __shared__ float izr[MODE == kGramFull ? 1 : T], izc[MODE == kGramPool || MODE == kGramNext ? T : 1], xr[MODE == kGramPool ? T : 1],
       xc[MODE == kGramPool ? T : 1];
   if (MODE != kGramFull) {
-    rows = cols = gram_list_rows(a, b, nj);
+    rows = cols = gram_list_rows<MODE>(a, b, nj);
     ni = nj;
     if (MODE == kGramPool) {  // nothing is nearer to tokens past the list, nor to selected ones (infinity)
       const int i = (tid < T ? tj * T : ti * T - T) + tid, ic = min(i, nj - 1);
@@ -218,9 +222,14 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
       (tid < T ? izr : izc)[tid & (T - 1)] = a.inv_norm[(size_t)b * a.N + rows[ic]];
       (tid < T ? xr : xc)[tid & (T - 1)] = i < nj ? x * (x > 0.f ? 1.f - a.margin : 1.f + a.margin) : INFINITY;
     }
-    if (MODE == kGramMax) {
-      if (tj * T >= nj) return;
+    if (LISTS) {
       cols = a.cols + (size_t)b * a.n_cols;
+      if (MODE == kGramNext && nj == 0) {  // a round without picks: the norms alone, with a column for a row
+        none = true;
+        rows = cols;
+        nj = 1;
+      }
+      if (tj * T >= nj) return;
       ni = a.n_cols;
       if (tid < T) izr[tid] = a.inv_norm[(size_t)b * a.N + rows[min(tj * T + tid, nj - 1)]];
     }
@@ -273,6 +282,9 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
     for (int n = 0; n < 2; ++n)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
+  f32x16 self;  // kGramNext: columns wave * 32.. by themselves
+#pragma unroll
+  for (int r = 0; r < 16; ++r) self[r] = 0.f;
   // k-step q: half h holds chunk 4h + q, or 2q + h in natural order.  The
   // rows a lane reads (32 apart) share the swizzle.
   const bool natural = MODE != kGramFull && a.natural;
@@ -293,6 +305,10 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
     for (int m = 0; m < 2; ++m)
 #pragma unroll
       for (int n = 0; n < 2; ++n) acc[m][n] = mfma_frag(fa[m], fb[n], acc[m][n], In{});
+    if constexpr (MODE == kGramNext) {
+      frag(st + SLAB, wave * 32, fa[0]);
+      self = mfma_frag(fa[0], fa[0], self, In{});
+    }
   };
   // stage 0's loads go out first: loads complete in order, so the first
   // store then waits only for them, not for stage 1's as well
@@ -313,9 +329,18 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
       if (s < n_slabs) compute(st);
     }
   }
-  if constexpr (MODE == kGramMax) {
+  if constexpr (MODE == kGramNext) {
+    const float iz = 1.f / fmaxf(sqrtf(fmaxf(mfma_diag(self, half, col), 0.f)), 1e-12f);
+    if (half == 0) izc[wave * 32 + col] = iz;
+    // (picked tokens have theirs, which other workgroups may be reading)
+    const int c = ti * T + wave * 32 + col;
+    if (half == 0 && tj == 0 && c < ni && a.near_pick[(size_t)b * a.N + cols[c]] != -INFINITY)
+      a.inv_norm[(size_t)b * a.N + cols[c]] = iz;
+    if (none) return;  // uniform
+  }
+  if constexpr (LISTS) {
     __syncthreads();  // the operand slabs are no longer read
-    gram_max_store<T, T, 2, 2>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
+    gram_max_store<MODE, T, T, 2, 2>(a, acc, izr, izc, reinterpret_cast<float*>(lds), b, ti, wj, wi);
     return;
   }
   // output: register r of block (m, n) is row wj*64 + m*32 + mfma_row(r),
@@ -492,8 +517,7 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   uint32_t offA[VPT], offB[VPB];
   if constexpr (MODE == kGramMax) {
     int nj;
-    const int32_t* rows = gram_list_rows(a, b, nj);
-    if (tj * T >= nj) return;
+    const int32_t* rows = gram_list_rows<MODE>(a, b, nj);
     const int32_t* cols = a.cols + (size_t)b * a.n_cols;
     if (tid < T) izr[tid] = a.inv_norm[(size_t)b * N + rows[min(tj * T + tid, nj - 1)]];
 #pragma unroll
@@ -633,7 +657,7 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
     }
   }
   if constexpr (MODE == kGramMax) {  // (the loop ended on a barrier)
-    gram_max_store<T, TC, 4, NB>(a, acc, izr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
+    gram_max_store<MODE, T, TC, 4, NB>(a, acc, izr, nullptr, reinterpret_cast<float*>(lds), b, ti, wj, wi);
     return;
   }
   if constexpr (MODE != kGramMax) {
@@ -721,9 +745,10 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
 // themselves in the k order of the Gram matrix, so that a round's distances are
 // those of the Gram matrix.  One wave per 32 tokens, operands straight from
 // memory; a ring of slabs keeps 48 loads in flight (with 16 issued and awaited
-// together, 480 of 2,880 tokens x 16 took 30 us instead of 15).  fp32 keeps the
-// norms of the relevance pass, which are sums in fp32 as well: the multiplies
-// alone would take 55 us here.
+// together, 480 of 2,880 tokens x 16 took 30 us instead of 15).  fp32 pivots keep
+// the norms of the relevance pass, which are sums in fp32 as well (near-ties can
+// swap against those of the full matrix): the multiplies alone would take 55 us
+// here.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void gram_norms_kernel(GramArgs a) {
   const int lane = threadIdx.x, half = lane >> 5, col = lane & 31;
@@ -764,7 +789,7 @@ __global__ __launch_bounds__(64) void gram_norms_kernel(GramArgs a) {
 // ---------------------------------------------------------------- kernels
 // One tile per workgroup.
 template <class In, int MODE>
-__global__ __launch_bounds__(kGramThreads) void gram_kernel(GramArgs a) {
+__global__ __launch_bounds__(kGramThreads, MODE == kGramNext ? 2 : 1) void gram_kernel(GramArgs a) {
   gram_tile<In, MODE>(a, blockIdx.x);
 }
 template <int MODE, int TC = 256>
@@ -858,6 +883,19 @@ hipError_t launch_gram_max(const GramArgs& g0, int tile, int ctile, int dtype, h
     hipLaunchKernelGGL((gram_kernel<BF16, kGramMax>), grid, dim3(kGramThreads), 0, s, g);
   else
     hipLaunchKernelGGL((gram_kernel<F32, kGramMax>), grid, dim3(kGramThreads), 0, s, g);
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_next(const GramArgs& g0, int dtype, hipStream_t s) {
+  GramArgs g = g0;
+  g.natural = gram256_ok(dtype, g.N, g.row_bytes);
+  g.n_rtiles = (g.n_rows + kGramTile - 1) / kGramTile;
+  g.n_ctiles = (g.n_cols + kGramTile - 1) / kGramTile;
+  const dim3 grid(gram_grid(g.n_rtiles * g.n_ctiles, g.B));
+  if (dtype == 1)
+    hipLaunchKernelGGL((gram_kernel<BF16, kGramNext>), grid, dim3(kGramThreads), 0, s, g);
+  else
+    hipLaunchKernelGGL((gram_kernel<F32, kGramNext>), grid, dim3(kGramThreads), 0, s, g);
   return hipGetLastError();
 }
 

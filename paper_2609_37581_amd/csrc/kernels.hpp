@@ -155,8 +155,8 @@ struct GramArgs {
   int n_rows, n_cols;
   int n_rtiles, n_ctiles;
   bool natural;              // k order of the 256-row tiles (set by the launchers)
-  bool by_round;             // the rows are the last round's picks, not all of them
   float* inv_norm;           // [B,N] 1 / max(||z_i||, 1e-12); set from G by launch_gram_full
+  const float* near_pick;    // [B,N] -inf: picked (launch_gram_next)
   uint32_t* mx;              // [B,n_cols] maxima, as keys (f2key), over 0 or what is there
   // pool: bit i of row j of mask [B,n_rows,mask_words] is set where token j may
   // bring token i nearer: its cosine to i is above that of the nearest selected
@@ -166,8 +166,9 @@ struct GramArgs {
   const float* nearest;
   float margin;
 };
-// A token's inverse norm as the relevance pass forms it is within this share of
-// the one from the Gram diagonal.  A sum of positive terms that pass n
+// The first round knows most tokens' norms from the relevance pass only.  Such
+// an inverse norm is within this share of
+// the one from the Gram diagonal, which the picks use.  A sum of positive terms that pass n
 // fp32 roundings each is within n 2^-24 of the exact one: at most d + 1 on the
 // diagonal (a multiply of n products rounds at most n times, an fp32 product once
 // more), d / 8 + 56 in the relevance pass (chunks of 16 bytes, one half-row a lane,
@@ -179,10 +180,12 @@ struct GramArgs {
 // the pool, at most `bound` far by the relevance pass's norms, is at most
 // bound + e |1 - bound| far by the Gram matrix's.  And pick j brings token i
 // nearer only if their cosine c, off by 2 e |c|, is above i's, off by e |x|: if
-// c > x - 3 e |x| / (1 - 2 e) by the relevance pass's norms.
+// c > x - 3 e |x| / (1 - 2 e) by the relevance pass's norms.  Later rounds have
+// every norm from the diagonal: only the order of a cosine's factors differs.
 inline float norm_gap(int d) { return (0.6f * d + 64.f) * 5.9604645e-8f; }
 constexpr int kNormGapMaxD = 1 << 18;  // a gap of 0.01
 constexpr float kMaskMargin = 3.1f;    // 3 / (1 - 2 e)
+constexpr float kCosRounding = 4 * 5.9604645e-8f;
 bool gram256_ok(int dtype, int N, int row_bytes);  // 256-row tiles can be used
 // G of all N tokens; with ctrl, of the samples that are not finished.
 hipError_t launch_gram_full(const GramArgs& g, int dtype, hipStream_t s);
@@ -190,6 +193,9 @@ hipError_t launch_gram_full(const GramArgs& g, int dtype, hipStream_t s);
 hipError_t launch_gram_pool(const GramArgs& g, int dtype, hipStream_t s);
 // Maxima, by tiles of 128 x 128, or, where gram256_ok, 256 x 256 or 256 x 192.
 hipError_t launch_gram_max(const GramArgs& g, int rtile, int ctile, int dtype, hipStream_t s);
+// Maxima over the last round's picks (of a.rows), as minus the least distance;
+// inv_norm of the other columns, as launch_gram_full would set it.
+hipError_t launch_gram_next(const GramArgs& g, int dtype, hipStream_t s);
 // inv_norm of the listed bf16 tokens (rows), as launch_gram_full would set it.
 hipError_t launch_gram_norms(const GramArgs& g, hipStream_t s);
 
@@ -198,12 +204,12 @@ struct PickPlan {
   int rounds;                // pool rounds before the full Gram matrix (0: none)
   int C, ldc;                // pool size, row stride of its Gram matrix
   int mask_words;            // 32-bit words of a row of its mask, a multiple of 4
-  int row_tile, col_tile;    // tile of the first round's distances
+  int row_tile, col_tile;    // tile of the first round's distances (later: 128 x 128)
   int ldg;                   // row stride of the full Gram matrix
   int n_psplit;              // pivot splits of the initial distances over the full Gram matrix
   size_t gram_floats(int N) const;  // floats of a sample's Gram matrix, full or of the pool
 };
-constexpr int kRoundTile = 128;  // row tile of the later rounds' distances
+constexpr int kRoundTile = 128;  // row tile of the products over pools and picks
 PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes);
 struct PickArgs {
   PickPlan p;
@@ -222,7 +228,7 @@ struct PickArgs {
   int32_t* cand;             // [B,C] pool tokens, ascending
   float* cand_piv;           // [B,C] their near_piv,
   float* cand_pick;          // [B,C] near_pick
-  float* cand_cos;           // [B,C] and cosine to the nearest, from the relevance pass's norms
+  float* cand_cos;           // [B,C] and cosine to the nearest
   uint32_t* mask;            // [B,C,mask_words]
   int32_t* picks;            // [B,K_d]
   int32_t* kept_idx;         // [B,K_r+K_d] ascending

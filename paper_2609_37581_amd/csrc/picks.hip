@@ -77,8 +77,9 @@ __global__ __launch_bounds__(kFpsInitThreads) void fps_init_kernel(PickArgs a) {
 // sample's other tokens (rest) up to date with the maxima that the list
 // products left (round 0: over the pivots; later: over the last round's
 // picks, as minus the least distance), and keeps the C farthest, in index
-// order.  The distances here are formed with the norms of the relevance pass,
-// which every token has; the C-th largest of them is the bound (see norm_gap).
+// order.  The distances of round 0 are formed with the norms of the relevance
+// pass, which every token has, later ones with those of the Gram diagonal; the
+// C-th largest is the bound (see norm_gap).
 // ---------------------------------------------------------------------------
 template <int E>
 __global__ __launch_bounds__(kSelThreads) void pool_select_kernel(PickArgs a, int round) {
@@ -350,7 +351,7 @@ __device__ __forceinline__ int batch_picks(int m, int limit, uint32_t out, const
 constexpr int kHits = 4096;  // marked (pick, entry) pairs taken at once
 constexpr int kMaxPoolPicks = kMaxPool / 2;
 
-__global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a) {
+__global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, float gap) {
   __shared__ PickShared sh;
   __shared__ uint32_t key[kMaxPool];
   __shared__ float iz[kMaxPool];
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a) {
   const int t0 = ctrl[kCtrlPicks];
   int t = t0;
   const float bound = __int_as_float(ctrl[kCtrlBound]);
-  const uint32_t floor_key = bound > -INFINITY ? f2key(bound + a.gap * fabsf(1.f - bound)) : f2key(-INFINITY);
+  const uint32_t floor_key = bound > -INFINITY ? f2key(bound + gap * fabsf(1.f - bound)) : f2key(-INFINITY);
   const int32_t* cand = a.cand + (size_t)b * C;
   const float* G = a.G + (size_t)b * C * ldc;
   const u32x4* mask = reinterpret_cast<const u32x4*>(a.mask) + (size_t)b * C * mw4;
@@ -775,13 +776,13 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
     g.ctrl = a.ctrl;
     g.rows = round ? a.picks : a.pivots;
     g.n_rows = round ? a.K_d : a.K_r;
-    g.by_round = round > 0;
     g.cols = a.rest;
     g.n_cols = a.R;
+    g.near_pick = a.near_pick;
     if (round == 0 && dtype == 1 && (err = launch_gram_norms(g, s)) != hipSuccess) return err;
-    if ((err = launch_gram_max(g, round ? kRoundTile : p.row_tile, round ? kRoundTile : p.col_tile, dtype, s)) !=
-        hipSuccess)
-      return err;
+    err = round ? launch_gram_next(g, dtype, s) : launch_gram_max(g, p.row_tile, p.col_tile, dtype, s);
+    if (err != hipSuccess) return err;
+    const float gap = round ? 0.f : a.gap;
 #define CALL(E_) \
   case E_: hipLaunchKernelGGL(pool_select_kernel<E_>, dim3(a.B), dim3(kSelThreads), 0, s, a, round); break
     switch (select_e(a.R)) {
@@ -791,14 +792,13 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
 #undef CALL
     g.rows = a.cand;
     g.n_rows = p.C;
-    g.by_round = false;
     g.ldg = p.ldc;
     g.mask = a.mask;
     g.mask_words = p.mask_words;
     g.nearest = a.cand_cos;
-    g.margin = kMaskMargin * a.gap;
+    g.margin = kMaskMargin * gap + kCosRounding;
     if ((err = launch_gram_pool(g, dtype, s)) != hipSuccess) return err;
-    hipLaunchKernelGGL(pool_pick_kernel, dim3(a.B), dim3(kSelThreads), 0, s, a);
+    hipLaunchKernelGGL(pool_pick_kernel, dim3(a.B), dim3(kSelThreads), 0, s, a, gap);
   }
   if (p.rounds > 0 && p.C >= a.R) return hipGetLastError();  // the pool held every token
   g.ldg = p.ldg;
