@@ -274,17 +274,17 @@ struct BatchScale {
   }
 };
 
-// The cut: the most bins of the scale that hold at most kBatch entries with
-// key above `floor_key`.  sh.hist holds zeros.  range: width of the scale, refined
-// here.  each(f) calls f(key, entry) for every entry of the thread.
-template <class Each>
-__device__ __forceinline__ void batch_cut(BatchScale& s, float& range, uint32_t floor_key, Each each, PickShared& sh) {
+// The cut: the most bins of the scale that hold at most kBatch entries that may
+// be picked, ok(key, entry).  sh.hist holds zeros.  range: width of the scale,
+// refined here.  each(f) calls f(key, entry) for every entry of the thread.
+template <class Ok, class Each>
+__device__ __forceinline__ void batch_cut(BatchScale& s, float& range, Ok ok, Each each, PickShared& sh) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   for (int zoom = 0;; ++zoom) {
     s.ties = zoom >= kZooms || !(range > 0.f);
     s.scale = (float)kBins / range;
     each([&](uint32_t key, int c) {
-      if (key > floor_key) {
+      if (ok(key, c)) {
         const int bin = s.bin(key, c);
         if (bin < kBins) atomicAdd(&sh.hist[bin], 1u);
       }
@@ -345,8 +345,11 @@ __device__ __forceinline__ int batch_picks(int m, int limit, uint32_t out, const
 // marked entries (reading whole rows of G, 9 KB for each pick at 37 GB/s a
 // CU, took 12 us of a batch's 32).
 // A pick must also be farther than every token outside the pool: its distance
-// is above the round's bound and what the norms may differ by.  The round ends
-// where that fails; at K_d picks the kept list is written.
+// is above the round's bound and what the norms may differ by.  Where they
+// cannot differ (later rounds, or no cosine at all: zero rows, orthogonal ones),
+// tokens at the bound itself can be picked too, as far as the pool holds them:
+// those outside have higher indices.  The round ends where that fails; at K_d
+// picks the kept list is written.
 // ---------------------------------------------------------------------------
 constexpr int kHits = 4096;  // marked (pick, entry) pairs taken at once
 constexpr int kMaxPoolPicks = kMaxPool / 2;
@@ -366,7 +369,8 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
   const int t0 = ctrl[kCtrlPicks];
   int t = t0;
   const float bound = __int_as_float(ctrl[kCtrlBound]);
-  const uint32_t floor_key = bound > -INFINITY ? f2key(bound + gap * fabsf(1.f - bound)) : f2key(-INFINITY);
+  const float floor = bound > -INFINITY ? bound + gap * fabsf(1.f - bound) : -INFINITY;
+  const uint32_t floor_key = f2key(floor);
   const int32_t* cand = a.cand + (size_t)b * C;
   const float* G = a.G + (size_t)b * C * ldc;
   const u32x4* mask = reinterpret_cast<const u32x4*>(a.mask) + (size_t)b * C * mw4;
@@ -389,22 +393,27 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
     for (int c = tid; c < C; c += kSelThreads) f(key[c], c);
   };
   __syncthreads();
-  for (int c = tid; c < C; c += kSelThreads)
+  int last = 0;  // entries below it may be picked at the floor
+  for (int c = tid; c < C; c += kSelThreads) {
     if (key[c] > inf_key) key[c] = 0u;
+    if (key[c] == floor_key && floor == bound) last = c + 1;
+  }
+  last = (int)block_max_u32((uint32_t)last, sh.red_out);
+  auto ok = [&](uint32_t k, int c) { return k > floor_key || (k == floor_key && c < last); };
   while (t < K_d) {
     uint32_t v = 0u;
-    each([&](uint32_t k, int) { v = max(v, k); });
+    each([&](uint32_t k, int c) { v = ok(k, c) ? max(v, k) : v; });
     if (tid == 0) sh.n_batch = n_hits = 0;
     if (tid < kBins) sh.hist[tid] = 0u;
     s.top = block_max_u32(v, sh.red);
-    if (s.top <= floor_key) break;  // uniform
+    if (s.top == 0u) break;  // uniform
     s.ftop = key2f(s.top);
-    if (range < 0.f) range = s.ftop - bound;
-    batch_cut(s, range, floor_key, each, sh);
+    if (range < 0.f || s.top == floor_key) range = s.ftop - bound;
+    batch_cut(s, range, ok, each, sh);
     // ---- the batch, and the largest key outside it
     uint32_t out = floor_key;
     each([&](uint32_t k, int c) {
-      if (k > floor_key && s.bin(k, c) < s.cut) {
+      if (ok(k, c) && s.bin(k, c) < s.cut) {
         const int at = atomicAdd(&sh.n_batch, 1);
         if (at < kBatch) {
           sh.bkey[at] = k;
@@ -470,7 +479,7 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
             words &= words - 1;
           }
           const int wl = lane < 32 ? lo : hi, c = (w0 + wl) * 32 + (lane & 31);
-          const bool hit = wl >= 0 && ((row[max(w0 + wl, 0)] >> (lane & 31)) & 1u) && key[max(c, 0)] > floor_key;
+          const bool hit = wl >= 0 && ((row[max(w0 + wl, 0)] >> (lane & 31)) & 1u) && key[max(c, 0)] >= floor_key;
           const unsigned long long bal = __ballot(hit);
           if (bal) {
             int base = 0;
@@ -637,7 +646,7 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
     s.top = block_max_u32(v, sh.red);
     if (s.top == 0u) break;  // uniform
     s.ftop = key2f(s.top);
-    batch_cut(s, range, 0u, each, sh);
+    batch_cut(s, range, [](uint32_t k, int) { return k > 0u; }, each, sh);
     uint32_t out = 0u;
 #pragma unroll
     for (int e = 0; e < E; ++e) {

@@ -161,23 +161,26 @@ def test_picks_do_not_depend_on_nearer_tokens(d):
     assert np.array_equal(order[0][:n], order[1][:n]), (order[0][:n], order[1][:n])
 
 
-@pytest.mark.parametrize("N,d,clusters,spread", [(8192, 256, 40, 0.3), (9001, 1032, 8, 0.0), (8192, 1024, 20, 0.0)])
-def test_picks_of_rounds_and_of_the_full_matrix(N, d, clusters, spread):
+@pytest.mark.parametrize("N,d,clusters,spread,zeros", [
+    (8192, 256, 40, 0.3, 0), (9001, 1032, 8, 0.0, 0), (8192, 1024, 20, 0.0, 0),
+    (8192, 256, 30, 0.1, 5000), (20001, 64, 9, 0.0, 9000),  # zero rows: distance 1, more than a pool holds
+])
+def test_picks_of_rounds_and_of_the_full_matrix(N, d, clusters, spread, zeros):
     """Few picks are made in rounds, more than 2048 over the Gram matrix of all
     tokens; the former are the beginning of the latter, bit for bit in bf16, near
     ties included (clusters leave much of them to the second round; those of
     copies of one row leave distances of a rounding error)."""
-    k_piv, size = 576, (N - 606) // clusters
+    k_piv, size = 576, (N - 606 - zeros) // clusters
     rng = np.random.default_rng(N + clusters)
     Z = np.empty((2, N, d), dtype=np.float32)
     cls = torch.zeros((2, 1, N))
     for b in range(2):
-        Z[b], free = clustered(rng, N, d, [(size, spread)] * clusters, 0, 0)
+        Z[b], free = clustered(rng, N, d, [(size, spread)] * clusters, 0, zeros)
         cls[b, 0, torch.from_numpy(free[:k_piv])] = 8.0
     Zt = torch.from_numpy(Z).bfloat16().cuda()
     picks = []
     for k_div in (192, 2100):
-        print(f"[picks-prefix] N={N} d={d} clusters={clusters} spread={spread} K_d={k_div}", flush=True)
+        print(f"[picks-prefix] N={N} d={d} clusters={clusters} spread={spread} zeros={zeros} K_d={k_div}", flush=True)
         call = trevs.Prellm(cls.bfloat16().cuda(), Zt, torch.ones((2, 1, d), dtype=torch.bfloat16, device="cuda"),
                             k_keep=k_piv + k_div, k_div=k_div, textual_ratio=0.0, ratio_mode="budget")
         call()
