@@ -606,9 +606,8 @@ trevs_status trevs_inllm_prune(const trevs_inllm_args* a, void* ws, size_t ws_by
   float* score = a->score_out ? a->score_out : reinterpret_cast<float*>(w + p.score);
 
   StatsArgs ta;
-  ta.q[0] = a->q;
-  ta.k[0] = a->k;
-  ta.n_questions = 1;
+  ta.q = a->q;
+  ta.k = a->k;
   ta.B = a->B;
   ta.S = a->S;
   ta.P = a->P;
@@ -621,32 +620,31 @@ trevs_status trevs_inllm_prune(const trevs_inllm_args* a, void* ws, size_t ws_by
   ta.n_split = p.n_split;
   ta.split_len = p.split_len;
   ta.n_rgroups = p.n_rgroups;
-  ta.part[0] = part;
+  ta.part = part;
   ta.rest_len = p.rest_len;
-  ta.part_rest[0] = part_rest;
+  ta.part_rest = part_rest;
   TREVS_TRY(record(a->events, 0, s));
-  if (!a->row_stats) TREVS_HIP(launch_stats(ta, a->dtype, a->d_head, s));
+  if (!a->row_stats) TREVS_HIP(launch_stats(&ta, 1, a->dtype, a->d_head, s));
   TREVS_TRY(record(a->events, 1, s));
 
   HeadArgs ha;
-  ha.part[0] = part;
-  ha.n_questions = 1;
+  ha.part = part;
   ha.B = a->B;
   ha.H_q = a->H_q;
   ha.T_max = a->T_max;
   ha.T_pad = (int)lse_rows_padded(a->T_max);
   ha.K_in = a->K_in;
   ha.n_split = p.n_split;
-  ha.text_len[0] = a->text_len;
-  ha.lse_rest[0] = a->lse_rest;
-  ha.part_rest[0] = part_rest;
-  ha.lse2[0] = lse2;
-  ha.head_var[0] = head_var;
+  ha.text_len = a->text_len;
+  ha.lse_rest = a->lse_rest;
+  ha.part_rest = part_rest;
+  ha.lse2 = lse2;
+  ha.head_var = head_var;
   TREVS_TRY(record(a->events, 2, s));
   if (a->row_stats)
     TREVS_HIP(launch_heads_given(a->row_stats, ha, s));
   else
-    TREVS_HIP(launch_heads(ha, s));
+    TREVS_HIP(launch_heads(&ha, 1, s));
   TREVS_TRY(record(a->events, 3, s));
 
   ScoreArgs sa;
@@ -747,8 +745,7 @@ trevs_status trevs_text_sensitivity(const trevs_sensitivity_args* a, void* ws, s
   sa.H_q = a->H_q;
   sa.K_in = a->K_in;
   sa.ts = a->ts;
-  StatsArgs ta;
-  ta.n_questions = 2;
+  StatsArgs ta{};
   ta.B = a->B;
   ta.S = a->S;
   ta.P = a->P;
@@ -762,8 +759,7 @@ trevs_status trevs_text_sensitivity(const trevs_sensitivity_args* a, void* ws, s
   ta.split_len = L.sp.split_len;
   ta.n_rgroups = L.sp.n_rgroups;
   ta.rest_len = L.sp.rest_len;
-  HeadArgs ha;
-  ha.n_questions = 2;
+  HeadArgs ha{};
   ha.B = a->B;
   ha.H_q = a->H_q;
   ha.T_max = a->T_max;
@@ -783,25 +779,27 @@ trevs_status trevs_text_sensitivity(const trevs_sensitivity_args* a, void* ws, s
   pa.n_split = n_split;
   pa.split_len = split_len;
   pa.scale_log2e = a->scale * kLog2e;
+  StatsArgs tq[2] = {ta, ta};
+  HeadArgs hq[2] = {ha, ha};
   for (int c = 0; c < 2; ++c) {
-    ta.q[c] = pa.q[c] = a->q[c];
-    ta.k[c] = pa.k[c] = a->k[c];
-    ha.part[c] = ta.part[c] = reinterpret_cast<float4*>(w + L.part[c]);
-    ha.part_rest[c] = ta.part_rest[c] = L.sp.rest_len ? reinterpret_cast<float4*>(w + L.part_rest[c]) : nullptr;
-    ha.text_len[c] = pa.text_len[c] = a->text_len[c];
-    ha.lse_rest[c] = a->lse_rest[c];
-    pa.lse2[c] = ha.lse2[c] = reinterpret_cast<float*>(w + L.lse2[c]);
-    ha.head_var[c] = a->head_var[c] ? a->head_var[c] : reinterpret_cast<float*>(w + L.head_var[c]);
+    tq[c].q = pa.q[c] = a->q[c];
+    tq[c].k = pa.k[c] = a->k[c];
+    hq[c].part = tq[c].part = reinterpret_cast<float4*>(w + L.part[c]);
+    hq[c].part_rest = tq[c].part_rest = L.sp.rest_len ? reinterpret_cast<float4*>(w + L.part_rest[c]) : nullptr;
+    hq[c].text_len = pa.text_len[c] = a->text_len[c];
+    hq[c].lse_rest = a->lse_rest[c];
+    pa.lse2[c] = hq[c].lse2 = reinterpret_cast<float*>(w + L.lse2[c]);
+    hq[c].head_var = a->head_var[c] ? a->head_var[c] : reinterpret_cast<float*>(w + L.head_var[c]);
     sa.profile[c] = pa.profile[c] =
         a->profile[c] ? a->profile[c] : reinterpret_cast<float*>(w + L.profile[c]);
   }
   // both questions in each launch; the second question's event slots (6..11)
   // bracket nothing
   TREVS_TRY(record(a->events, 0, s));
-  TREVS_HIP(launch_stats(ta, a->dtype, a->d_head, s));
+  TREVS_HIP(launch_stats(tq, 2, a->dtype, a->d_head, s));
   TREVS_TRY(record(a->events, 1, s));
   TREVS_TRY(record(a->events, 2, s));
-  TREVS_HIP(launch_heads(ha, s));
+  TREVS_HIP(launch_heads(hq, 2, s));
   TREVS_TRY(record(a->events, 3, s));
   TREVS_TRY(record(a->events, 4, s));
   TREVS_HIP(launch_profile(pa, a->dtype, a->d_head, s));

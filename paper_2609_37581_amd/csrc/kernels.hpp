@@ -81,37 +81,50 @@ struct SelArgs {
 };
 
 // ---------------------------------------------------------------- stage 2
-// The statistics, head and profile passes take the two questions of the text
-// sensitivity in one launch (the last grid dimension); stage 2 has one.  Three
-// launches less, and twice the workgroups of grids that fill the GPU once:
-// 4 x 4096 visual tokens 147.4 -> 130.9 us a call (with the rank correlation),
-// 12 x 72 57.2 -> 36.6.
+// The statistics and head passes of the two questions of the text sensitivity
+// run in one launch (QuestionPair, the last grid dimension), and so does the
+// profile pass.  Three launches less, and twice the workgroups of grids that
+// fill the GPU once: 4 x 4096 visual tokens 147.4 -> 130.9 us a call (with the
+// rank correlation), 12 x 72 57.2 -> 36.6.  Stage 2 has one question and takes
+// its arguments as they are (with a choice between two: 4 x 4096 tokens 70.8 -> 71.1
+// us a call).
 struct StatsArgs {
-  const void* q[2];          // [B,S,H_q,dh]
-  const void* k[2];          // [B,S,H_kv,dh]
-  int n_questions;
+  const void* q;             // [B,S,H_q,dh]
+  const void* k;             // [B,S,H_kv,dh]
   int B, S, P, K_in, T_max, H_q, H_kv, G;
   float scale_log2e;         // scale * log2 e
   int n_split, split_len;    // visual columns per split (multiple of 32)
   int n_rgroups;             // workgroups along the (head-in-group, text row) axis
-  float4* part[2];           // [B,H_q,T_max,n_split]: (max, sum e, sum e^2, -) in log2 units
+  float4* part;              // [B,H_q,T_max,n_split]: (max, sum e, sum e^2, -) in log2 units
   // Causal softmax domain: split s also reduces the non-visual causal keys
   // [s*rest_len, (s+1)*rest_len) of each text row (key j < P is prefix row j,
   // j >= P text row j - P, valid for text row q while j - P <= q).
   int rest_len;              // multiple of 32; 0 for the visual-only domain
-  float4* part_rest[2];      // [B,H_q,T_max,n_split]: as part, over the non-visual keys
+  float4* part_rest;         // [B,H_q,T_max,n_split]: as part, over the non-visual keys
 };
 
 struct HeadArgs {
-  const float4* part[2];
-  int n_questions;
+  const float4* part;
   int B, H_q, T_max, T_pad, K_in, n_split;
-  const int32_t* text_len[2];
-  const float* lse_rest[2];     // [B,H_q,T_max] natural log, or null
-  const float4* part_rest[2];   // [B,H_q,T_max,n_split] non-visual causal statistics, or null
-  float* lse2[2];               // [B,H_q,T_pad] row log-sum-exp in log2 units (T_pad = T_max rounded up to 32)
-  float* head_var[2];           // [B,H_q] u_h
+  const int32_t* text_len;
+  const float* lse_rest;     // [B,H_q,T_max] natural log, or null
+  const float4* part_rest;   // [B,H_q,T_max,n_split] non-visual causal statistics, or null
+  float* lse2;               // [B,H_q,T_pad] row log-sum-exp in log2 units (T_pad = T_max rounded up to 32)
+  float* head_var;           // [B,H_q] u_h
 };
+
+template <class A>
+struct QuestionPair {
+  A of[2];
+};
+template <class A>
+__device__ __forceinline__ const A& question(const A& a, int) {
+  return a;
+}
+template <class A>
+__device__ __forceinline__ const A& question(const QuestionPair<A>& a, int c) {
+  return a.of[c];
+}
 
 struct ScoreArgs {
   const void* q;
@@ -312,8 +325,9 @@ hipError_t launch_budget_select(const SelArgs& a, int B, hipStream_t s);
 // its min/max reduction).
 hipError_t launch_topk(const float* scores, int B, int N, int K, int32_t* out, hipStream_t s,
                        bool nonneg = false);
-hipError_t launch_stats(const StatsArgs& a, int dtype, int dh, hipStream_t s);
-hipError_t launch_heads(const HeadArgs& a, hipStream_t s);
+// (n questions of the same sizes, one or two)
+hipError_t launch_stats(const StatsArgs* a, int n, int dtype, int dh, hipStream_t s);
+hipError_t launch_heads(const HeadArgs* a, int n, hipStream_t s);
 // u_h and the row log-sum-exps from the caller's per-row statistics
 // [B,H_q,T_max,3] = (log-sum-exp, sum A, sum A^2) instead of the
 // statistics pass.

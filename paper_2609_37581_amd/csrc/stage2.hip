@@ -40,8 +40,9 @@ constexpr int stats_ring(int vectors_per_tile) { return vectors_per_tile >= 4 ? 
 // 45.5 -> 43.3 us; wider rows hold too many Q registers for four)
 template <class In, int DH>
 constexpr int stats_min_waves(int NW) { return NW == 2 && DH * In::kBytes <= 256 ? 4 : 1; }
-template <class In, int DH, int NW, bool CAUSAL>
-__global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_stats_kernel(StatsArgs a) {
+template <class In, int DH, int NW, bool CAUSAL, class Args>
+__global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_stats_kernel(Args args) {
+  const StatsArgs& a = question(args, blockIdx.y);
   constexpr int ROWB = DH * In::kBytes;
   constexpr int HALFB = ROWB / 2;
   constexpr int NF = HALFB / 64;
@@ -50,8 +51,6 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   constexpr int TV = 32 * ROWB / 16;           // 16-byte vectors of one key tile
   constexpr int TVT = (TV + NT - 1) / NT;
   __shared__ __attribute__((aligned(16))) uint8_t klds[2][32 * LROW];
-  // (both pointers load with the other arguments; an index would wait for them)
-  const bool second = blockIdx.y != 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
@@ -67,7 +66,7 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
 
   u32x4 qf[NF][4];
   {
-    const uint8_t* qp = reinterpret_cast<const uint8_t*>((second ? a.q[1] : a.q[0])) +
+    const uint8_t* qp = reinterpret_cast<const uint8_t*>(a.q) +
                         (((size_t)b * a.S + a.P + a.K_in + q) * a.H_q + h) * ROWB + half * HALFB;
 #pragma unroll
     for (int f = 0; f < NF; ++f)
@@ -83,7 +82,7 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   const int j_end = CAUSAL ? min(a.P + a.T_max, j_begin + a.rest_len) : 0;
   const int n_tiles = nv + (j_end - j_begin + 31) / 32;
   const int climit = a.P + q;  // last non-visual key index this lane's row attends
-  const uint8_t* kbase = reinterpret_cast<const uint8_t*>((second ? a.k[1] : a.k[0])) +
+  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(a.k) +
                          (size_t)b * a.S * a.H_kv * ROWB + (size_t)g * ROWB;
   const size_t kstride = (size_t)a.H_kv * ROWB;
   // tile t into registers: rows past a range (and tiles past the last) re-read
@@ -203,10 +202,10 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
   };
   const size_t slot = (((size_t)b * a.H_q + h) * a.T_max + q) * a.n_split + split;
   const float4 vs = merge_halves(m, l, l2);
-  if (half == 0 && rvalid) (second ? a.part[1] : a.part[0])[slot] = vs;
+  if (half == 0 && rvalid) a.part[slot] = vs;
   if constexpr (CAUSAL) {
     const float4 rs = merge_halves(mr, lr, l2r);
-    if (half == 0 && rvalid) (second ? a.part_rest[1] : a.part_rest[0])[slot] = rs;
+    if (half == 0 && rvalid) a.part_rest[slot] = rs;
   }
 }
 
@@ -219,23 +218,18 @@ __global__ __launch_bounds__(64 * NW, (stats_min_waves<In, DH>(NW))) void t2v_st
 // ---------------------------------------------------------------------------
 constexpr int kHeadThreads = 128;
 
-__global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
+template <class Args>
+__global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(Args args) {
+  const HeadArgs& a = question(args, blockIdx.z);
   __shared__ float red[kHeadThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = blockIdx.x, b = blockIdx.y;
-  const bool second = blockIdx.z != 0;
-  const int32_t* const q_text_len = second ? a.text_len[1] : a.text_len[0];
-  const float4* const q_part = second ? a.part[1] : a.part[0];
-  const float4* const q_part_rest = second ? a.part_rest[1] : a.part_rest[0];
-  const float* const q_lse_rest = second ? a.lse_rest[1] : a.lse_rest[0];
-  float* const q_lse2 = second ? a.lse2[1] : a.lse2[0];
-  float* const q_head_var = second ? a.head_var[1] : a.head_var[0];
-  const int Tb = text_rows(q_text_len, b, a.T_max);
+  const int Tb = text_rows(a.text_len, b, a.T_max);
   const float invK = 1.f / (float)a.K_in;
   float vs = 0.f;
   for (int q = tid; q < a.T_max; q += kHeadThreads) {
     const size_t row = ((size_t)b * a.H_q + h) * a.T_max + q;
-    const float4* pp = q_part + row * a.n_split;
+    const float4* pp = a.part + row * a.n_split;
     const size_t lrow = ((size_t)b * a.H_q + h) * a.T_pad + q;
     // the splits' partials 8 at a time, every load issued before the merge
     float m = -INFINITY, l = 0.f, l2 = 0.f;
@@ -256,10 +250,10 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
       }
     }
     float lse2 = m + log2f(l);
-    if (q_lse_rest || q_part_rest) {
+    if (a.lse_rest || a.part_rest) {
       float r2;
-      if (q_part_rest) {
-        const float4* pr = q_part_rest + row * a.n_split;
+      if (a.part_rest) {
+        const float4* pr = a.part_rest + row * a.n_split;
         float mr = -INFINITY, lr = 0.f;
         for (int s0 = 0; s0 < a.n_split; s0 += 8) {
           float4 pv[8];
@@ -277,12 +271,12 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
         }
         r2 = mr + log2f(lr);
       } else {
-        r2 = q_lse_rest[row] * kLog2e;
+        r2 = a.lse_rest[row] * kLog2e;
       }
       const float mx = fmaxf(lse2, r2);
       lse2 = mx + log2f(fast_exp2(lse2 - mx) + fast_exp2(r2 - mx));
     }
-    q_lse2[lrow] = lse2;
+    a.lse2[lrow] = lse2;
     if (q < Tb) {
       const float f = fast_exp2(m - lse2);
       vs += f * f * (l2 - l * l * invK) * invK;
@@ -294,7 +288,7 @@ __global__ __launch_bounds__(kHeadThreads) void t2v_heads_kernel(HeadArgs a) {
   if (tid == 0) {
     float t = 0.f;
     for (int w = 0; w < kHeadThreads / 64; ++w) t += red[w];
-    q_head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
+    a.head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
   }
 }
 
@@ -309,17 +303,13 @@ __global__ __launch_bounds__(kHeadThreads) void heads_given_kernel(const float* 
   __shared__ float red[kHeadThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = blockIdx.x, b = blockIdx.y;
-  const bool second = blockIdx.z != 0;
-  const int32_t* const q_text_len = second ? a.text_len[1] : a.text_len[0];
-  float* const q_lse2 = second ? a.lse2[1] : a.lse2[0];
-  float* const q_head_var = second ? a.head_var[1] : a.head_var[0];
-  const int Tb = text_rows(q_text_len, b, a.T_max);
+  const int Tb = text_rows(a.text_len, b, a.T_max);
   const float invK = 1.f / (float)a.K_in;
   float vs = 0.f;
   for (int q = tid; q < a.T_max; q += kHeadThreads) {
     const size_t row = ((size_t)b * a.H_q + h) * a.T_max + q;
     const float lse = row_stats[3 * row], s1 = row_stats[3 * row + 1], s2 = row_stats[3 * row + 2];
-    q_lse2[((size_t)b * a.H_q + h) * a.T_pad + q] = lse * kLog2e;
+    a.lse2[((size_t)b * a.H_q + h) * a.T_pad + q] = lse * kLog2e;
     if (q < Tb) {
       const float mean = s1 * invK;
       vs += s2 * invK - mean * mean;
@@ -331,7 +321,7 @@ __global__ __launch_bounds__(kHeadThreads) void heads_given_kernel(const float* 
   if (tid == 0) {
     float t = 0.f;
     for (int w = 0; w < kHeadThreads / 64; ++w) t += red[w];
-    q_head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
+    a.head_var[(size_t)b * a.H_q + h] = t / (float)Tb;
   }
 }
 
@@ -668,45 +658,58 @@ int stats_waves(int G, int T_max) {
   return nrb >= 8 ? 8 : (nrb >= 4 ? 4 : (nrb >= 2 ? 2 : 1));
 }
 
-template <class In, int DH, bool CAUSAL>
-static void launch_stats_c(const StatsArgs& a, hipStream_t s) {
-  const dim3 grid(a.n_split * a.n_rgroups * a.H_kv * a.B, a.n_questions);
+template <class In, int DH, bool CAUSAL, class Args>
+static void launch_stats_n(const StatsArgs& a, const Args& args, int n, hipStream_t s) {
+  const dim3 grid(a.n_split * a.n_rgroups * a.H_kv * a.B, n);
   switch (stats_waves(a.G, a.T_max)) {
-    case 8: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 8, CAUSAL>), grid, dim3(512), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 4, CAUSAL>), grid, dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 2, CAUSAL>), grid, dim3(128), 0, s, a); break;
-    default: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 1, CAUSAL>), grid, dim3(64), 0, s, a); break;
+    case 8: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 8, CAUSAL, Args>), grid, dim3(512), 0, s, args); break;
+    case 4: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 4, CAUSAL, Args>), grid, dim3(256), 0, s, args); break;
+    case 2: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 2, CAUSAL, Args>), grid, dim3(128), 0, s, args); break;
+    default: hipLaunchKernelGGL((t2v_stats_kernel<In, DH, 1, CAUSAL, Args>), grid, dim3(64), 0, s, args); break;
   }
 }
 
-template <class In, int DH>
-static void launch_stats_t(const StatsArgs& a, hipStream_t s) {
-  if (a.rest_len > 0)
-    launch_stats_c<In, DH, true>(a, s);
+template <class In, int DH, bool CAUSAL>
+static void launch_stats_c(const StatsArgs* a, int n, hipStream_t s) {
+  if (n == 2)
+    launch_stats_n<In, DH, CAUSAL>(a[0], QuestionPair<StatsArgs>{{a[0], a[1]}}, 2, s);
   else
-    launch_stats_c<In, DH, false>(a, s);
+    launch_stats_n<In, DH, CAUSAL>(a[0], a[0], 1, s);
+}
+
+template <class In, int DH>
+static void launch_stats_t(const StatsArgs* a, int n, hipStream_t s) {
+  if (a->rest_len > 0)
+    launch_stats_c<In, DH, true>(a, n, s);
+  else
+    launch_stats_c<In, DH, false>(a, n, s);
 }
 
 template <class In>
-static void launch_stats_d(const StatsArgs& a, int dh, hipStream_t s) {
+static void launch_stats_d(const StatsArgs* a, int n, int dh, hipStream_t s) {
   if (dh == 64)
-    launch_stats_t<In, 64>(a, s);
+    launch_stats_t<In, 64>(a, n, s);
   else if (dh == 128)
-    launch_stats_t<In, 128>(a, s);
+    launch_stats_t<In, 128>(a, n, s);
   else
-    launch_stats_t<In, 256>(a, s);
+    launch_stats_t<In, 256>(a, n, s);
 }
 
-hipError_t launch_stats(const StatsArgs& a, int dtype, int dh, hipStream_t s) {
+hipError_t launch_stats(const StatsArgs* a, int n, int dtype, int dh, hipStream_t s) {
   if (dtype == 1)
-    launch_stats_d<BF16>(a, dh, s);
+    launch_stats_d<BF16>(a, n, dh, s);
   else
-    launch_stats_d<F32>(a, dh, s);
+    launch_stats_d<F32>(a, n, dh, s);
   return hipGetLastError();
 }
 
-hipError_t launch_heads(const HeadArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(t2v_heads_kernel, dim3(a.H_q, a.B, a.n_questions), dim3(kHeadThreads), 0, s, a);
+hipError_t launch_heads(const HeadArgs* a, int n, hipStream_t s) {
+  const dim3 grid(a->H_q, a->B, n);
+  if (n == 2)
+    hipLaunchKernelGGL(t2v_heads_kernel<QuestionPair<HeadArgs>>, grid, dim3(kHeadThreads), 0, s,
+                       QuestionPair<HeadArgs>{{a[0], a[1]}});
+  else
+    hipLaunchKernelGGL(t2v_heads_kernel<HeadArgs>, grid, dim3(kHeadThreads), 0, s, a[0]);
   return hipGetLastError();
 }
 
