@@ -1,6 +1,7 @@
 // Stage 1 (pre-LLM) kernels: [CLS] saliency, textual relevance, robust
 // normalisation, fusion and pivot top-K (Sec. 4.1, Eq. (2)-(7)).
 #include <algorithm>
+#include <cfloat>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -170,9 +171,10 @@ __device__ __forceinline__ void tile_stats(const RelArgs& a, int b, int seg0, in
           float vm = m[r];
 #pragma unroll
           for (int u = 0; u < U; ++u) vm = i + u * 64 < a.seg_len ? fmaxf(vm, x[r][u]) : vm;
-          float acc = s[r] * __builtin_amdgcn_exp2f(m[r] - vm);
+          const float mf = fmaxf(vm, -FLT_MAX);  // (masked logits, -inf, add nothing)
+          float acc = s[r] * __builtin_amdgcn_exp2f(m[r] - mf);
 #pragma unroll
-          for (int u = 0; u < U; ++u) acc += i + u * 64 < a.seg_len ? __builtin_amdgcn_exp2f(x[r][u] - vm) : 0.f;
+          for (int u = 0; u < U; ++u) acc += i + u * 64 < a.seg_len ? __builtin_amdgcn_exp2f(x[r][u] - mf) : 0.f;
           s[r] = acc;
           m[r] = vm;
         }

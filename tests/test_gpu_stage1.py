@@ -170,6 +170,19 @@ def test_stage1_text_median_and_mad_zero():
     check(inp, w, g, o)
 
 
+@pytest.mark.parametrize("name,B,N,d", [("llava15-b1-f32", 1, 1201, 4096), ("llava15-b64-bf16", 2, 1201, 4096)])
+def test_stage1_masked_cls_logits(name, B, N, d):
+    """-inf [CLS] logits (masked patches) get no saliency, and the others theirs:
+    the first 512 tokens are masked, which the row statistics inside the relevance
+    launch read eight a lane before they see another one."""
+    w = WORKLOADS[name].with_(B=B, N=N, d=d, M_max=32, K1=300, n_sal=8, n_qm=8, text_len=("fixed",))
+    inp = stage1_inputs(w)
+    inp["cls_logits"][:, :, :512] = -np.inf if w.dtype == "f32" else 0xff80
+    g = run_gpu(inp, w)
+    assert np.all(g["sal"][:, :512] == 0.0)
+    check(inp, w, g, run_oracle(inp, w))
+
+
 def test_stage1_identical_tokens_score_identically():
     """Position independence: tokens with identical inputs get bit-identical
     scores wherever they sit in the tiles."""
