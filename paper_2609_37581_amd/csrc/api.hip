@@ -294,10 +294,11 @@ InllmPlan inllm_plan_of(const trevs_inllm_args* a, bool coarse) {
   return p;
 }
 
-// The finer splits, unless the coarser ones fit the static array of
-// trevs_inllm_prune_noalloc and the finer do not (a call that it can serve is
-// not refused for a faster split), or the finer ones' head sums are so large
-// that the split was given up.
+// The finer splits, but the coarser ones where just one of the two fits the static
+// array of trevs_inllm_prune_noalloc (which so serves the calls whose coarser
+// plan fits, whatever the finer one needs), and where the finer ones' head sums are
+// so large that the split was given up (the coarser split is then the faster
+// plan, though the finer one, without any, may need less memory).
 InllmPlan inllm_plan(const trevs_inllm_args* a) {
   const InllmPlan fine = inllm_plan_of(a, false), coarse = inllm_plan_of(a, true);
   const size_t room = TREVS_NOALLOC_SCRATCH_BYTES;
