@@ -87,9 +87,11 @@ typedef enum trevs_dtype { TREVS_F32 = 0, TREVS_BF16 = 1 } trevs_dtype;
  * selected token is largest (ties to the lower index).  Tokens whose distance
  * is not a number (the squares of a row overflow fp32) follow after all others,
  * in index order.  The workspace has
- * room for the Gram matrix Z Z^T of every sample, which is formed where the
- * picks need all of it (B*N*N floats and some MB beyond the k_div = 0 size,
- * e.g. 4.3 GB at B = 4, N = 16,384; 85 MB at B = 64, N = 576);
+ * room for a Gram matrix of every sample, beyond the k_div = 0 size: of all N
+ * tokens (85 MB at B = 64, N = 576), or, where the picks are made in rounds over
+ * pools of tokens, of those that are no pivots, for what the rounds leave, and
+ * for lists, a few words a token and a bit for each pair of a pool (2.8 GB at
+ * B = 4, N = 16,384, K_r = 3072; 0.37 GB at B = 16, N = 2880, K_r = 480);
  * trevs_prellm_workspace_size includes it, and the call itself allocates
  * nothing.
  * With ratio_mode = TREVS_RATIO_BUDGET the textual ratio is instead the

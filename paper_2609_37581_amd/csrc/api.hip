@@ -144,7 +144,7 @@ PrellmLayout prellm_layout(const trevs_prellm_args* a) {
     take(L.pivots, B * K_r);
     take(L.ctrl, B * kPickCtrl);
     take(L.picks, B * a->k_div);
-    take(L.gram, B * p.gram_floats(a->N));
+    take(L.gram, B * p.gram_floats());
     if (p.rounds == 0) {
       take(L.pick_part, p.n_psplit * B * N);
     } else {

@@ -107,8 +107,9 @@ __host__ __device__ constexpr int gram_grid(int per_b, int B) {
 // by the one workgroup that selects the pool).  kGramNext: the same over the last
 // round's picks only, as distances; the columns' norms are formed on the way,
 // each wave multiplying 32 columns by themselves (a quarter more multiplies,
-// in place of a launch that is empty in most calls).
-enum { kGramFull = 0, kGramPool = 1, kGramMax = 2, kGramNext = 3 };
+// in place of a launch that is empty in most calls).  kGramRest: all pairs of the
+// tokens that are no pivots (a.cols), where the rounds did not suffice.
+enum { kGramFull = 0, kGramPool = 1, kGramMax = 2, kGramNext = 3, kGramRest = 4 };
 
 __device__ __forceinline__ bool gram_done(const GramArgs& a, int b) {
   return a.ctrl && a.ctrl[b * kPickCtrl + kCtrlPicks] >= a.K_d;
@@ -136,10 +137,14 @@ __device__ __forceinline__ bool gram_list_work(const GramArgs& a, int w, int& b,
   return true;
 }
 
-// The listed rows of this launch for sample b: all of a.rows, or the picks of
-// the last round.
+// The listed rows of this launch for sample b: all of a.rows, the picks of
+// the last round, or the columns.
 template <int MODE>
 __device__ __forceinline__ const int32_t* gram_list_rows(const GramArgs& a, int b, int& count) {
+  if (MODE == kGramRest) {
+    count = a.n_cols;
+    return a.cols + (size_t)b * a.n_cols;
+  }
   const int32_t* rows = a.rows + (size_t)b * a.n_rows;
   count = a.n_rows;
   if (MODE == kGramNext) {
@@ -345,7 +350,7 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   }
   // output: register r of block (m, n) is row wj*64 + m*32 + mfma_row(r),
   // column wi*64 + n*32 + col of the tile
-  if (MODE == kGramFull && tj == ti) {  // the diagonal tile holds ||z_i||^2
+  if ((MODE == kGramFull || MODE == kGramRest) && tj == ti) {  // the diagonal tile holds ||z_i||^2
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -355,7 +360,7 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
           const int jl = wj * 64 + m * 32 + mfma_row(r, half), il = wi * 64 + n * 32 + col;
           const int i = ti * T + il;
           if (jl == il && i < N)
-            a.inv_norm[(size_t)b * N + i] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
+            a.inv_norm[(size_t)b * a.N + (MODE == kGramFull ? i : rows[i])] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
         }
   }
   if constexpr (MODE == kGramPool) {
@@ -486,7 +491,11 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   constexpr int LDS_OUT = (PR * TA + T * TB) * 4;
   constexpr int LDS = MODE == kGramMax || LDS_OPS > LDS_OUT ? LDS_OPS : LDS_OUT;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tid = threadIdx.x;
+  // (a workgroup that walks several tiles forms its addresses anew for each: kept
+  // from tile to tile they spilled 75 registers)
+  if (MODE == kGramRest) asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int nT = a.n_tiles;
   int b, t, tj, ti;
@@ -515,11 +524,11 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   // listed tokens: an offset per row (rows past the last re-read it)
   __shared__ float izr[MODE == kGramMax ? T : 1];
   uint32_t offA[VPT], offB[VPB];
-  if constexpr (MODE == kGramMax) {
+  if constexpr (MODE != kGramFull) {
     int nj;
     const int32_t* rows = gram_list_rows<MODE>(a, b, nj);
     const int32_t* cols = a.cols + (size_t)b * a.n_cols;
-    if (tid < T) izr[tid] = a.inv_norm[(size_t)b * N + rows[min(tj * T + tid, nj - 1)]];
+    if (MODE == kGramMax && tid < T) izr[tid] = a.inv_norm[(size_t)b * N + rows[min(tj * T + tid, nj - 1)]];
 #pragma unroll
     for (int k = 0; k < VPT; ++k) offA[k] = (uint32_t)rows[min(tj * T + cr + RSTEP * k, nj - 1)] * rb + cc * 16;
 #pragma unroll
@@ -663,7 +672,8 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   if constexpr (MODE != kGramMax) {
   // register r of block (m, n) is row wj*128 + m*32 + mfma_row(r), column
   // wi*128 + n*32 + col of the tile
-  if (MODE == kGramFull && tj == ti) {  // the diagonal tile holds ||z_i||^2
+  const int n_tok = MODE == kGramRest ? a.n_cols : N;  // rows and columns of G
+  if (tj == ti) {  // the diagonal tile holds ||z_i||^2
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -672,8 +682,8 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
         for (int r = 0; r < 16; ++r) {
           const int jl = wj * 128 + m * 32 + mfma_row(r, half), il = wi * 128 + n * 32 + col;
           const int i = ti * T + il;
-          if (jl == il && i < N)
-            a.inv_norm[(size_t)b * N + i] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
+          if (jl == il && i < n_tok)
+            a.inv_norm[(size_t)b * N + (MODE == kGramRest ? a.cols[(size_t)b * n_tok + i] : i)] = 1.f / fmaxf(sqrtf(fmaxf(acc[m][n][r], 0.f)), 1e-12f);
         }
   }
   // The tile leaves through LDS, 32 rows j at a time, and is stored as
@@ -687,9 +697,9 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
   float* tA = reinterpret_cast<float*>(lds);
   float* tB = tA + PR * TA;
   const int ld = a.ldg;
-  float* gbm = a.G + (size_t)b * N * ld;
+  float* gbm = a.G + (size_t)b * n_tok * ld;
   const bool mirror = tj != ti;
-  const bool fast = (ti + 1) * T <= N && (ld & 3) == 0;  // tj <= ti
+  const bool fast = (ti + 1) * T <= n_tok && (ld & 3) == 0;  // tj <= ti
 #pragma unroll
   for (int p = 0; p < T / PR; ++p) {  // unrolled: the accumulator block m is a constant
     __syncthreads();  // the operand slabs, or the previous pass, are no longer read
@@ -716,7 +726,8 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
       } else {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (j < N && i + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)j * ld + i + u]);
+          if (j < n_tok && i + u < n_tok)
+            __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)j * ld + i + u]);
       }
     }
     if (mirror) {  // G[i, j]: T rows of PR / 4 runs
@@ -732,7 +743,8 @@ __device__ __forceinline__ void gram256_tile(const GramArgs& a, int w) {
         } else {
 #pragma unroll
           for (int u = 0; u < 4; ++u)
-            if (i < N && j + u < N) __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)i * ld + j + u]);
+            if (i < n_tok && j + u < n_tok)
+              __builtin_nontemporal_store(__uint_as_float(v[u]), &gbm[(size_t)i * ld + j + u]);
         }
       }
     }
@@ -797,26 +809,27 @@ __global__ __launch_bounds__(kGram256Threads, 1) void gram256_kernel(GramArgs a)
   gram256_tile<MODE, TC>(a, blockIdx.x);
 }
 
-// The full Gram matrix of the samples that the pool rounds left unfinished,
-// most often none: as many workgroups as are resident at once walk the tiles
-// (8320 workgroups that only find nothing to do take 104 us, these 5 us).
+// The Gram matrix of the tokens that are no pivots, in the samples that the pool
+// rounds left unfinished, most often none: as many workgroups as are resident at
+// once walk the tiles (8320 workgroups that only find nothing to do take 104 us,
+// these 5 us).
 __device__ __forceinline__ bool gram_any_left(const GramArgs& a) {
   bool left = false;
   for (int b = threadIdx.x; b < a.B; b += blockDim.x) left |= !gram_done(a, b);
   return __syncthreads_or(left);
 }
 template <class In>
-__global__ __launch_bounds__(kGramThreads) void gram_left_kernel(GramArgs a, int n_work) {
+__global__ __launch_bounds__(kGramThreads) void gram_rest_kernel(GramArgs a, int n_work) {
   if (!gram_any_left(a)) return;
   for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
-    gram_tile<In, kGramFull>(a, w);
+    gram_tile<In, kGramRest>(a, w);
     __syncthreads();
   }
 }
-__global__ __launch_bounds__(kGram256Threads, 1) void gram256_left_kernel(GramArgs a, int n_work) {
+__global__ __launch_bounds__(kGram256Threads, 1) void gram256_rest_kernel(GramArgs a, int n_work) {
   if (!gram_any_left(a)) return;
   for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
-    gram256_tile<kGramFull>(a, w);
+    gram256_tile<kGramRest>(a, w);
     __syncthreads();
   }
 }
@@ -832,21 +845,29 @@ hipError_t launch_gram_full(const GramArgs& g0, int dtype, hipStream_t s) {
   const int T = big ? 256 : kGramTile;
   g.n_tiles = (g.N + T - 1) / T;
   const int n_work = gram_grid(gram_tiles(g.n_tiles), g.B);
-  if (g.ctrl) {
-    const dim3 grid(std::min(n_work, big ? 256 : 512));
-    if (big)
-      hipLaunchKernelGGL(gram256_left_kernel, grid, dim3(kGram256Threads), 0, s, g, n_work);
-    else if (dtype == 1)
-      hipLaunchKernelGGL(gram_left_kernel<BF16>, grid, dim3(kGramThreads), 0, s, g, n_work);
-    else
-      hipLaunchKernelGGL(gram_left_kernel<F32>, grid, dim3(kGramThreads), 0, s, g, n_work);
-  } else if (big) {
+  if (big)
     hipLaunchKernelGGL(gram256_kernel<kGramFull>, dim3(n_work), dim3(kGram256Threads), 0, s, g);
-  } else if (dtype == 1) {
+  else if (dtype == 1)
     hipLaunchKernelGGL((gram_kernel<BF16, kGramFull>), dim3(n_work), dim3(kGramThreads), 0, s, g);
-  } else {
+  else
     hipLaunchKernelGGL((gram_kernel<F32, kGramFull>), dim3(n_work), dim3(kGramThreads), 0, s, g);
-  }
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_rest(const GramArgs& g0, int dtype, hipStream_t s) {
+  GramArgs g = g0;
+  const bool big = gram256_ok(dtype, g.N, g.row_bytes);  // the tiles, and so the k order, of the full matrix
+  const int T = big ? 256 : kGramTile;
+  g.natural = false;
+  g.n_tiles = (g.n_cols + T - 1) / T;
+  const int n_work = gram_grid(gram_tiles(g.n_tiles), g.B);
+  const dim3 grid(std::min(n_work, big ? 256 : 512));
+  if (big)
+    hipLaunchKernelGGL(gram256_rest_kernel, grid, dim3(kGram256Threads), 0, s, g, n_work);
+  else if (dtype == 1)
+    hipLaunchKernelGGL(gram_rest_kernel<BF16>, grid, dim3(kGramThreads), 0, s, g, n_work);
+  else
+    hipLaunchKernelGGL(gram_rest_kernel<F32>, grid, dim3(kGramThreads), 0, s, g, n_work);
   return hipGetLastError();
 }
 

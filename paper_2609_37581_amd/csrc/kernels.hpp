@@ -200,8 +200,11 @@ constexpr int kNormGapMaxD = 1 << 18;  // a gap of 0.01
 constexpr float kMaskMargin = 3.1f;    // 3 / (1 - 2 e)
 constexpr float kCosRounding = 4 * 5.9604645e-8f;
 bool gram256_ok(int dtype, int N, int row_bytes);  // 256-row tiles can be used
-// G of all N tokens; with ctrl, of the samples that are not finished.
+// G of all N tokens.
 hipError_t launch_gram_full(const GramArgs& g, int dtype, hipStream_t s);
+// G of the tokens that are no pivots (cols), and their inv_norm, in the samples
+// that are not finished.
+hipError_t launch_gram_rest(const GramArgs& g, int dtype, hipStream_t s);
 // G of the listed tokens (rows).
 hipError_t launch_gram_pool(const GramArgs& g, int dtype, hipStream_t s);
 // Maxima, by tiles of 128 x 128, or, where gram256_ok, 256 x 256 or 256 x 192.
@@ -214,13 +217,13 @@ hipError_t launch_gram_norms(const GramArgs& g, hipStream_t s);
 
 // How the K_d picks are made (see pick_plan).
 struct PickPlan {
-  int rounds;                // pool rounds before the full Gram matrix (0: none)
+  int rounds;                // pool rounds (0: none, and the Gram matrix of all tokens)
   int C, ldc;                // pool size, row stride of its Gram matrix
   int mask_words;            // 32-bit words of a row of its mask, a multiple of 4
   int row_tile, col_tile;    // tile of the first round's distances (later: 128 x 128)
-  int ldg;                   // row stride of the full Gram matrix
+  int n_gram, ldg;           // tokens of the Gram matrix without or after the rounds, its row stride
   int n_psplit;              // pivot splits of the initial distances over the full Gram matrix
-  size_t gram_floats(int N) const;  // floats of a sample's Gram matrix, full or of the pool
+  size_t gram_floats() const;  // floats of a sample's Gram matrix, of n_gram tokens or of the pool
 };
 constexpr int kRoundTile = 128;  // row tile of the products over pools and picks
 PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes);
@@ -231,7 +234,7 @@ struct PickArgs {
   const int32_t* pivots;     // [B,K_r] ascending
   const int32_t* rest;       // [B,R] ascending, the other tokens (pool rounds)
   float* inv_norm;           // [B,N]
-  float* G;                  // [B,N,ldg], or [B,C,ldc]
+  float* G;                  // [B,n_gram,ldg], or [B,C,ldc]
   float* part;               // [n_psplit,B,N]: per split, max over its pivots j of G_ij / ||z_j||
   int32_t* ctrl;             // [B,kPickCtrl]
   // pool rounds

@@ -13,9 +13,10 @@
 // the top of that order: a round takes the C farthest tokens, forms their Gram
 // matrix, and picks among them until a token outside this pool could be
 // farther.  Distances are then brought up to date and the next round follows.
-// Where the rounds do not suffice (tokens in many large clusters), and where
-// the problem is so small that a round saves nothing, the picks are made over
-// the Gram matrix of all tokens.
+// Where the rounds do not suffice (tokens in many large clusters, slow changes
+// over the image), the rest of the picks is made over the Gram matrix of all tokens
+// but the pivots, and where the problem is so small that a round saves nothing,
+// all picks are made over the Gram matrix of all tokens.
 #include <algorithm>
 #include <climits>
 
@@ -336,6 +337,27 @@ __device__ __forceinline__ int batch_picks(int m, int limit, uint32_t out, const
   return k;
 }
 
+// Vectors of CH floats.
+template <int CH>
+struct Chunk;
+template <>
+struct Chunk<1> {
+  typedef float T;
+  static __device__ __forceinline__ float at(const T& v, int) { return v; }
+};
+template <>
+struct Chunk<2> {
+  typedef float2 T;
+  static __device__ __forceinline__ float at(const T& v, int i) { return i ? v.y : v.x; }
+};
+template <>
+struct Chunk<4> {
+  typedef float4 T;
+  static __device__ __forceinline__ float at(const T& v, int i) {
+    return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w));
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Picks of a round, over the pool.  Distances are those of the Gram matrix
 // (its diagonal gives the norms).  Few pairs matter: entry i is brought nearer
@@ -529,31 +551,12 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
 
 // ---------------------------------------------------------------------------
 // Picks over the Gram matrix of all tokens, from the pivots' partial maxima, or
-// from where the rounds stopped (after_rounds).  The keys stay in registers:
-// element e of thread t is token (e / CH) * CH * 1024 + t * CH + e % CH, so that
-// rows of G load as vectors of CH values, up to U rows at a time.
+// (REST) over that of the tokens that are no pivots (a.rest), from where the rounds
+// stopped.  The keys stay in registers: element e of thread t is row
+// (e / CH) * CH * 1024 + t * CH + e % CH of the matrix, so that its rows load as
+// vectors of CH values, up to U rows at a time.
 // ---------------------------------------------------------------------------
-template <int CH>
-struct Chunk;
-template <>
-struct Chunk<1> {
-  typedef float T;
-  static __device__ __forceinline__ float at(const T& v, int) { return v; }
-};
-template <>
-struct Chunk<2> {
-  typedef float2 T;
-  static __device__ __forceinline__ float at(const T& v, int i) { return i ? v.y : v.x; }
-};
-template <>
-struct Chunk<4> {
-  typedef float4 T;
-  static __device__ __forceinline__ float at(const T& v, int i) {
-    return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w));
-  }
-};
-
-template <int E>
+template <int E, bool REST>
 __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
   constexpr int CH = E < 4 ? E : 4;        // entries per vector
   constexpr int NR = E / CH;               // vectors per thread and row
@@ -561,14 +564,15 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
   typedef typename Chunk<CH>::T Vec;
   __shared__ PickShared sh;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int N = a.N, ldg = a.p.ldg, K_d = a.K_d;
+  const int N = REST ? a.R : a.N, ldg = a.p.ldg, K_d = a.K_d;
   if (picks_done(a, b)) return;
   const int32_t* ctrl = a.ctrl + b * kPickCtrl;
-  const bool after_rounds = a.p.rounds > 0;
-  const int t0 = ctrl[kCtrlPicks];
+  const int t0 = REST ? ctrl[kCtrlPicks] : 0;
   int t = t0;
   const float* G = a.G + (size_t)b * N * ldg;
-  const float* inv_norm = a.inv_norm + (size_t)b * N;
+  const int32_t* rest = a.rest + (size_t)b * a.R;
+  auto token = [&](int c) { return REST ? rest[c] : c; };  // of row c < N
+  const float* inv_norm = a.inv_norm + (size_t)b * a.N;
   int32_t* picks = a.picks + (size_t)b * K_d;
   auto entry = [&](int e) { return (e / CH) * CH * kSelThreads + tid * CH + e % CH; };
   // selected tokens and those past N hold key 0: they never win, and the row
@@ -576,21 +580,21 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
   float iz[E];
   uint32_t key[E];
   const uint32_t inf_key = f2key(INFINITY);
-  mark_selected(a, b, 0, sh);
+  if (!REST) mark_selected(a, b, 0, sh);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int c = entry(e), cc = min(c, N - 1);
-    iz[e] = inv_norm[cc];
+    const int c = entry(e), cc = min(c, N - 1), tok = token(cc);
+    iz[e] = inv_norm[tok];
     float mx, least = INFINITY;
-    if (after_rounds) {
-      mx = a.near_piv[(size_t)b * N + cc];
-      least = a.near_pick[(size_t)b * N + cc];
+    if (REST) {
+      mx = a.near_piv[(size_t)b * a.N + tok];
+      least = a.near_pick[(size_t)b * a.N + tok];
     } else {
       mx = a.part[(size_t)b * N + cc];
       for (int sp = 1; sp < a.p.n_psplit; ++sp) mx = fmaxf(mx, a.part[((size_t)sp * a.B + b) * N + cc]);
     }
     const float d = 1.f - mx * iz[e];
-    const bool sel = c >= N || ((sh.bits[cc >> 5] >> (cc & 31)) & 1u) || least == -INFINITY;
+    const bool sel = c >= N || (REST ? least == -INFINITY : (sh.bits[cc >> 5] >> (cc & 31)) & 1u);
     const uint32_t k = f2key(least < d ? least : d);
     key[e] = sel || k > inf_key ? 0u : k;
   }
@@ -618,13 +622,22 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
       }
     }
   };
-  if (after_rounds) {  // the last round's picks are not yet in the distances
+  if (REST) {  // the last round's picks are not yet in the distances
     for (int p0 = ctrl[kCtrlRound]; p0 < t0; p0 += kBatch) {
       const int np = min(kBatch, t0 - p0);
       __syncthreads();
       if (tid < np) {
-        sh.pc[tid] = min(max(picks[p0 + tid], 0), N - 1);
-        sh.piz[tid] = inv_norm[sh.pc[tid]];
+        const int tok = min(max(picks[p0 + tid], 0), a.N - 1);
+        int lo = 0, hi = N - 1;  // the pick's row
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if (rest[mid] < tok)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        sh.pc[tid] = lo;
+        sh.piz[tid] = inv_norm[tok];
       }
       __syncthreads();
       take_rows(np);
@@ -685,8 +698,9 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
         const int c = sh.bc[won];
         sh.pc[lane] = c;
         sh.piz[lane] = sh.biz[won];
-        picks[t + lane] = c;
-        if (a.div_idx) a.div_idx[(size_t)b * K_d + t + lane] = c;
+        const int tok = token(c);
+        picks[t + lane] = tok;
+        if (a.div_idx) a.div_idx[(size_t)b * K_d + t + lane] = tok;
       }
     }
     __syncthreads();
@@ -708,8 +722,8 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
 }
 
 // ---------------------------------------------------------------- launchers
-size_t PickPlan::gram_floats(int N) const {
-  return std::max((size_t)N * ldg, (size_t)C * ldc);
+size_t PickPlan::gram_floats() const {
+  return std::max((size_t)n_gram * ldg, rounds > 0 ? (size_t)C * ldc : 0);
 }
 
 // Time of a Gram launch in microseconds per 128-byte slab of the feature
@@ -731,6 +745,22 @@ static double gram_us256(long wgs, int cols = 256) { return (cols == 256 ? 1.72 
 // candidates behind, and the neediest sample of a batch decides.  Pool tokens that the K_d picks reach down
 // to, over K_d, on features of regions of 24 tokens: 1.2 with pivots 3/8 of
 // the tokens, 1.5 at 1/4, 2.0 at 3/16, 2.5-3.2 at 1/6, 8-11 at 1/12.
+//
+// How many rounds suffice depends on the tokens: one on features of small
+// regions or of no structure, 2 or 3 where few directions are far from the
+// pivots (large regions, clusters, copies), up to 7 where features change
+// slowly over the image; a round takes a launch each of four kernels even if it
+// finds nothing to do.  What the rounds leave costs the Gram matrix of the
+// other tokens on top, so:
+//  - No round where one saves less than a quarter and its pool holds less than
+//    two thirds of the tokens (64 x 576 tokens, 48 picks of 192: 345 -> 342 us with a
+//    round that suffices, 382 -> 515 with one that does not; 37 x 795, 22 of 88,
+//    pool 0.7: 234 -> 180 and 257 -> 338).
+//  - A second, and a third where the matrix takes more than 1.5 ms, while the estimate with all of them in vain is within
+//    1.4 times the full matrix.  16 x 2880 tokens, 160 of 640 (full
+//    matrix 935-1008 us): one round 490, in vain 1135; three 505 and 1465.
+//    4 x 16,384, 1024 of 4096 (6420-6590): three 1672, in vain 6275.  2 x 20,000, 500
+//    of 2000 (2840-3210): three 531, in vain 3720.
 // (TREVS_PICK_ROUNDS: a number of rounds for measurements, whatever the estimate)
 #ifndef TREVS_PICK_ROUNDS
 #define TREVS_PICK_ROUNDS -1
@@ -739,15 +769,17 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
   PickPlan p{};
   auto up = [](long x, long m) { return (x + m - 1) / m; };
   auto tri = [](long n) { return n * (n + 1) / 2; };
-  p.ldg = (int)up(N, 4) * 4;
   p.n_psplit = std::min(std::max(K_r / 256, 1), 8);  // about 256 pivots each
   const int R = N - K_r;
   const bool big = gram256_ok(dtype, N, row_bytes);
   const int d = row_bytes / (dtype == 1 ? 2 : 4);
   const double slabs = up(row_bytes, 128);
-  // stores of G at 4 TB/s, the initial distances; a pick reads a row at 37 GB/s
-  const double full = slabs * (big ? gram_us256(B * tri(up(N, 256))) : gram_us128(B * tri(up(N, 128)), dtype)) +
-                      B * 4e-6 * N * N / 4 + 15 + K_d * (0.25 + N * 4 / 37e3);
+  // a square Gram matrix, its stores at 4 TB/s, the initial distances; a pick reads a row at 37 GB/s
+  auto square = [&](long n) {
+    return slabs * (big ? gram_us256(B * tri(up(n, 256))) : gram_us128(B * tri(up(n, 128)), dtype)) +
+           B * 1e-6 * n * n + 15 + K_d * (0.25 + n * 4 / 37e3);
+  };
+  const double full = square(N);
   long ct = up(9L * K_d / 4, kRoundTile);
   const long room = 5L * K_r > N || dtype != 1 ? 256 : 512;
   while (B * tri(ct + 1) <= room) ++ct;
@@ -760,12 +792,20 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
   p.mask_words = (int)up(p.C, 128) * 4;
   p.row_tile = big && r256 < r128 ? 256 : 128;
   p.col_tile = p.row_tile == 128 ? 128 : (r256n < r256w ? 192 : 256);
-  // the pivots' norms, the pool selection, rounds that find nothing left to do
-  const double pool = slabs * ((p.row_tile == 256 ? r256 : r128) + gram_us128(B * tri(up(p.C, 128)), dtype)) +
-                      (dtype == 1 ? 0.3 * slabs : 0) + 10 + R / 700 + (p.C < R ? 27 : 0) + K_d * 0.35;
-  p.rounds = pool < full && K_d <= kMaxPoolPicks && d <= kNormGapMaxD ? (full > 1500 ? 3 : 2) : 0;
-  if (TREVS_PICK_ROUNDS >= 0 && K_d <= kMaxPoolPicks) p.rounds = TREVS_PICK_ROUNDS;
-  if (p.C >= R) p.rounds = std::min(p.rounds, 1);
+  // the pivots' norms, the pool selection, launches that find nothing left to do
+  const double gram = slabs * gram_us128(B * tri(up(p.C, 128)), dtype);
+  const double pool = slabs * (p.row_tile == 256 ? r256 : r128) + gram + (dtype == 1 ? 0.3 * slabs : 0) + 10 +
+                      R / 700 + (p.C < R ? 10 : 0) + K_d * 0.35;
+  p.rounds = pool < full && K_d <= kMaxPoolPicks && d <= kNormGapMaxD ? 1 : 0;
+  if (p.C < R) {
+    if (pool > 0.75 * full && 3 * p.C < 2 * R) p.rounds = 0;
+    // a round that ends early makes few picks
+    const double next = slabs * 1.25 * gram_us128(B * up(R, kRoundTile), dtype) + gram + 30 + R / 700;
+    while (p.rounds > 0 && p.rounds < (full > 1500 ? 3 : 2) && pool + p.rounds * next + square(R) <= 1.4 * full) ++p.rounds;
+  }
+  if (TREVS_PICK_ROUNDS >= 0 && K_d <= kMaxPoolPicks) p.rounds = p.C < R ? TREVS_PICK_ROUNDS : std::min(TREVS_PICK_ROUNDS, 1);
+  p.n_gram = p.rounds > 0 ? R : N;
+  p.ldg = (int)up(p.n_gram, 4) * 4;
   return p;
 }
 
@@ -811,14 +851,21 @@ hipError_t launch_picks(const PickArgs& a, const void* Z, int row_bytes, int dty
   }
   if (p.rounds > 0 && p.C >= a.R) return hipGetLastError();  // the pool held every token
   g.ldg = p.ldg;
-  if ((err = launch_gram_full(g, dtype, s)) != hipSuccess) return err;
-  if (p.rounds == 0)
-    hipLaunchKernelGGL(fps_init_kernel, dim3((a.N + kFpsInitThreads - 1) / kFpsInitThreads, a.B, p.n_psplit),
-                       dim3(kFpsInitThreads), 0, s, a);
-#define CALL(E_) \
-  case E_: hipLaunchKernelGGL(full_pick_kernel<E_>, dim3(a.B), dim3(kSelThreads), 0, s, a); break
+  err = p.rounds > 0 ? launch_gram_rest(g, dtype, s) : launch_gram_full(g, dtype, s);
+  if (err != hipSuccess) return err;
+#define CALL(E_, REST_) \
+  case E_: hipLaunchKernelGGL((full_pick_kernel<E_, REST_>), dim3(a.B), dim3(kSelThreads), 0, s, a); break
+  if (p.rounds > 0) {
+    switch (select_e(a.R)) {
+      CALL(1, true); CALL(2, true); CALL(4, true); CALL(8, true); CALL(16, true); CALL(32, true);
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(fps_init_kernel, dim3((a.N + kFpsInitThreads - 1) / kFpsInitThreads, a.B, p.n_psplit),
+                     dim3(kFpsInitThreads), 0, s, a);
   switch (select_e(a.N)) {
-    CALL(1); CALL(2); CALL(4); CALL(8); CALL(16); CALL(32);
+    CALL(1, false); CALL(2, false); CALL(4, false); CALL(8, false); CALL(16, false); CALL(32, false);
     default: return hipErrorInvalidValue;
   }
 #undef CALL

@@ -188,6 +188,41 @@ def test_picks_of_rounds_and_of_the_full_matrix(N, d, clusters, spread, zeros):
     assert np.array_equal(picks[0], picks[1][:, :192])
 
 
+@pytest.mark.parametrize("B,N,d,K,k_div,dtype,spread", [
+    (2, 5003, 264, 901, 225, "bf16", 0.02),  # 256-row tiles, rows of G not a multiple of four
+    (8, 1999, 264, 400, 100, "bf16", 0.02),  # 128-row tiles
+    (4, 3001, 260, 600, 150, "f32", 0.05),
+    (2, 5003, 264, 901, 225, "bf16", 1.0),   # the rounds suffice
+])
+def test_picks_of_slowly_changing_features(B, N, d, K, k_div, dtype, spread):
+    """Features that change slowly over the image, the pivots at its beginning: a pool
+    holds runs of near tokens and gives few picks, and most are made over the Gram
+    matrix of the tokens that are no pivots.  In bf16 they are, bit for bit, the
+    beginning of those over the matrix of all tokens (more than 2048 picks)."""
+    rng = np.random.default_rng(N + d)
+    x = np.arange(N) / 64.0
+    i, f = x.astype(int), (x % 1.0)[None, :, None]
+    knots = rng.standard_normal((B, N // 64 + 2, d))
+    Z = knots[:, i] * (1 - f) + knots[:, i + 1] * f + spread * rng.standard_normal((B, N, d))
+    Z = np.ascontiguousarray(Z, dtype=np.float32)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Zt = torch.from_numpy(Z).to(dt)
+    cls = torch.zeros((B, 1, N))
+    cls[:, :, :K - k_div] = 8.0
+    picks = []
+    for n in (k_div, 2100)[:2 if N > 4500 else 1]:
+        print(f"[picks-smooth] B={B} N={N} d={d} K_r={K - k_div} K_d={n} {dtype} spread={spread}", flush=True)
+        call = trevs.Prellm(cls.to(dt).cuda(), Zt.cuda(), torch.ones((B, 1, d), dtype=dt, device="cuda"),
+                            k_keep=K - k_div + n, k_div=n, textual_ratio=0.0, ratio_mode="budget")
+        call()
+        picks.append(call.div_idx.cpu().numpy())
+    if dtype == "bf16" and len(picks) == 2:
+        assert np.array_equal(picks[0], picks[1][:, :k_div])
+    for b in range(B):
+        assert np.unique(picks[0][b]).size == k_div, b
+        check_fps_picks(Zt[b].double().numpy(), np.arange(K - k_div), picks[0][b])
+
+
 @pytest.mark.parametrize("d,dtype", [(1032, "bf16"), (1024, "bf16"), (1028, "f32")])
 def test_relevance_text_lengths_at_block_edges(d, dtype):
     """Question lengths around the 32-row text blocks (the blocks past the last
