@@ -489,6 +489,7 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
     // (marks cluster, so a wave takes a row's nonzero words two at a time, a
     // lane to a bit)
     for (int q = wave; q < np; q += kSelWaves) {
+      if (*(volatile int*)&n_hits > kHits) break;  // too many for the list
       const uint32_t* row = reinterpret_cast<const uint32_t*>(mrow[sh.pslot[q]]);
       for (int w0 = 0; w0 < 4 * mw4; w0 += kWave) {
         unsigned long long words = __ballot(w0 + lane < 4 * mw4 && row[min(w0 + lane, 4 * mw4 - 1)] != 0u);
@@ -521,10 +522,29 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
     };
     if (n_hits <= kHits) {
       for (int h = tid; h < n_hits; h += kSelThreads) take(hits[h] >> 16, hits[h] & 0xffffu);
-    } else {  // most pairs marked: whole rows
-#pragma unroll 4
-      for (int q = 0; q < np; ++q)
-        for (int c = tid; c < C; c += kSelThreads) take(q, c);
+    } else {  // most pairs marked: whole rows, eight vectors of four entries in flight
+      constexpr int U = 8;
+      const int nv = (C + 3) / 4, total = np * nv;
+      for (int i0 = tid; i0 < total; i0 += U * kSelThreads) {
+        float4 g[U];
+        int at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = min(i0 + u * kSelThreads, total - 1), q = i / nv;
+          at[u] = q << 16 | (i - q * nv) * 4;
+          g[u] = *reinterpret_cast<const float4*>(G + (size_t)sh.pc[q] * ldc + (at[u] & 0xffff));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int c0 = at[u] & 0xffff;
+          const float izq = sh.piz[at[u] >> 16];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t k = dist_key(1.f - Chunk<4>::at(g[u], j) * iz[c0 + j] * izq);
+            if (c0 + j < C && k < key[c0 + j]) atomicMin(&key[c0 + j], k);  // (a key read late is too large)
+          }
+        }
+      }
     }
     t += np;
     // a batch that is far from full asks for a wider scale

@@ -36,6 +36,8 @@ CASES = {
     "unfinished-odd-f32": (16387, 20, 600, 150, "f32", [([(4500, 0.02)] * 3, 0, 0)]),
     "copies-and-zeros-bf16": (6000, 128, 640, 160, "bf16", [([], 2500, 0), ([], 300, 900)]),
     "pool-of-all-bf16": (2304, 1024, 1152, 288, "bf16", [([(500, 0.1)], 100, 3)] * 2),
+    # one tight cluster: most pairs are marked, and rows of G are no multiple of four
+    "pool-of-one-cluster-bf16": (2305, 1024, 800, 200, "bf16", [([(1700, 0.05)], 0, 0), ([(850, 0.05)] * 2, 0, 0)]),
     "pool-tail-f32": (3000, 1028, 700, 175, "f32", [([(200, 0.1)] * 4, 50, 1)]),
 }
 
