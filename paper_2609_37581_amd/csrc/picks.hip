@@ -92,52 +92,60 @@ __global__ __launch_bounds__(kSelThreads) void pool_select_kernel(PickArgs a, in
   float* near_piv = a.near_piv + (size_t)b * a.N;
   float* near_pick = a.near_pick + (size_t)b * a.N;
   uint32_t* mx = a.mx + (size_t)b * R;
-  float d[E], v[E];
-  int tok[E];
+  uint32_t key[E];
+  // groups of 16 tokens a thread (32 at once spilled 252 registers)
+  constexpr int G = E < 16 ? E : 16;
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = min(e * kSelThreads + tid, R - 1);
-    d[e] = key2f(mx[i]);
-    tok[e] = rest[i];
-  }
+  for (int e0 = 0; e0 < E; e0 += G) {
+    float d[G], v[G];
+    int tok[G];
+    const int first = e0 * kSelThreads + tid;
 #pragma unroll
-  for (int e = 0; e < E; ++e)  // the next round's maxima start over
-    if (e * kSelThreads + tid < R) mx[e * kSelThreads + tid] = 0u;
-  if (round == 0) {
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (e * kSelThreads + tid < R) {
-        near_piv[tok[e]] = d[e];
-        near_pick[tok[e]] = INFINITY;
-      }
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = a.inv_norm[(size_t)b * a.N + tok[e]];
-#pragma unroll
-    for (int e = 0; e < E; ++e) d[e] = 1.f - d[e] * v[e];
-  } else {
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = near_pick[tok[e]];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      d[e] = -d[e] < v[e] ? -d[e] : v[e];
-      if (e * kSelThreads + tid < R) near_pick[tok[e]] = d[e];
+    for (int e = 0; e < G; ++e) {
+      const int i = min(first + e * kSelThreads, R - 1);
+      d[e] = key2f(mx[i]);
+      tok[e] = rest[i];
     }
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = 1.f - near_piv[tok[e]] * a.inv_norm[(size_t)b * a.N + tok[e]];
+    for (int e = 0; e < G; ++e)  // the next round's maxima start over
+      if (first + e * kSelThreads < R) mx[first + e * kSelThreads] = 0u;
+    if (round == 0) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) d[e] = d[e] < v[e] ? d[e] : v[e];
+      for (int e = 0; e < G; ++e)
+        if (first + e * kSelThreads < R) {
+          near_piv[tok[e]] = d[e];
+          near_pick[tok[e]] = INFINITY;
+        }
+#pragma unroll
+      for (int e = 0; e < G; ++e) v[e] = a.inv_norm[(size_t)b * a.N + tok[e]];
+#pragma unroll
+      for (int e = 0; e < G; ++e) d[e] = 1.f - d[e] * v[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < G; ++e) v[e] = near_pick[tok[e]];
+#pragma unroll
+      for (int e = 0; e < G; ++e) {
+        d[e] = -d[e] < v[e] ? -d[e] : v[e];
+        if (first + e * kSelThreads < R) near_pick[tok[e]] = d[e];
+      }
+#pragma unroll
+      for (int e = 0; e < G; ++e) v[e] = 1.f - near_piv[tok[e]] * a.inv_norm[(size_t)b * a.N + tok[e]];
+#pragma unroll
+      for (int e = 0; e < G; ++e) d[e] = d[e] < v[e] ? d[e] : v[e];
+    }
+#pragma unroll
+    for (int e = 0; e < G; ++e) key[e0 + e] = f2key(d[e]);
+    if (E > G) __builtin_amdgcn_sched_barrier(0);
   }
-  uint32_t key[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) key[e] = f2key(d[e]);
   int32_t* cand = a.cand + (size_t)b * C;
   float* cand_cos = a.cand_cos + (size_t)b * C;
   float* cand_piv = a.cand_piv + (size_t)b * C;
   float* cand_pick = a.cand_pick + (size_t)b * C;
   auto put = [&](int at, int e) {
-    const float piv = near_piv[tok[e]], pick = near_pick[tok[e]];
-    cand[at] = tok[e];
-    cand_cos[at] = fmaxf(piv * a.inv_norm[(size_t)b * a.N + tok[e]], 1.f - pick);
+    const int tok = rest[e * kSelThreads + tid];
+    const float piv = near_piv[tok], pick = near_pick[tok];
+    cand[at] = tok;
+    cand_cos[at] = fmaxf(piv * a.inv_norm[(size_t)b * a.N + tok], 1.f - pick);
     cand_piv[at] = piv;
     cand_pick[at] = pick;
   };
@@ -583,6 +591,11 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
   constexpr int U = E <= 2 ? 16 : 32 / E;  // rows in flight
   typedef typename Chunk<CH>::T Vec;
   __shared__ PickShared sh;
+  // inverse norms: in registers, or, with 32 entries a thread (where keys, norms
+  // and a row spilled 70 to 110 registers), in LDS
+  constexpr bool IN_LDS = E > 16;
+  __shared__ __attribute__((aligned(16))) float iz_lds[IN_LDS ? E * kSelThreads : 1];
+  float iz_reg[IN_LDS ? 1 : E];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int N = REST ? a.R : a.N, ldg = a.p.ldg, K_d = a.K_d;
   if (picks_done(a, b)) return;
@@ -597,14 +610,18 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
   auto entry = [&](int e) { return (e / CH) * CH * kSelThreads + tid * CH + e % CH; };
   // selected tokens and those past N hold key 0: they never win, and the row
   // updates (a minimum) keep them there; so do tokens whose distance is not a number
-  float iz[E];
+  auto inv = [&](int e) { return IN_LDS ? iz_lds[entry(e)] : iz_reg[IN_LDS ? 0 : e]; };
   uint32_t key[E];
   const uint32_t inf_key = f2key(INFINITY);
   if (!REST) mark_selected(a, b, 0, sh);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int c = entry(e), cc = min(c, N - 1), tok = token(cc);
-    iz[e] = inv_norm[tok];
+    const float iz = inv_norm[tok];
+    if (IN_LDS)
+      iz_lds[c] = iz;
+    else
+      iz_reg[IN_LDS ? 0 : e] = iz;
     float mx, least = INFINITY;
     if (REST) {
       mx = a.near_piv[(size_t)b * a.N + tok];
@@ -613,7 +630,7 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
       mx = a.part[(size_t)b * N + cc];
       for (int sp = 1; sp < a.p.n_psplit; ++sp) mx = fmaxf(mx, a.part[((size_t)sp * a.B + b) * N + cc]);
     }
-    const float d = 1.f - mx * iz[e];
+    const float d = 1.f - mx * iz;
     const bool sel = c >= N || (REST ? least == -INFINITY : (sh.bits[cc >> 5] >> (cc & 31)) & 1u);
     const uint32_t k = f2key(least < d ? least : d);
     key[e] = sel || k > inf_key ? 0u : k;
@@ -638,7 +655,7 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
         const float izw = sh.piz[min(q0 + u, np - 1)];
 #pragma unroll
         for (int e = 0; e < E; ++e)
-          key[e] = min(key[e], dist_key(1.f - Chunk<CH>::at(g[u][e / CH], e % CH) * iz[e] * izw));
+          key[e] = min(key[e], dist_key(1.f - Chunk<CH>::at(g[u][e / CH], e % CH) * inv(e) * izw));
       }
     }
   };
@@ -688,7 +705,7 @@ __global__ __launch_bounds__(kSelThreads) void full_pick_kernel(PickArgs a) {
         const int at = atomicAdd(&sh.n_batch, 1);
         if (at < kBatch) {
           sh.bkey[at] = key[e];
-          sh.biz[at] = iz[e];
+          sh.biz[at] = inv(e);
           sh.bc[at] = c;
         }
       } else {
@@ -780,7 +797,7 @@ static double gram_us256(long wgs, int cols = 256) { return (cols == 256 ? 1.72 
 //    1.4 times the full matrix.  16 x 2880 tokens, 160 of 640 (full
 //    matrix 935-1008 us): one round 490, in vain 1135; three 505 and 1465.
 //    4 x 16,384, 1024 of 4096 (6420-6590): three 1672, in vain 6275.  2 x 20,000, 500
-//    of 2000 (2840-3210): three 531, in vain 3720.
+//    of 2000 (2840-3210): three 515, in vain 3510.
 // (TREVS_PICK_ROUNDS: a number of rounds for measurements, whatever the estimate)
 #ifndef TREVS_PICK_ROUNDS
 #define TREVS_PICK_ROUNDS -1
