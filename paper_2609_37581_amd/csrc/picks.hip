@@ -798,10 +798,6 @@ static double gram_us256(long wgs, int cols = 256) { return (cols == 256 ? 1.72 
 //    matrix 935-1008 us): one round 490, in vain 1135; three 505 and 1465.
 //    4 x 16,384, 1024 of 4096 (6420-6590): three 1672, in vain 6275.  2 x 20,000, 500
 //    of 2000 (2840-3210): three 515, in vain 3510.
-// (TREVS_PICK_ROUNDS: a number of rounds for measurements, whatever the estimate)
-#ifndef TREVS_PICK_ROUNDS
-#define TREVS_PICK_ROUNDS -1
-#endif
 PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
   PickPlan p{};
   auto up = [](long x, long m) { return (x + m - 1) / m; };
@@ -840,7 +836,6 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
     const double next = slabs * 1.25 * gram_us128(B * up(R, kRoundTile), dtype) + gram + 30 + R / 700;
     while (p.rounds > 0 && p.rounds < (full > 1500 ? 3 : 2) && pool + p.rounds * next + square(R) <= 1.4 * full) ++p.rounds;
   }
-  if (TREVS_PICK_ROUNDS >= 0 && K_d <= kMaxPoolPicks) p.rounds = p.C < R ? TREVS_PICK_ROUNDS : std::min(TREVS_PICK_ROUNDS, 1);
   p.n_gram = p.rounds > 0 ? R : N;
   p.ldg = (int)up(p.n_gram, 4) * 4;
   return p;
