@@ -180,9 +180,9 @@ def run_analysis(args, w):
         if all_events:
             sens(stream, events=ev.handles[base:base + nk])
         else:
-            # profile launches of both questions only (slots 4,5 and 10,11)
+            # the profile launch of both questions only (slots 4, 5)
             e = [None] * nk
-            for j in (4, 5, 10, 11):
+            for j in (4, 5):
                 e[j] = ev.handles[base + j]
             sens(stream, events=e)
         if all_events:
@@ -203,21 +203,21 @@ def run_analysis(args, w):
     torch.cuda.synchronize()
     t_wall = time.perf_counter() - t_wall
     ms_step = start.elapsed_time(stop) / args.steps
-    prof_ms = [sum(ev.elapsed_ms(i * per + a, i * per + a + 1) for i in range(args.steps)) / args.steps
-               for a in (4, 10)]
+    prof_ms = sum(ev.elapsed_ms(i * per + 4, i * per + 5) for i in range(args.steps)) / args.steps
     nb_steps = min(args.steps, 20)
     for i in range(nb_steps):
         step(i, all_events=True)
     torch.cuda.synchronize()
     names = list(trevs.SENSITIVITY_KERNELS) + ["topk_spearman"]
-    kern_ms = {n: 0.0 for n in names}
+    kern_ms = {n: 0.0 for n in names if n}
     for i in range(nb_steps):
         for j, n in enumerate(names):
-            kern_ms[n] += ev.elapsed_ms(i * per + 2 * j, i * per + 2 * j + 1) / nb_steps
+            if n:
+                kern_ms[n] += ev.elapsed_ms(i * per + 2 * j, i * per + 2 * j + 1) / nb_steps
     ev.close()
 
-    flops = [profile_flops(w, si["text_len0"]), profile_flops(w, si["text_len1"])]
-    achieved = (flops[0] + flops[1]) / ((prof_ms[0] + prof_ms[1]) * 1e-3) / 1e12
+    flops = profile_flops(w, si["text_len0"]) + profile_flops(w, si["text_len1"])
+    achieved = flops / (prof_ms * 1e-3) / 1e12
     peak = MFMA_PEAK_TFLOPS[w.dtype]
     result = {
         "metric": ANALYSIS_METRIC,
@@ -237,7 +237,7 @@ def run_analysis(args, w):
         "roofline": {"bound": "mfma", "kernel": "analysis.profile", "achieved": achieved,
                      "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": None,
                      "flops_per_launch": flops},
-        "profile_us": [m * 1e3 for m in prof_ms],
+        "profile_us": prof_ms * 1e3,
         "kernels_us_separate_pass": {n: round(v * 1e3, 3) for n, v in kern_ms.items()},
         "wall_s": t_wall,
     }

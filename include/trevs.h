@@ -35,7 +35,8 @@
  *   - Optional `events`: NULL, or an array of 2*TREVS_*_NUM_KERNELS
  *     hipEvent_t handles (entries may be NULL).  Event 2k is recorded on the
  *     stream right before kernel k of the call and event 2k+1 right after
- *     it, for per-kernel timing by the caller.
+ *     it, for per-kernel timing by the caller.  Kernels that a call does not
+ *     launch (see the limits below) leave both events next to each other.
  */
 #ifndef TREVS_H
 #define TREVS_H
@@ -60,9 +61,9 @@ typedef enum trevs_dtype { TREVS_F32 = 0, TREVS_BF16 = 1 } trevs_dtype;
 /* Implementation limits (TREVS_ERR_UNSUPPORTED beyond them). */
 #define TREVS_MAX_SELECT_N 65536 /* tokens ranked per sample by one top-K */
 #define TREVS_MAX_FPS_N 32768    /* tokens per sample with a diversity set (k_div > 0) */
-#define TREVS_PRELLM_NUM_KERNELS 5 /* prep, relevance, robust stats, fuse+top-K (+ diversity set), gather */
+#define TREVS_PRELLM_NUM_KERNELS 5 /* prep (none on small grids: the relevance launch does it), relevance, robust stats, fuse+top-K (+ diversity set), gather */
 #define TREVS_INLLM_NUM_KERNELS 5  /* t2v stats (+ causal rest keys), head variance, head set+token score, top-K, compaction */
-#define TREVS_SENSITIVITY_NUM_KERNELS 7 /* per question: t2v stats, head variance, profile; then Eq. (1) */
+#define TREVS_SENSITIVITY_NUM_KERNELS 7 /* both questions: t2v stats, head variance, profile; three without a launch; Eq. (1) */
 
 /* ------------------------------------------------------------------------
  * Stage 1 (pre-LLM), Sec. 4.1.  Per sample b:
@@ -245,8 +246,7 @@ typedef struct trevs_sensitivity_args {
   float* ts;                 /* OUT [B,H_q] text sensitivity */
   float* profile[2];         /* OPTIONAL OUT per question [B,H_q,K_in] s^c_h */
   float* head_var[2];        /* OPTIONAL OUT per question [B,H_q] u_h */
-  void* const* events;       /* OPTIONAL [2*TREVS_SENSITIVITY_NUM_KERNELS] hipEvent_t; both questions run
-                                in one launch each, bracketed by the first question's slots */
+  void* const* events;       /* OPTIONAL [2*TREVS_SENSITIVITY_NUM_KERNELS] hipEvent_t */
   int32_t softmax;           /* trevs_softmax, as in trevs_inllm_args (0 = VISUAL) */
 } trevs_sensitivity_args;
 

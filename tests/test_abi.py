@@ -291,3 +291,14 @@ def test_very_long_text_keeps_its_head_split():
     a = _inllm(dtype=trevs.TREVS_F32, B=1, S=8000, P=0, K_in=2000, T_max=6000, H_q=32, H_kv=8, n_keep_heads=16,
                k_keep=1)
     assert trevs.lib().trevs_inllm_workspace_size(ctypes.byref(a)) > 4 * 6000 * 2000 * 4 - 1
+
+
+def test_kernel_names_match_the_event_slots():
+    """One name per pair of event slots; a slot without a launch (both questions of
+    the text sensitivity share theirs) has none, and no launch is named twice."""
+    for names, n in ((trevs.PRELLM_KERNELS, trevs.PRELLM_NUM_KERNELS), (trevs.INLLM_KERNELS, trevs.INLLM_NUM_KERNELS),
+                     (trevs.SENSITIVITY_KERNELS, trevs.SENSITIVITY_NUM_KERNELS)):
+        assert len(names) == n
+        named = [x for x in names if x]
+        assert len(set(named)) == len(named)
+    assert [x for x in trevs.SENSITIVITY_KERNELS if x] == ["t2v_stats", "head_var", "profile", "sensitivity"]
