@@ -279,9 +279,21 @@ InllmPlan inllm_plan_of(const trevs_inllm_args* a, bool coarse) {
   off = align_up(off + (size_t)a->B * a->K_in * sizeof(float));
   const int vt = score_tile_tokens(a->dtype, a->d_head);
   p.n_vtiles = (a->K_in + vt - 1) / vt;
-  // rows over 256 bytes: 64-token tiles halve the tiles and so double the splits
-  const int st = coarse && a->d_head * elem_bytes(a->dtype) > 256 ? 32 : vt;
-  const int hs = score_head_splits(a->B, (a->K_in + st - 1) / st, a->n_keep_heads);
+  // Rows over 256 bytes: 64-token tiles halve the tiles and so double the splits,
+  // except where that costs more than it gives (us a call, double against not):
+  //  - bf16, where 32-token tiles need no split: the merge pass (8 heads, 4
+  //    kept, 6 x 855 keys, 128 text rows 54.1 and 45.2, 32 rows 33.4 and 30.5; 16
+  //    heads, 8 kept, 4 x 2048 keys 65.4 and 63.2, at 86 rows 51.6 and 51.1);
+  //  - fp32, two heads a split and more than 96 text rows: the head sums (1 x 1024
+  //    keys, 128 rows 61.3 and 58.3; 2 x 576 69.1 and 65.9; up to 86 rows -3 to 4%).
+  // Everywhere else it gains, up to a quarter (fp32, 6 x 855 keys 128 and 173).
+  int hs = score_head_splits(a->B, p.n_vtiles, a->n_keep_heads);
+  if (a->d_head * elem_bytes(a->dtype) > 256) {
+    const int h32 = score_head_splits(a->B, (a->K_in + 31) / 32, a->n_keep_heads);
+    auto per = [&](int n) { return (a->n_keep_heads + n - 1) / n; };
+    const bool bf16 = a->dtype == TREVS_BF16;
+    if (coarse || (bf16 ? h32 == 1 : a->T_max > 96 && per(h32) == 2 && per(hs) == 1)) hs = h32;
+  }
   p.hps = (a->n_keep_heads + hs - 1) / hs;
   p.n_hsplit = (a->n_keep_heads + p.hps - 1) / p.hps;  // no split is empty
   if ((size_t)a->B * p.n_hsplit * a->T_max * a->K_in * sizeof(float) > (size_t(256) << 20)) {

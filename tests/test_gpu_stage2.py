@@ -83,6 +83,12 @@ CASES = {
     # 3 + 2 over two workgroups per tile
     "b64-unsplit-score-bf16": WORKLOADS["llava15-b64-bf16"].with_(H_q=8, H_kv=8, n_keep=4, D=64),
     "b32-head-split-score-bf16": WORKLOADS["sweep-llava15-b32-bf16"].with_(H_q=8, H_kv=8, n_keep=5, D=64),
+    # rows of 512 bytes whose heads are split as for 32-token tiles: 80 tiles of
+    # 64 tokens unsplit, and 9 tiles with two heads a split
+    "bf16-dh256-unsplit-score": WORKLOADS["llava15-b64-bf16"].with_(
+        B=5, K1=1001, K2=250, M_max=70, H_q=8, H_kv=1, d_h=256, D=64, n_keep=4, N=1225, grid=35),
+    "f32-two-heads-a-split": WORKLOADS["llava15-b1-f32"].with_(
+        B=1, K1=570, K2=100, M_max=101, H_q=32, H_kv=8, D=64, n_keep=16),
 }
 
 
