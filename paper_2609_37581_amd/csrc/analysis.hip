@@ -358,10 +358,12 @@ __global__ __launch_bounds__(64) void spearman_final_kernel(SpearmanArgs a) {
 // pairs instead costs 8 K^2 lane operations: the top 4096 of 16,384 tokens,
 // 4 samples, took 42 us in three launches (selection 12, pairs 25, final 4.5)
 // and take 34 here; a bitonic sort and binary searches in one workgroup took 70.
-// Larger sets, which do not fit a workgroup's registers, keep the pairs, and so do
-// those below kBinRanksMin, whose pairs are few (a call with both questions of
-// the text sensitivity: top 3888 77.8 -> 72.8 us, top 2326 75.2 -> 74.1, top 1586
-// 80.8 -> 82.6, top 607 46.0 -> 52.4).
+// Sets below kBinRanksMin keep the pairs, which are few (a call with both questions
+// of the text sensitivity: top 3888 77.8 -> 72.8 us, top 2326 75.2 -> 74.1, top
+// 1586 80.8 -> 82.6, top 607 46.0 -> 52.4).  So do sets above kBinRanks: four
+// entries a thread and 16 bytes of LDS an entry (64 of 160 KB) are what this is
+// laid out for, and more entries were not tried (4 samples of 16,384, ranks
+// alone: top 4096 31 us, top 4097 54, top 8192 89).
 // ---------------------------------------------------------------------------
 constexpr int kBinRanks = 4096, kBinRanksMin = 2048;
 constexpr int kRankPerThread = kBinRanks / kSelThreads;
