@@ -61,7 +61,9 @@ typedef enum trevs_dtype { TREVS_F32 = 0, TREVS_BF16 = 1 } trevs_dtype;
 /* Implementation limits (TREVS_ERR_UNSUPPORTED beyond them). */
 #define TREVS_MAX_SELECT_N 65536 /* tokens ranked per sample by one top-K */
 #define TREVS_MAX_FPS_N 32768    /* tokens per sample with a diversity set (k_div > 0) */
-#define TREVS_PRELLM_NUM_KERNELS 5 /* prep (none on small grids: the relevance launch does it), relevance, robust stats, fuse+top-K (+ diversity set), gather */
+/* prep (none on small grids: the relevance launch does it), relevance, robust stats, fuse+top-K
+ * (+ diversity set), gather */
+#define TREVS_PRELLM_NUM_KERNELS 5
 #define TREVS_INLLM_NUM_KERNELS 5  /* t2v stats (+ causal rest keys), head variance, head set+token score, top-K, compaction */
 #define TREVS_SENSITIVITY_NUM_KERNELS 7 /* both questions: t2v stats, head variance, profile; three without a launch; Eq. (1) */
 

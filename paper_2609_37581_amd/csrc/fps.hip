@@ -216,8 +216,8 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int w) {
   int nj = a.N, ni = a.N;  // tokens along the rows and columns
   const int32_t *rows = nullptr, *cols = nullptr;
   bool none = false;
-  __shared__ float izr[MODE == kGramFull ? 1 : T], izc[MODE == kGramPool || MODE == kGramNext ? T : 1], xr[MODE == kGramPool ? T : 1],
-      xc[MODE == kGramPool ? T : 1];
+  __shared__ float izr[MODE == kGramFull || MODE == kGramRest ? 1 : T], izc[MODE == kGramPool || MODE == kGramNext ? T : 1];
+  __shared__ float xr[MODE == kGramPool ? T : 1], xc[MODE == kGramPool ? T : 1];
   if (MODE != kGramFull) {
     rows = cols = gram_list_rows<MODE>(a, b, nj);
     ni = nj;

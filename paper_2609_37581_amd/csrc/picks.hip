@@ -834,7 +834,8 @@ PickPlan pick_plan(int B, int N, int K_r, int K_d, int dtype, int row_bytes) {
     if (pool > 0.75 * full && 3 * p.C < 2 * R) p.rounds = 0;
     // a round that ends early makes few picks
     const double next = slabs * 1.25 * gram_us128(B * up(R, kRoundTile), dtype) + gram + 30 + R / 700;
-    while (p.rounds > 0 && p.rounds < (full > 1500 ? 3 : 2) && pool + p.rounds * next + square(R) <= 1.4 * full) ++p.rounds;
+    const int most = full > 1500 ? 3 : 2;
+    while (p.rounds > 0 && p.rounds < most && pool + p.rounds * next + square(R) <= 1.4 * full) ++p.rounds;
   }
   p.n_gram = p.rounds > 0 ? R : N;
   p.ldg = (int)up(p.n_gram, 4) * 4;

@@ -846,7 +846,8 @@ RelPlan relevance_plan(int B, int N, int M_max, int row_bytes, int H, int n_seg)
   // 116.0 us a call either way) or costs registers (4 x 16,384: 156 -> 169 us).
   const int seg_len = N / n_seg;
   const long ns = std::min<long>(n_seg, (p.tile_tokens - 1) / seg_len + 2);
-  p.fused_stats = p.n_split > 1 && tiles * (p.n_split + 1) <= resident && H * ns <= kStatRows && H * ns * seg_len <= kStatValues;
+  p.fused_stats = p.n_split > 1 && tiles * (p.n_split + 1) <= resident && H * ns <= kStatRows &&
+                  H * ns * seg_len <= kStatValues;
   return p;
 }
 
