@@ -399,7 +399,10 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
   const int t0 = ctrl[kCtrlPicks];
   int t = t0;
   const float bound = __int_as_float(ctrl[kCtrlBound]);
-  const float floor = bound > -INFINITY ? bound + gap * fabsf(1.f - bound) : -INFINITY;
+  // what the norms may move a distance by, and its rounding with them (an ulp on
+  // either side of 1)
+  const float slack = gap * fabsf(1.f - bound);
+  const float floor = bound > -INFINITY ? bound + (slack > 0.f ? slack + 2.4e-7f : 0.f) : -INFINITY;
   const uint32_t floor_key = f2key(floor);
   const int32_t* cand = a.cand + (size_t)b * C;
   const float* G = a.G + (size_t)b * C * ldc;

@@ -190,6 +190,36 @@ def test_picks_of_rounds_and_of_the_full_matrix(N, d, clusters, spread, zeros):
     assert np.array_equal(picks[0], picks[1][:, :192])
 
 
+@pytest.mark.parametrize("cosine", [1e-5, 1e-4])
+def test_picks_among_distances_an_ulp_apart(cosine):
+    """Mutually orthogonal rows with one small cosine to the pivots: thousands of
+    distances within an ulp or two of each other, which the norms' rounding can
+    order either way.  The picks of a pool are those over all tokens, bit for bit."""
+    m, N, k_piv = 2048, 8192, 400
+    H = np.ones((1, 1))
+    while H.shape[0] < m:
+        H = np.block([[H, H], [H, -H]])
+    rng = np.random.default_rng(m)
+    Z = np.zeros((1, N, m + 8), dtype=np.float32)
+    c = rng.uniform(1.0, 2.0, N)
+    Z[0, :, :m] = H[rng.integers(0, 2000, N)] * c[:, None]
+    Z[0, :, m] = cosine * np.sqrt(m) * c
+    piv = rng.permutation(N)[:k_piv]
+    Z[0, piv] = 0.0
+    Z[0, piv, m] = rng.uniform(1.0, 2.0, k_piv)
+    cls = torch.zeros((1, 1, N))
+    cls[0, 0, torch.from_numpy(piv)] = 8.0
+    picks = []
+    for k_div in (192, 2100):
+        print(f"[picks-ulp] N={N} d={m + 8} cosine={cosine} K_d={k_div}", flush=True)
+        call = trevs.Prellm(cls.bfloat16().cuda(), torch.from_numpy(Z).bfloat16().cuda(),
+                            torch.ones((1, 1, m + 8), dtype=torch.bfloat16, device="cuda"), k_keep=k_piv + k_div,
+                            k_div=k_div, textual_ratio=0.0, ratio_mode="budget")
+        call()
+        picks.append(call.div_idx.cpu().numpy())
+    assert np.array_equal(picks[0], picks[1][:, :192])
+
+
 @pytest.mark.parametrize("B,N,d,K,k_div,dtype,spread", [
     (2, 5003, 264, 901, 225, "bf16", 0.02),  # 256-row tiles, rows of G not a multiple of four
     (8, 1999, 264, 400, 100, "bf16", 0.02),  # 128-row tiles
