@@ -408,15 +408,19 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
   const float* G = a.G + (size_t)b * C * ldc;
   const u32x4* mask = reinterpret_cast<const u32x4*>(a.mask) + (size_t)b * C * mw4;
   int32_t* picks = a.picks + (size_t)b * K_d;
-  for (int c = tid; c < C; c += kSelThreads) {
-    const float z = 1.f / fmaxf(sqrtf(fmaxf(G[(size_t)c * ldc + c], 0.f)), 1e-12f);
-    const float d = 1.f - a.cand_piv[(size_t)b * C + c] * z, dp = a.cand_pick[(size_t)b * C + c];
-    iz[c] = z;
-    key[c] = dp == -INFINITY ? 0u : f2key(dp < d ? dp : d);
-  }
   // a round over few candidates is short of NaN and selected entries alike:
   // keys of NaN distances (above infinity's) never win
   const uint32_t inf_key = f2key(INFINITY);
+  const bool tied = bound > -INFINITY && floor == bound;
+  int last = 0;  // entries below it may be picked at the floor
+  for (int c = tid; c < C; c += kSelThreads) {
+    const float z = 1.f / fmaxf(sqrtf(fmaxf(G[(size_t)c * ldc + c], 0.f)), 1e-12f);
+    const float d = 1.f - a.cand_piv[(size_t)b * C + c] * z, dp = a.cand_pick[(size_t)b * C + c];
+    const uint32_t k = dp == -INFINITY ? 0u : f2key(dp < d ? dp : d);
+    iz[c] = z;
+    key[c] = k > inf_key ? 0u : k;
+    if (tied && k == floor_key) last = c + 1;
+  }
   const float range0 = bound > -INFINITY ? -1.f : 2.f;  // down to the bound (-1), or anywhere (distances: 0..2)
   float range = range0;
   BatchScale s;
@@ -426,13 +430,8 @@ __global__ __launch_bounds__(kSelThreads) void pool_pick_kernel(PickArgs a, floa
     for (int c = tid; c < C; c += kSelThreads) f(key[c], c);
   };
   __syncthreads();
-  int last = 0;  // entries below it may be picked at the floor
-  for (int c = tid; c < C; c += kSelThreads) {
-    if (key[c] > inf_key) key[c] = 0u;
-    if (key[c] == floor_key && floor == bound) last = c + 1;
-  }
-  last = (int)block_max_u32((uint32_t)last, sh.red_out);
-  auto ok = [&](uint32_t k, int c) { return k > floor_key || (k == floor_key && c < last); };
+  if (tied) last = (int)block_max_u32((uint32_t)last, sh.red_out);  // uniform
+  auto ok = [&](uint32_t k, int c) { return k > (c < last ? floor_key - 1u : floor_key); };
   while (t < K_d) {
     uint32_t v = 0u;
     each([&](uint32_t k, int c) { v = ok(k, c) ? max(v, k) : v; });
